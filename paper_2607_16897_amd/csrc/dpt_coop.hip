@@ -80,16 +80,53 @@ __device__ __forceinline__ void wave_min_max(int& lo, int& hi) {
   lo = min(lo, (int)lane_xor_u<32>((uint32_t)lo)), hi = max(hi, (int)lane_xor_u<32>((uint32_t)hi));
 }
 
+// Where a lane of wave 0 finds its words when it polls the chunks of a stream:
+// the wave's 64 / NV lane groups read consecutive ranges of the chunks (group q
+// the q-th range, lane v word v), kPollBatch chunks per batch.  The offsets and
+// the marks of the words past the range's end are the same in every exchange of
+// a launch, so they are formed once: a poll round is its loads and two or three
+// instructions per word.  (Forming them in the round cost 105 instructions, 420
+// cycles of issue per round; the loads' latency is about 700.)
+struct PollLanes {
+  uint32_t off[kPollBatch];  // bytes from the buffer's start, first batch
+  float in[kPollBatch];      // 1: the word belongs to the range, 0: a repeat of its last chunk
+  int cb, ce;                // the range
+};
+
+template <int NV>
+__device__ __forceinline__ PollLanes poll_lanes(int nch) {
+  constexpr int G = 64 / NV;
+  const int lane = threadIdx.x & 63, q = lane / NV, v = lane % NV;
+  PollLanes p;
+  const int per = (nch + G - 1) / G;
+  p.cb = q * per;
+  p.ce = p.cb + per < nch ? p.cb + per : nch;
+#pragma unroll
+  for (int j = 0; j < kPollBatch; ++j) {
+    // an empty range (fewer chunks than groups) re-reads the last chunk, marked out
+    const int c = max(0, min(min(p.cb + j, p.ce - 1), nch - 1));
+    p.off[j] = (uint32_t)(c * 32 + v) * 8u;
+    p.in[j] = p.cb + j < p.ce ? 1.0f : 0.0f;
+  }
+  return p;
+}
+
+// A pointer that is the same in every lane, held in scalar registers.
+__device__ __forceinline__ uint64_t* uniform_ptr(uint64_t* p) {
+  const uint64_t u = (uint64_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+  return (uint64_t*)(((uint64_t)hi << 32) | lo);
+}
+
 // Wave 0 only.  Publish this chunk's column sums (`mine`, lanes < NV) under
 // `tag`, wait until all nch chunks of the stream published theirs, and return
 // the stream totals (lanes < NV).  False on timeout.  A chunk's words are 32
-// apart whatever NV is.  The wave's 64 / NV lane groups poll consecutive
-// ranges of the chunks (group q the q-th range, lane v word v), so a poll
-// round has 64 loads in flight, and the group sums meet in a fixed tree, the
-// same in every chunk of the stream.
+// apart whatever NV is.  pl: poll_lanes<NV>(nch).  The lane groups' sums meet
+// in a fixed tree, the same in every chunk of the stream.
 template <bool KAHAN, int NV>
-__device__ __forceinline__ bool exchange_partials(uint64_t* partials, int chunk, int nch, uint32_t tag, float mine,
-                                                  int spin_limit, float* total, int* polls = nullptr) {
+__device__ __forceinline__ bool exchange_partials(uint64_t* partials, const PollLanes& pl, int chunk, int nch,
+                                                  uint32_t tag, float mine, int spin_limit, float* total,
+                                                  int* polls = nullptr) {
   constexpr int G = 64 / NV;
   static_assert(G == 2 || G == 4, "32 or 16 values per chunk");
   static_assert(!(KAHAN && G != 2), "compensated sums use 32 values");
@@ -97,41 +134,53 @@ __device__ __forceinline__ bool exchange_partials(uint64_t* partials, int chunk,
   // global-memory pointers: global loads and stores, which unlike flat ones
   // leave the LDS counter alone and skip the aperture check
   using gptr = __attribute__((address_space(1))) uint64_t*;
-  gptr buf = (gptr)(partials + (size_t)(tag & 1u) * nch * 32);
-  gptr slow = (gptr)(partials + (size_t)(2 + (tag & 1u)) * nch * 32);
+  using gbytes = __attribute__((address_space(1))) char*;
+  const uint32_t half = (uint32_t)nch * 256u;  // bytes of one copy of one parity
+  const gbytes buf = (gbytes)partials + (tag & 1u) * half;
   const uint64_t hi = (uint64_t)tag << 32;
-  if (lane < NV) publish_word(&buf[chunk * 32 + lane], &slow[chunk * 32 + lane], hi | __float_as_uint(mine));
-  const int per = (nch + G - 1) / G, cb = q * per, ce = cb + per < nch ? cb + per : nch;
+  if (lane < NV) {
+    const uint32_t o = (uint32_t)(chunk * 32 + lane) * 8u;
+    publish_word((gptr)(buf + o), (gptr)(buf + 2u * half + o), hi | __float_as_uint(mine));
+  }
   for (int t = 0; t < spin_limit; ++t) {
-    const gptr rb = (t & kSlowPollMask) == kSlowPollMask ? slow : buf;
+    const gbytes rb = buf + ((t & kSlowPollMask) == kSlowPollMask ? 2u * half : 0u);
+    // a batch of loads in flight, then the checks, with no branch between the
+    // loads: past its range's end a lane re-reads the range's last chunk and
+    // leaves the word out
+    uint64_t w[kPollBatch];
+#pragma unroll
+    for (int j = 0; j < kPollBatch; ++j)
+      w[j] = __hip_atomic_load((gptr)(rb + pl.off[j]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // every load issued before the first wait: the scheduler otherwise starts
+    // on the first words before the last load, a second latency per round
+    __builtin_amdgcn_sched_barrier(0);
     float s = 0.0f, comp = 0.0f;
-    int ok = 1;
-    for (int c0 = cb; c0 < ce; c0 += kPollBatch) {
-      // a batch of loads in flight, then the checks, with no branch between
-      // the loads: past its range's end a lane re-reads the range's last
-      // chunk and leaves the word out
-      uint64_t w[kPollBatch];
+    uint32_t stale = 0;
+    auto add = [&](uint64_t word, float in) {
+      stale |= (uint32_t)(word >> 32) ^ tag;
+      const float x = __uint_as_float((uint32_t)word);
+      if (KAHAN) {
+        const float y = x - comp;
+        const float u = s + y;
+        const float cn = (u - s) - y;
+        s = in != 0.0f ? u : s;
+        comp = in != 0.0f ? cn : comp;
+      } else {
+        s = fmaf(x, in, s);
+      }
+    };
+#pragma unroll
+    for (int j = 0; j < kPollBatch; ++j) add(w[j], pl.in[j]);
+    for (int c0 = pl.cb + kPollBatch; c0 < pl.ce; c0 += kPollBatch) {
 #pragma unroll
       for (int j = 0; j < kPollBatch; ++j)
-        w[j] = __hip_atomic_load(&rb[min(c0 + j, ce - 1) * 32 + v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        w[j] = __hip_atomic_load((gptr)(rb + (uint32_t)(min(c0 + j, pl.ce - 1) * 32 + v) * 8u), __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int j = 0; j < kPollBatch; ++j) {
-        const bool in = c0 + j < ce;
-        ok &= !in | ((uint32_t)(w[j] >> 32) == tag);
-        const float x = __uint_as_float((uint32_t)w[j]);
-        if (KAHAN) {
-          const float y = x - comp;
-          const float u = s + y;
-          const float cn = (u - s) - y;
-          s = in ? u : s;
-          comp = in ? cn : comp;
-        } else {
-          const float u = s + x;
-          s = in ? u : s;
-        }
-      }
+      for (int j = 0; j < kPollBatch; ++j) add(w[j], c0 + j < pl.ce ? 1.0f : 0.0f);
     }
-    if (__all(ok)) {
+    if (__all(stale == 0)) {
       if constexpr (G == 4) s += lane_xor<16>(s);  // (g0 + g1), (g2 + g3)
       if constexpr (KAHAN) {  // the two compensated sums: (s0 - c0) + (s1 - c1)
         const float ps = lane_xor<32>(s), pc = lane_xor<32>(comp);
@@ -159,7 +208,7 @@ __device__ __forceinline__ bool exchange_partials(uint64_t* partials, int chunk,
 // shared by every chunk of the stream.  All threads; false on timeout.
 template <bool KAHAN, int NV>
 __device__ __forceinline__ bool exchange_wide(const uint64_t* partials, int nch, uint32_t tag, int spin_limit,
-                                              float* sh_grp, float* sh_tot) {
+                                              float* sh_grp, float* sh_tot, int2 place) {
   const int t = threadIdx.x, v = t & 31, q = t >> 5, G = blockDim.x >> 5;
   // global-memory pointers, no branch between a batch's loads and no sleep
   // between rounds, as in exchange_partials: past the last chunk a lane
@@ -214,21 +263,32 @@ __device__ __forceinline__ bool exchange_wide(const uint64_t* partials, int nch,
         tot += x;
       }
     }
-    sh_tot[t] = tot;
+    sh_tot[place.x] = tot;
+    sh_tot[place.y] = tot;
   }
   return bad == 0;
 }
 
+// What a thread takes from the stream totals: its lane's row of (H | b) with
+// the diagonal entry (robust mode) or b_i alone in row[6] (fixed H), i = lane %
+// 16 capped at 5, and the counts.
+struct LaneTotals {
+  float row[7], diag;
+  float n, pts;
+};
+
 // Block sum of acc[NV] (after each thread accumulated its point), exchanged
-// across the stream's chunks; the totals land in sh_tot and, in every thread,
-// in tot.  Returns false on timeout (same value in every thread).  NV = 32 or
-// 16.  WIDE: streams of more than kPollBatch chunks are polled by the whole
-// workgroup (exchange_wide, sh_grp: blockDim floats of LDS); otherwise wave 0
-// polls alone.  NW: the workgroup's waves (blockDim / 64).
+// across the stream's chunks; the totals land in sh_tot (kTotals floats, the
+// layout of the lane-parallel solve) and the lane's share of them in tot.
+// Returns false on timeout (same value in every thread).  NV = 32 or 16.
+// place: total_place of lane % 32.  WIDE: streams of more than kPollBatch
+// chunks are polled by the whole workgroup (exchange_wide, sh_grp: blockDim
+// floats of LDS); otherwise wave 0 polls alone.  NW: the workgroup's waves
+// (blockDim / 64).
 template <bool KAHAN, int NV, bool WIDE, int NW>
-__device__ __forceinline__ bool stream_total(float (&acc)[NV], float* sh_red, float* sh_tot, int* sh_ok,
-                                             uint64_t* partials, int chunk, int nch, uint32_t tag,
-                                             int spin_limit, float* sh_grp, float (&tot)[NV],
+__device__ __forceinline__ bool stream_total(float (&acc)[NV], float* sh_red, float* sh_tot, int2 place,
+                                             uint64_t* partials, const PollLanes& pl, int chunk, int nch, uint32_t tag,
+                                             int spin_limit, float* sh_grp, LaneTotals& tot,
                                              uint64_t* t_bar = nullptr, int* polls = nullptr) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   constexpr int PER_ROW = NV / 4;  // values per 16-lane row after the wave reduction
@@ -245,9 +305,13 @@ __device__ __forceinline__ bool stream_total(float (&acc)[NV], float* sh_red, fl
   if (wave == 0) {
     float s = 0.0f, comp = 0.0f;
     if (lane < NV) {
+      float part[NW];  // all NW reads in flight at once, then the sum in wave order
 #pragma unroll
-      for (int w = 0; w < NW; ++w) {  // all NW reads in flight at once, then the sum in wave order
-        const float x = sh_red[w * NV + lane];
+      for (int w = 0; w < NW; ++w) part[w] = sh_red[w * NV + lane];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const float x = part[w];
         if (KAHAN) {
           const float y = x - comp;
           const float u = s + y;
@@ -267,26 +331,31 @@ __device__ __forceinline__ bool stream_total(float (&acc)[NV], float* sh_red, fl
     } else {
       float tot = s;
       bool ok = true;
-      if (nch > 1) ok = exchange_partials<KAHAN, NV>(partials, chunk, nch, tag, s, spin_limit, &tot, polls);
-      if (lane < NV) sh_tot[lane] = tot;
-      if (lane == 0) *sh_ok = ok ? 1 : 0;
+      if (nch > 1) ok = exchange_partials<KAHAN, NV>(partials, pl, chunk, nch, tag, s, spin_limit, &tot, polls);
+      if (lane < NV) sh_tot[place.x] = tot, sh_tot[place.y] = tot;
+      if (lane == 0) sh_tot[kTotOk] = ok ? 1.0f : 0.0f;
     }
   }
-  bool ok;
-  if (WIDE && nch > kPollBatch) {
-    ok = exchange_wide<KAHAN, NV>(partials, nch, tag, spin_limit, sh_grp, sh_tot);
-    __syncthreads();
-  } else {
-    __syncthreads();
-    ok = *sh_ok != 0;
-  }
+  bool ok = true;
+  const bool wide = WIDE && nch > kPollBatch;
+  if (wide) ok = exchange_wide<KAHAN, NV>(partials, nch, tag, spin_limit, sh_grp, sh_tot, place);
+  __syncthreads();
   // every total requested with the verdict, before any test of either: left to
   // itself the compiler reads each behind the branch that first needs it, one
   // LDS round trip per test on the iteration's path
-#pragma unroll
-  for (int j = 0; j < NV; ++j) tot[j] = sh_tot[j];
+  const int i = min(lane & 15, 5);
+  const float4 cnt = *reinterpret_cast<const float4*>(sh_tot + kTotE);
+  if constexpr (NV == 32) {
+    const float4 h0 = *reinterpret_cast<const float4*>(sh_tot + 8 * i), h1 = *reinterpret_cast<const float4*>(sh_tot + 8 * i + 4);
+    tot.row[0] = h0.x, tot.row[1] = h0.y, tot.row[2] = h0.z, tot.row[3] = h0.w;
+    tot.row[4] = h1.x, tot.row[5] = h1.y, tot.row[6] = h1.z;
+    tot.diag = sh_tot[9 * i];
+  } else {
+    tot.row[6] = sh_tot[8 * i + kTotB];
+  }
+  tot.n = cnt.y, tot.pts = cnt.z;
   asm volatile("" ::: "memory");
-  return ok;
+  return wide ? ok : cnt.w != 0.0f;
 }
 
 // 3x4 rigid transforms (row-major [R | t]) in FP64, one output element per
@@ -526,14 +595,11 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
   constexpr int PPC = CH / TPP;                        // points per chunk
   constexpr int NS = 8 / LPP;                          // samples per thread (8-pixel kernels)
   constexpr int NV = FIXED ? kFixSlots : 32;
-  constexpr int sE = FIXED ? kFixE : kSlotE, sN = FIXED ? kFixN : kSlotN, sP = FIXED ? kFixPts : kSlotPts;
   __shared__ CoopStream ss;
-  __shared__ float sh_fac[FIXED ? 2 : 1][28];  // fixed H: factor of the level (L, invd, bad), by level parity
   __shared__ double sh_T0[12], sh_rw[12], sh_h0[12], sh_h1[12], sh_m1[12], sh_m2[12];
-  __shared__ float sh_tot[32];
+  __shared__ __align__(16) float sh_tot[kTotals];
   __shared__ float sh_red[(CH / 64) * 32];
   __shared__ float sh_grp[GENERIC ? CH : 1];  // the whole-workgroup exchange of many-chunk streams
-  __shared__ int sh_ok;
   __shared__ int sh_band[2 * (CH / 64)];
   extern __shared__ __align__(16) uint8_t sh_tile[];  // tile_bytes + kTilePad for the 8-pixel kernels, else none
   __shared__ const uint8_t* sh_l0;
@@ -556,10 +622,16 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
   const TrackArgs& a = ss.a;
   const IterParams ip(a);
   const PatRegs pregs = pattern_regs(a.pat);
-  const int chunk = w.y, nch = ss.n_chunks;
+  // the same in every thread: scalar registers
+  const int chunk = __builtin_amdgcn_readfirstlane(w.y), nch = __builtin_amdgcn_readfirstlane(ss.n_chunks);
+  uint64_t* const partials = uniform_ptr(ss.partials);
   const int i = chunk * PPC + (int)threadIdx.x / TPP;
   const int sub = (int)threadIdx.x % TPP;
   const int nf = WIN ? n_frames : 1;
+  const int2 place = total_place<NV>(threadIdx.x & 31);
+  const PollLanes pl = poll_lanes<NV>(nch);
+  const int li = threadIdx.x & 15;  // the lane's row of the system, its element of the pose
+  using Pose = typename std::conditional<MIXED, double, float>::type;
   uint32_t tag = tag_base;
   uint64_t cy[4] = {0, 0, 0, 0}, cy_iters = 0, cy_t0 = 0, cy_rt0 = 0, cy_polls = 0;
   uint64_t cy_fr[5] = {0, 0, 0, 0, 0};  // frame start, level starts, final pass, frames, frame end
@@ -578,14 +650,11 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
     // level 0 of the frame: from the source frames themselves when the window
     // pyramids were built without it
     const PIX* cur0 = WIN && sh_l0 ? reinterpret_cast<const PIX*>(sh_l0 + f * sh_l0_stride) : cur + a.lv[0].off;
-    // pose state, identical in every thread of every chunk of the stream
+    // pose state, identical in every 16-lane row of every chunk of the stream:
+    // one element per lane, and every element for the points' transforms
+    Pose Tl = (Pose)sh_T0[min(li, 11)];
     float T[12];
-    double Td[MIXED ? 12 : 1];
-#pragma unroll
-    for (int j = 0; j < 12; ++j) {
-      T[j] = (float)sh_T0[j];
-      if (MIXED) Td[j] = sh_T0[j];
-    }
+    spread_pose((float)Tl, T);
     int status = 0, iterations = 0;
     int ipl[kMaxLevels];
 #pragma unroll
@@ -617,13 +686,13 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
         __syncthreads();
         if (l == 0) tile0 = tile, at0 = true;
       }
+      float hinv[6];  // fixed H: the lane's row of the level's H^-1
+      int hbad = 0;
       if constexpr (FIXED) {
-        // read by every thread after the next exchange's barrier; the other
-        // parity's copy may still be in use by a previous level's solve
-        const FixedH& fh = a.ref.fixed[l];
-        if (threadIdx.x < 21) sh_fac[l & 1][threadIdx.x] = fh.L[threadIdx.x];
-        if (threadIdx.x >= 32 && threadIdx.x < 38) sh_fac[l & 1][21 + threadIdx.x - 32] = fh.invd[threadIdx.x - 32];
-        if (threadIdx.x == 40) sh_fac[l & 1][27] = fh.bad ? 1.0f : 0.0f;
+        const FixedH* fh = a.ref.fixed + l;
+#pragma unroll
+        for (int j = 0; j < 6; ++j) hinv[j] = gload(fh->inv + 6 * min(li, 5) + j);
+        hbad = gload(&fh->bad);
       }
       bool converged = false;
       const int it0 = iterations;
@@ -641,8 +710,8 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
                                                pr, acc, sub == 0);
         if constexpr (kCycleProfile) c1 = clock64();
         int polls = 0;
-        float tot[NV];
-        if (!stream_total<MIXED, NV, GENERIC, CH / 64>(acc, sh_red, sh_tot, &sh_ok, ss.partials, chunk, nch, tag,
+        LaneTotals tot;
+        if (!stream_total<MIXED, NV, GENERIC, CH / 64>(acc, sh_red, sh_tot, place, partials, pl, chunk, nch, tag,
                                                        spin_limit, sh_grp, tot, &c2, &polls)) {
           timed_out = stop = true;
           break;
@@ -651,41 +720,42 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
         if constexpr (kCycleProfile) c3 = clock64();
         ++tag;
         // the 8-pixel kernels count samples as 8 per point outside the final pass
-        samples += GENERIC ? (int64_t)(int)tot[sN] : 8 * (int64_t)(int)tot[sP];  // counts < 2^24: exact
-        if ((int)tot[sP] < ip.min_points) {
+        samples += GENERIC ? (int64_t)(int)tot.n : 8 * (int64_t)(int)tot.pts;  // counts < 2^24: exact
+        if (__builtin_expect((int)tot.pts < ip.min_points, 0)) {
           status = 2;  // too few points
           stop = true;
           break;
         }
-        int bad;
-        double step;
-        if (FIXED) {
-          const float* fac = sh_fac[FIXED ? (l & 1) : 0];
-          bad = fac[27] != 0.0f;
-          float stepf = 0.0f;
-          if (!bad) solve_fixed(fac, fac + 21, tot + kFixB, T, &stepf);
-          step = stepf;
-        } else if (MIXED) {
-          bad = solve_update_d(tot, Td, &step);
-          if (!bad)
-#pragma unroll
-            for (int j = 0; j < 12; ++j) T[j] = (float)Td[j];
+        bool bad;
+        Pose delta, step = 0;
+        if constexpr (FIXED) {
+          bad = hbad != 0;
+          const float b = tot.row[6];
+          delta = fmaf(hinv[0], row_bcast<0>(b), fmaf(hinv[1], row_bcast<1>(b), hinv[2] * row_bcast<2>(b))) +
+                  fmaf(hinv[3], row_bcast<3>(b), fmaf(hinv[4], row_bcast<4>(b), hinv[5] * row_bcast<5>(b)));
         } else {
-          float stepf;
-          bad = solve_update(tot, T, &stepf);
-          step = stepf;
+          Pose row[7];
+#pragma unroll
+          for (int j = 0; j < 7; ++j) row[j] = (Pose)tot.row[j];
+          delta = solve_rows(row, (Pose)tot.diag, (Pose)(MIXED ? 1e-12 : 1e-6), li, &bad);
+        }
+        if (__builtin_expect(!bad, 1)) {
+          Tl = update_lanes(Tl, delta, &step);
+          spread_pose((float)Tl, T);
         }
         if constexpr (kCycleProfile) {
           const uint64_t c4 = clock64();
           cy[0] += c1 - c0, cy[1] += c2 - c1, cy[2] += c3 - c2, cy[3] += c4 - c3, ++cy_iters, cy_polls += polls;
         }
-        if (bad) {
+        if (__builtin_expect(bad, 0)) {
           status = 3;  // not positive definite
           stop = true;
           break;
         }
         ++iterations;
-        if (step < (double)ip.step_eps) {
+        // the same in every lane; as a vote the compiler knows it, and the loop's
+        // branches and counters stay scalar
+        if (__any(step < (Pose)ip.step_eps)) {
           converged = true;
           break;
         }
@@ -715,18 +785,21 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
         lane_offsets<NS>(pregs, g.W, sub, offs);
         accumulate_point8<true, PR, NV, NS>(ip, pregs, offs, g, WIN ? cur0 : cur + g.off, tile0, T, pr, acc, sub == 0);
       }
-      float tot[NV];
-      if (!stream_total<MIXED, NV, GENERIC, CH / 64>(acc, sh_red, sh_tot, &sh_ok, ss.partials, chunk, nch, tag,
+      LaneTotals tot;
+      if (!stream_total<MIXED, NV, GENERIC, CH / 64>(acc, sh_red, sh_tot, place, partials, pl, chunk, nch, tag,
                                                      spin_limit, sh_grp, tot))
         timed_out = true;
       ++tag;
     }
     if constexpr (kCycleProfile) cy_fr[2] += clock64() - cp0;
+    // the pose in FP64 where thread 0 finishes it (sh_m1 is free between frames)
+    if (threadIdx.x < 12) sh_m1[threadIdx.x] = (double)Tl;
+    __syncthreads();
     if constexpr (!WIN) {
       if (chunk == 0 && threadIdx.x == 0) {
         TrackOut* o = out_ring + (size_t)slot * n_out + w.x;
         double Tf[12];
-        for (int j = 0; j < 12; ++j) Tf[j] = MIXED ? Td[j] : (double)T[j];
+        for (int j = 0; j < 12; ++j) Tf[j] = sh_m1[j];
         orthonormalize34(Tf);
         for (int j = 0; j < 12; ++j) {
           o->T[j] = T[j];
@@ -738,13 +811,13 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
           ss.hist[j] = sh_h1[j];
           ss.hist[12 + j] = compose34_elem(Tf, sh_rw, j);
         }
-        o->E = sh_tot[sE];
-        o->n = sh_tot[sN];
+        o->E = sh_tot[kTotE];
+        o->n = sh_tot[kTotN];
         o->iterations = iterations;
         for (int j = 0; j < kMaxLevels; ++j) o->iters_per_level[j] = ipl[j];
-        o->n_valid_points = (int)sh_tot[sP];
+        o->n_valid_points = (int)sh_tot[kTotPts];
         o->status = timed_out ? kStatusTimeout : status;
-        o->samples = samples + (int64_t)sh_tot[sN];
+        o->samples = samples + (int64_t)sh_tot[kTotN];
         // the fields reach the host before the sequence number: a system-scope
         // release (no acquire, so the L2 keeps the reference data it holds)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
@@ -757,7 +830,7 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
     if constexpr (kCycleProfile) ct0 = clock64();
     if (threadIdx.x == 0) {
       double Tf[12];
-      for (int j = 0; j < 12; ++j) Tf[j] = MIXED ? Td[j] : (double)T[j];
+      for (int j = 0; j < 12; ++j) Tf[j] = sh_m1[j];
       orthonormalize34(Tf);
       for (int j = 0; j < 12; ++j) sh_m1[j] = Tf[j];
       if (chunk == 0) {
@@ -766,13 +839,13 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
           o->T[j] = T[j];
           o->Td[j] = Tf[j];
         }
-        o->E = sh_tot[sE];
-        o->n = sh_tot[sN];
+        o->E = sh_tot[kTotE];
+        o->n = sh_tot[kTotN];
         o->iterations = iterations;
         for (int j = 0; j < kMaxLevels; ++j) o->iters_per_level[j] = ipl[j];
-        o->n_valid_points = (int)sh_tot[sP];
+        o->n_valid_points = (int)sh_tot[kTotPts];
         o->status = timed_out ? kStatusTimeout : status;
-        o->samples = samples + (int64_t)sh_tot[sN];
+        o->samples = samples + (int64_t)sh_tot[kTotN];
         // a chunk gave up: so do the frames after this one
         if (timed_out)
           for (int q = f + 1; q < nf; ++q) out_ring[(size_t)((slot + q) % kRing) * n_out + w.x].status = kStatusTimeout;

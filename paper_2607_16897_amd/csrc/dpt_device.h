@@ -565,78 +565,150 @@ __device__ __forceinline__ void substitute_update(const float (&L)[21], const fl
   compose_exp(T, w0, w1, w2, -d[3], -d[4], -d[5], th2, A, B, C);
 }
 
-// FP64 variant of solve_update: Cholesky solve (pivot <= 1e-12 of the largest
-// diagonal entry: not positive definite) and T <- T exp(-delta), pose in FP64.
-__device__ __forceinline__ int solve_update_d(const float* tot_lds, double* T, double* max_step) {
-  float tot[27];
-#pragma unroll
-  for (int q = 0; q < 27; ++q) tot[q] = tot_lds[q];
-  double L[21], invd[6];
-  double dmax = 0.0;
-#pragma unroll
-  for (int j = 0; j < 6; ++j) dmax = fmax(dmax, (double)tot[tri(j, j)]);
-  int bad = 0;
-#pragma unroll
-  for (int j = 0; j < 6; ++j) {
-    double s = tot[tri(j, j)];
-#pragma unroll
-    for (int k = 0; k < j; ++k) s = fma(-L[tri(k, j)], L[tri(k, j)], s);
-    bad |= !(s > 1e-12 * dmax);
-    s = fmax(s, 1e-300);
-    // 1/sqrt(s): hardware estimate, then two Newton steps (each squares the
-    // relative error) to full double precision; only 1/L(j, j) is used later
-    double inv = __builtin_amdgcn_rsq(s);
-    inv = inv * fma(-0.5 * s * inv, inv, 1.5);
-    inv = inv * fma(-0.5 * s * inv, inv, 1.5);
-    invd[j] = inv;
-#pragma unroll
-    for (int i = j + 1; i < 6; ++i) {
-      double t = tot[tri(j, i)];
-#pragma unroll
-      for (int k = 0; k < j; ++k) t = fma(-L[tri(k, i)], L[tri(k, j)], t);
-      L[tri(j, i)] = t * inv;
-    }
-  }
-  if (bad) return 1;
-  double y[6], d[6];
-#pragma unroll
-  for (int i = 0; i < 6; ++i) {
-    double s = tot[kSlotB + i];
-#pragma unroll
-    for (int k = 0; k < i; ++k) s = fma(-L[tri(k, i)], y[k], s);
-    y[i] = s * invd[i];
-  }
-#pragma unroll
-  for (int i = 5; i >= 0; --i) {
-    double s = y[i];
-#pragma unroll
-    for (int k = i + 1; k < 6; ++k) s = fma(-L[tri(i, k)], d[k], s);
-    d[i] = s * invd[i];
-  }
-  double m = 0.0;
-#pragma unroll
-  for (int j = 0; j < 6; ++j) m = fmax(m, fabs(d[j]));
-  *max_step = m;
-  const double w0 = -d[0], w1 = -d[1], w2 = -d[2];
-  const double th2 = fma(w0, w0, fma(w1, w1, w2 * w2));
-  double A, B, C;
-  if (th2 < 0.0025) {  // |w| < 0.05: series through th^8, truncation below 1e-20
-    A = fma(-th2 * (1.0 / 6.0), fma(-th2 * (1.0 / 20.0), fma(-th2 * (1.0 / 42.0), fma(-th2, 1.0 / 72.0, 1.0), 1.0), 1.0),
-            1.0);
-    B = 0.5 * fma(-th2 * (1.0 / 12.0),
-                  fma(-th2 * (1.0 / 30.0), fma(-th2 * (1.0 / 56.0), fma(-th2, 1.0 / 90.0, 1.0), 1.0), 1.0), 1.0);
-    C = (1.0 / 6.0) * fma(-th2 * (1.0 / 20.0),
-                          fma(-th2 * (1.0 / 42.0), fma(-th2 * (1.0 / 72.0), fma(-th2, 1.0 / 110.0, 1.0), 1.0), 1.0),
-                          1.0);
+// ---------------------------------------------------------------- solve and update across the lanes
+
+// Lane K of each 16-lane row, in every lane of the row (DPP row_newbcast).
+template <int K>
+__device__ __forceinline__ float row_bcast(float v) {
+  return __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x150 + K, 0xf, 0xf, true));
+}
+template <int K>
+__device__ __forceinline__ double row_bcast(double v) {
+  const uint64_t u = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_mov_dpp((uint32_t)u, 0x150 + K, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_mov_dpp((uint32_t)(u >> 32), 0x150 + K, 0xf, 0xf, true);
+  return __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+// Lane K of each quad, in every lane of the quad (DPP quad_perm).
+template <int K>
+__device__ __forceinline__ float quad_bcast(float v) {
+  return __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), K * 0x55, 0xf, 0xf, true));
+}
+template <int K>
+__device__ __forceinline__ double quad_bcast(double v) {
+  const uint64_t u = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_mov_dpp((uint32_t)u, K * 0x55, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_mov_dpp((uint32_t)(u >> 32), K * 0x55, 0xf, 0xf, true);
+  return __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+
+// The stream totals of an iteration as the solve reads them (floats, LDS): row
+// i of the symmetric H at 8 i .. 8 i + 5 and b_i at 8 i + 6, then the cost and
+// the counts.
+constexpr int kTotB = 6, kTotE = 48, kTotN = 49, kTotPts = 50, kTotOk = 51, kTotals = 52;
+
+// Where the total of reduction slot v goes: two places for an off-diagonal
+// entry of H (else twice the same).  Slots without a use go to a spare word of
+// the rows.
+template <int NV>
+__device__ __forceinline__ int2 total_place(int v) {
+  if constexpr (NV == kFixSlots) {
+    const int d = v < 6 ? 8 * v + kTotB : v == kFixE ? kTotE : v == kFixN ? kTotN : v == kFixPts ? kTotPts : 7;
+    return make_int2(d, d);
   } else {
-    const double th = sqrt(th2);
-    const double sn = sin(th), sh = sin(0.5 * th);
-    A = sn / th;
-    B = 2.0 * sh * sh / th2;
-    C = (th - sn) / (th2 * th);
+    const int r = (v >= 6) + (v >= 11) + (v >= 15) + (v >= 18) + (v >= 20);
+    const int c = v - (6 * r - r * (r - 1) / 2) + r;
+    if (v < kSlotB) return make_int2(8 * r + c, 8 * c + r);
+    const int d = v < kSlotE ? 8 * (v - kSlotB) + kTotB
+                             : v == kSlotE ? kTotE : v == kSlotN ? kTotN : v == kSlotPts ? kTotPts : 7;
+    return make_int2(d, d);
   }
-  compose_exp(T, w0, w1, w2, -d[3], -d[4], -d[5], th2, A, B, C);
-  return 0;
+}
+
+// 1 / p: the hardware estimate, in FP64 refined by two Newton steps.
+__device__ __forceinline__ float recip(float p) { return __builtin_amdgcn_rcpf(p); }
+__device__ __forceinline__ double recip(double p) {
+  double r = __builtin_amdgcn_rcp(p);
+  r = r * fma(-p, r, 2.0);
+  return r * fma(-p, r, 2.0);
+}
+
+// One elimination step of solve_rows (K = 0..5), then the next.
+template <int K, class F>
+__device__ __forceinline__ void eliminate(F (&a)[7], int i, F& piv, F& inv_own) {
+  const F p = row_bcast<K>(a[K]);
+  const F inv = recip(p);
+  const F f = (i == K ? F(0) : -a[K]) * inv;
+  piv = i == K ? p : piv;
+  inv_own = i == K ? inv : inv_own;
+#pragma unroll
+  for (int j = K + 1; j < 7; ++j) a[j] = fma(row_bcast<K>(a[j]), f, a[j]);
+  if constexpr (K < 5) eliminate<K + 1>(a, i, piv, inv_own);
+}
+
+// Solve H delta = b (6x6 SPD) across the lanes of each 16-lane row: lane i < 6
+// holds row i of (H | b) in a, Gauss-Jordan elimination without pivoting (the
+// pivots are those of the Cholesky factorisation squared), every step one
+// instruction per remaining column for all rows at once.  Lane i returns
+// delta_i; *bad (every lane) is set if a pivot is not above eps times the
+// largest diagonal entry (diag: the lane's own), NaN included.  A thread that
+// solves the system and updates the pose by itself issues about 330
+// instructions, these lanes 200 (the phase is bound by their issue, 4 cycles
+// each, and by their chains).  With the exchange's poll offsets formed once
+// and the iteration loop's branches scalar, a nine-frame window track of 2000
+// points takes 434 instead of 475 us (two threads per point; one thread per
+// point 479 instead of 535, fixed H 355 instead of 408, mixed precision 493
+// instead of 534).
+template <class F>
+__device__ __forceinline__ F solve_rows(F (&a)[7], F diag, F eps, int i, bool* bad) {
+  const F thr = eps * fmax(fmax(fmax(row_bcast<0>(diag), row_bcast<1>(diag)), fmax(row_bcast<2>(diag), row_bcast<3>(diag))),
+                           fmax(row_bcast<4>(diag), row_bcast<5>(diag)));
+  F piv = F(0), inv_own = F(0);
+  eliminate<0>(a, i, piv, inv_own);
+  *bad = __any((i < 6) & !(piv > thr));
+  return a[6] * inv_own;
+}
+
+// The pose held across the lanes: element (r, c) of the 3x4 [R | t] in lane
+// 4 r + c of each 16-lane row (lanes 12 to 15 hold a fourth row that nothing
+// reads).  T <- T exp(-delta), lane i < 6 giving delta_i (rotation first);
+// *max_step (every lane) = max |delta_i|.  Column c of the exponential is
+// alpha q + beta (w x q) + gamma (w.q) w with q the unit vector c and
+// (1 - B th2, A, B), or, for the translation, q = v and (1 - C th2, B, C): each
+// lane forms its own column, so the update costs a third of the instructions
+// of the entries one by one.
+template <class F>
+__device__ __forceinline__ F update_lanes(F T, F delta, F* max_step) {
+  const F w0 = -row_bcast<0>(delta), w1 = -row_bcast<1>(delta), w2 = -row_bcast<2>(delta);
+  const F v0 = -row_bcast<3>(delta), v1 = -row_bcast<4>(delta), v2 = -row_bcast<5>(delta);
+  *max_step = fmax(fmax(fmax(fabs(w0), fabs(w1)), fmax(fabs(w2), fabs(v0))), fmax(fabs(v1), fabs(v2)));
+  const int c = threadIdx.x & 3;
+  const bool tr = c == 3;
+  const F q0 = tr ? v0 : c == 0 ? F(1) : F(0), q1 = tr ? v1 : c == 1 ? F(1) : F(0),
+          q2 = tr ? v2 : c == 2 ? F(1) : F(0);
+  const F th2 = fma(w0, w0, fma(w1, w1, w2 * w2));
+  F be, ga;  // A and B, or B and C in the translation's lanes
+  if (__builtin_expect(th2 < F(0.0025), 1)) {  // |w| < 0.05
+    const F k1 = tr ? F(0.5) : F(1), g1 = tr ? F(1.0 / 6.0) : F(0.5);
+    const F k2 = tr ? F(1.0 / 24.0) : F(1.0 / 6.0), g2 = tr ? F(1.0 / 120.0) : F(1.0 / 24.0);
+    const F k3 = tr ? F(1.0 / 30.0) : F(1.0 / 20.0), g3 = tr ? F(1.0 / 42.0) : F(1.0 / 30.0);
+    if constexpr (sizeof(F) == 4) {
+      be = fma(-th2 * k2, fma(-th2, k3, F(1)), k1);
+      ga = fma(-th2 * g2, fma(-th2, g3, F(1)), g1);
+    } else {  // through th^8: truncation below 1e-20
+      const F k4 = tr ? F(1.0 / 56.0) : F(1.0 / 42.0), g4 = tr ? F(1.0 / 72.0) : F(1.0 / 56.0);
+      const F k5 = tr ? F(1.0 / 90.0) : F(1.0 / 72.0), g5 = tr ? F(1.0 / 110.0) : F(1.0 / 90.0);
+      be = fma(-th2 * k2, fma(-th2 * k3, fma(-th2 * k4, fma(-th2, k5, F(1)), F(1)), F(1)), k1);
+      ga = fma(-th2 * g2, fma(-th2 * g3, fma(-th2 * g4, fma(-th2, g5, F(1)), F(1)), F(1)), g1);
+    }
+  } else {
+    const F th = sqrt(th2);
+    const F sn = sin(th), sh = sin(F(0.5) * th);
+    const F A = sn / th, B = F(2) * sh * sh / th2, C = (th - sn) / (th2 * th);
+    be = tr ? B : A, ga = tr ? C : B;
+  }
+  const F al = fma(-ga, th2, F(1)), gd = ga * fma(w0, q0, fma(w1, q1, w2 * q2));
+  const F e0 = fma(al, q0, fma(be, fma(w1, q2, -(w2 * q1)), gd * w0));
+  const F e1 = fma(al, q1, fma(be, fma(w2, q0, -(w0 * q2)), gd * w1));
+  const F e2 = fma(al, q2, fma(be, fma(w0, q1, -(w1 * q0)), gd * w2));
+  return fma(quad_bcast<0>(T), e0, fma(quad_bcast<1>(T), e1, fma(quad_bcast<2>(T), e2, tr ? T : F(0))));
+}
+
+// Every element of a pose held across the lanes, in every lane.
+__device__ __forceinline__ void spread_pose(float Tl, float (&T)[12]) {
+  T[0] = row_bcast<0>(Tl), T[1] = row_bcast<1>(Tl), T[2] = row_bcast<2>(Tl), T[3] = row_bcast<3>(Tl);
+  T[4] = row_bcast<4>(Tl), T[5] = row_bcast<5>(Tl), T[6] = row_bcast<6>(Tl), T[7] = row_bcast<7>(Tl);
+  T[8] = row_bcast<8>(Tl), T[9] = row_bcast<9>(Tl), T[10] = row_bcast<10>(Tl), T[11] = row_bcast<11>(Tl);
 }
 
 // One map point's IC cache (K = 8) held in registers across the iterations of

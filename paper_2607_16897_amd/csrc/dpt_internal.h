@@ -44,6 +44,7 @@ struct FixedH {
   double H[21];    // upper triangle, tri() order
   float L[21];     // factor L(i, j), i >= j, stored at tri(j, i)
   float invd[6];   // 1 / L(j, j)
+  float inv[36];   // H^-1, row-major (the cooperative track's solve: one dot product per row)
   int32_t bad;     // 1: a pivot <= 1e-6 of the largest diagonal entry (not positive definite)
   int32_t pad;
 };

@@ -223,9 +223,10 @@ __global__ __launch_bounds__(256) void fixed_h_partial_kernel(PrecomputeArgs one
 // Level blockIdx.x: H = the workgroup partials summed in FP64 in workgroup
 // order, and its Cholesky factor in FP64 (pivot <= 1e-6 of the largest
 // diagonal entry: not positive definite, the FP32 solve's criterion), stored
-// rounded to FP32 for the track's substitutions.
+// rounded to FP32 for the one-workgroup track's substitutions, and from it H^-1,
+// rounded alike, for the cooperative track.
 __global__ __launch_bounds__(64) void fixed_h_final_kernel(PrecomputeArgs one, const PrecomputeArgs* __restrict__ many) {
-  __shared__ double sh_H[21];
+  __shared__ double sh_H[21], L[21], invd[6];
   const PrecomputeArgs& a = many ? many[blockIdx.y] : one;
   const int l = blockIdx.x;
   if (l >= a.levels) return;
@@ -236,26 +237,46 @@ __global__ __launch_bounds__(64) void fixed_h_final_kernel(PrecomputeArgs one, c
     sh_H[threadIdx.x] = s;
   }
   __syncthreads();
-  if (threadIdx.x != 0) return;
   FixedH& f = a.fixed[l];
-  double L[21], invd[6], dmax = 0.0;
-  for (int j = 0; j < 6; ++j) dmax = fmax(dmax, sh_H[tri(j, j)]);
-  int bad = 0;
-  for (int j = 0; j < 6; ++j) {
-    double d = sh_H[tri(j, j)];
-    for (int k = 0; k < j; ++k) d -= L[tri(k, j)] * L[tri(k, j)];
-    bad |= !(d > 1e-6 * dmax);
-    const double inv = 1.0 / sqrt(fmax(d, 1e-300));
-    invd[j] = inv;
-    for (int i = j + 1; i < 6; ++i) {
-      double t = sh_H[tri(j, i)];
-      for (int k = 0; k < j; ++k) t -= L[tri(k, i)] * L[tri(k, j)];
-      L[tri(j, i)] = t * inv;
+  if (threadIdx.x == 0) {
+    double dmax = 0.0;
+    for (int j = 0; j < 6; ++j) dmax = fmax(dmax, sh_H[tri(j, j)]);
+    int bad = 0;
+    for (int j = 0; j < 6; ++j) {
+      double d = sh_H[tri(j, j)];
+      for (int k = 0; k < j; ++k) d -= L[tri(k, j)] * L[tri(k, j)];
+      bad |= !(d > 1e-6 * dmax);
+      const double inv = 1.0 / sqrt(fmax(d, 1e-300));
+      invd[j] = inv;
+      for (int i = j + 1; i < 6; ++i) {
+        double t = sh_H[tri(j, i)];
+        for (int k = 0; k < j; ++k) t -= L[tri(k, i)] * L[tri(k, j)];
+        L[tri(j, i)] = t * inv;
+      }
     }
+    for (int q = 0; q < 21; ++q) f.H[q] = sh_H[q], f.L[q] = (float)L[q];
+    for (int j = 0; j < 6; ++j) f.invd[j] = (float)invd[j];
+    f.bad = bad;
   }
-  for (int q = 0; q < 21; ++q) f.H[q] = sh_H[q], f.L[q] = (float)L[q];
-  for (int j = 0; j < 6; ++j) f.invd[j] = (float)invd[j];
-  f.bad = bad;
+  __syncthreads();
+  if (threadIdx.x >= 6) return;
+  const int c = threadIdx.x;  // column c of H^-1 = L^-T L^-1 e_c
+  double y[6];
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    double t = i == c ? 1.0 : 0.0;
+#pragma unroll
+    for (int k = 0; k < i; ++k) t -= L[tri(k, i)] * y[k];
+    y[i] = t * invd[i];
+  }
+#pragma unroll
+  for (int i = 5; i >= 0; --i) {
+    double t = y[i];
+#pragma unroll
+    for (int k = i + 1; k < 6; ++k) t -= L[tri(i, k)] * y[k];
+    y[i] = t * invd[i];
+    f.inv[6 * i + c] = (float)y[i];
+  }
 }
 
 hipError_t launch_fixed_h(const PrecomputeArgs& a, hipStream_t s) {
