@@ -274,70 +274,61 @@ __device__ __forceinline__ bool exchange_wide(const uint64_t* partials, int nch,
 // 16 capped at 5, and the counts.
 struct LaneTotals {
   float row[7], diag;
-  float n, pts;
+  float E, pts;
 };
 
-// Block sum of acc[NV] (after each thread accumulated its point), exchanged
-// across the stream's chunks; the totals land in sh_tot (kTotals floats, the
-// layout of the lane-parallel solve) and the lane's share of them in tot.
-// Returns false on timeout (same value in every thread).  NV = 32 or 16.
-// place: total_place of lane % 32.  WIDE: streams of more than kPollBatch
-// chunks are polled by the whole workgroup (exchange_wide, sh_grp: blockDim
-// floats of LDS); otherwise wave 0 polls alone.  NW: the workgroup's waves
-// (blockDim / 64).
-template <bool KAHAN, int NV, bool WIDE, int NW>
-__device__ __forceinline__ bool stream_total(float (&acc)[NV], float* sh_red, float* sh_tot, int2 place,
-                                             uint64_t* partials, const PollLanes& pl, int chunk, int nch, uint32_t tag,
-                                             int spin_limit, float* sh_grp, LaneTotals& tot,
-                                             uint64_t* t_bar = nullptr, int* polls = nullptr) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  constexpr int PER_ROW = NV / 4;  // values per 16-lane row after the wave reduction
-  if constexpr (NV == 32)
-    wave_reduce32(acc);
-  else
-    wave_reduce16(acc);
-  if ((lane & 15) == 0) {
+// Wave 0's sum over the workgroup's NW waves of the words at sh_red + w * stride
+// + word: all reads in flight at once, then the sum in wave order.
+template <bool KAHAN, int NW>
+__device__ __forceinline__ float sum_waves(const float* sh_red, int stride, int word) {
+  float part[NW];
 #pragma unroll
-    for (int j = 0; j < PER_ROW; ++j) sh_red[wave * NV + PER_ROW * (lane >> 4) + j] = acc[j];
-  }
-  __syncthreads();
-  if (kCycleProfile && t_bar) *t_bar = clock64();
-  if (wave == 0) {
-    float s = 0.0f, comp = 0.0f;
-    if (lane < NV) {
-      float part[NW];  // all NW reads in flight at once, then the sum in wave order
+  for (int w = 0; w < NW; ++w) part[w] = sh_red[w * stride + word];
+  __builtin_amdgcn_sched_barrier(0);
+  float s = part[0], comp = 0.0f;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) part[w] = sh_red[w * NV + lane];
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        const float x = part[w];
-        if (KAHAN) {
-          const float y = x - comp;
-          const float u = s + y;
-          comp = (u - s) - y;
-          s = u;
-        } else {
-          s += x;
-        }
-      }
+  for (int w = 1; w < NW; ++w) {
+    if (KAHAN) {
+      const float y = part[w] - comp;
+      const float u = s + y;
+      comp = (u - s) - y;
+      s = u;
+    } else {
+      s += part[w];
     }
-    if (WIDE && nch > kPollBatch) {  // publish; the whole workgroup polls below
+  }
+  return s;
+}
+
+// The stream totals of the workgroup's column sums: `mine` (wave 0, lane v < NV:
+// slot v) exchanged across the stream's chunks; the totals land in sh_tot
+// (kTotals floats, the layout of the lane-parallel solve) and the lane's share
+// of them in tot.  Returns false on timeout (same value in every thread).  NV =
+// 32 or 16.  place: total_place of lane % 32.  WIDE: streams of more than
+// kPollBatch chunks are polled by the whole workgroup (exchange_wide, sh_grp:
+// blockDim floats of LDS); otherwise wave 0 polls alone.
+template <bool KAHAN, int NV, bool WIDE>
+__device__ __forceinline__ bool stream_total(float mine, float* sh_tot, int2 place, uint64_t* partials,
+                                             const PollLanes& pl, int chunk, int nch, uint32_t tag, int spin_limit,
+                                             float* sh_grp, LaneTotals& tot, int* polls = nullptr) {
+  const int lane = threadIdx.x & 63;
+  const bool wide = WIDE && nch > kPollBatch;
+  if (threadIdx.x < 64) {
+    if (wide) {  // publish; the whole workgroup polls below
       if (lane < NV)
         publish_word((__attribute__((address_space(1))) uint64_t*)&partials[(size_t)(tag & 1u) * nch * 32 + chunk * 32 + lane],
                      (__attribute__((address_space(1))) uint64_t*)&partials[(size_t)(2 + (tag & 1u)) * nch * 32 +
                                                                            chunk * 32 + lane],
-                     ((uint64_t)tag << 32) | __float_as_uint(s));
+                     ((uint64_t)tag << 32) | __float_as_uint(mine));
     } else {
-      float tot = s;
+      float total = mine;
       bool ok = true;
-      if (nch > 1) ok = exchange_partials<KAHAN, NV>(partials, pl, chunk, nch, tag, s, spin_limit, &tot, polls);
-      if (lane < NV) sh_tot[place.x] = tot, sh_tot[place.y] = tot;
+      if (nch > 1) ok = exchange_partials<KAHAN, NV>(partials, pl, chunk, nch, tag, mine, spin_limit, &total, polls);
+      if (lane < NV) sh_tot[place.x] = total, sh_tot[place.y] = total;
       if (lane == 0) sh_tot[kTotOk] = ok ? 1.0f : 0.0f;
     }
   }
   bool ok = true;
-  const bool wide = WIDE && nch > kPollBatch;
   if (wide) ok = exchange_wide<KAHAN, NV>(partials, nch, tag, spin_limit, sh_grp, sh_tot, place);
   __syncthreads();
   // every total requested with the verdict, before any test of either: left to
@@ -353,7 +344,7 @@ __device__ __forceinline__ bool stream_total(float (&acc)[NV], float* sh_red, fl
   } else {
     tot.row[6] = sh_tot[8 * i + kTotB];
   }
-  tot.n = cnt.y, tot.pts = cnt.z;
+  tot.E = cnt.x, tot.pts = cnt.z;
   asm volatile("" ::: "memory");
   return wide ? ok : cnt.w != 0.0f;
 }
@@ -496,23 +487,21 @@ constexpr int kBandMargin = 4;
 // Copies the 16-byte granules that overlap those rows (each holds at least one
 // byte of them, so none crosses into a page the level does not touch).
 // Block-wide (NW waves); the caller has finished every read of the previous
-// tile.  The points' geometry arrives as loaded (raw) and is completed into pr
-// here: before the band is computed from it, or, for a whole level, after the
-// copy is issued, so the copy's latency and the point loads' overlap.
+// tile.  can: the thread's point may be valid (its validity at this level is
+// still being loaded with its template: the band does not wait for it).
 template <int NW, class PR>
 __device__ __forceinline__ Tile8 stage_tile(const IterParams& a, const PatRegs& pat, const LevelGeom& g,
-                                            const uint8_t* img, const float* T, PR& pr, GeoRaw& raw,
+                                            const uint8_t* img, const float* T, const PR& pr, bool can,
                                             uint8_t* tile_mem, int tile_bytes, int* sh_band) {
   const int W = g.W, H = g.H;
   const int rows_fit = (tile_bytes - 32) / W;
   int lo = 0, hi = H - 1;
   if (rows_fit < H) {
-    finish_geometry(pr, raw);
     float X, Y, Z;
     transform(T, pr.X0, pr.Y0, pr.Z0, X, Y, Z);
     const float iz = __builtin_amdgcn_rcpf(Z);
     const float u = fmaf(g.fx * X, iz, g.cx), v = fmaf(g.fy * Y, iz, g.cy);
-    const bool ok = pr.ok & (Z > a.z_min) & inside(g, pat, u, v);
+    const bool ok = can & (Z > a.z_min) & inside(g, pat, u, v);
     const int iv = (int)floorf(ok ? v : 0.0f);
     int rlo = ok ? iv + (int)pat.dy_min : INT_MAX, rhi = ok ? iv + (int)pat.dy_max + 1 : INT_MIN;
     wave_min_max(rlo, rhi);
@@ -542,7 +531,6 @@ __device__ __forceinline__ Tile8 stage_tile(const IterParams& a, const PatRegs& 
       __builtin_amdgcn_global_load_lds(reinterpret_cast<const uint32_t*>(s0 + 16 * (uintptr_t)q),
                                        (__attribute__((address_space(3))) void*)(tile_mem + 16 * q0), 16, 0, 0);
   }
-  if (rows_fit >= H) finish_geometry(pr, raw);
   Tile8 t;
   t.lds = (const __attribute__((address_space(3))) uint8_t*)(tile_mem);
   t.lo = lo, t.hi = hi, t.delta = delta, t.bytes = ng * 16;
@@ -598,7 +586,8 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
   __shared__ CoopStream ss;
   __shared__ double sh_T0[12], sh_rw[12], sh_h0[12], sh_h1[12], sh_m1[12], sh_m2[12];
   __shared__ __align__(16) float sh_tot[kTotals];
-  __shared__ float sh_red[(CH / 64) * 32];
+  constexpr int NW = CH / 64;
+  __shared__ __align__(16) float sh_red[NW * kWaveWords];
   __shared__ float sh_grp[GENERIC ? CH : 1];  // the whole-workgroup exchange of many-chunk streams
   __shared__ int sh_band[2 * (CH / 64)];
   extern __shared__ __align__(16) uint8_t sh_tile[];  // tile_bytes + kTilePad for the 8-pixel kernels, else none
@@ -631,6 +620,22 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
   const int2 place = total_place<NV>(threadIdx.x & 31);
   const PollLanes pl = poll_lanes<NV>(nch);
   const int li = threadIdx.x & 15;  // the lane's row of the system, its element of the pose
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int sE = FIXED ? kFixE : kSlotE, sP = FIXED ? kFixPts : kSlotPts;
+  // where wave 0's lane finds its slot in a wave's partial sums: in an iteration
+  // (wave_word, or in order for the fixed H) and in the final pass (cost, count, 0)
+  const int word = FIXED ? min(lane, NV - 1) : wave_word(lane & 31);
+  const int slot_v = lane % NV, word_final = slot_v == sE ? 0 : slot_v == sP ? 1 : 2;
+  const int K = GENERIC ? a.pat.K : 8;
+  // the point, the same for every level and frame
+  PR pr;
+  int j0;
+  const bool can = load_geometry_once(a, i, pr, &j0);
+  float ju[6], jv[6];
+  warp_rows(pr.X0, pr.Y0, pr.Z0, ju, jv);
+  constexpr int QP = 4 / TPP;  // points per quad
+  QuadRows<FIXED ? 1 : QP> rows;
+  if constexpr (!FIXED) quad_rows_of<QP, 0>(ju, jv, rows);
   using Pose = typename std::conditional<MIXED, double, float>::type;
   uint32_t tag = tag_base;
   uint64_t cy[4] = {0, 0, 0, 0}, cy_iters = 0, cy_t0 = 0, cy_rt0 = 0, cy_polls = 0;
@@ -661,7 +666,7 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
     for (int j = 0; j < kMaxLevels; ++j) ipl[j] = 0;
     int64_t samples = 0;
     bool stop = false, timed_out = false;
-    PR pr;
+    LaneTotals tot = {};
     // the level-0 tile and point registers, reused by the final pass when the
     // levels ran down to 0
     Tile8 tile0 = no_tile(sh_tile);
@@ -674,18 +679,20 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
       const PIX* img = WIN && l == 0 ? cur0 : cur + g.off;
       Tile8 tile;
       int offs[NS];
+      const int64_t e = (int64_t)l * a.ref.cap + j0;
+      const uint8_t vb = gload(a.ref.valid + e);
       if constexpr (GENERIC) {
-        load_point_geo(a, l, i, pr);
+        pr.s0 = e * K;
       } else {
-        GeoRaw raw;
-        load_point_raw(a, l, i, sub, pr, raw);
+        load_template(a, e, sub, pr);
         lane_offsets<NS>(pregs, g.W, sub, offs);
-        tile = stage_tile<CH / 64>(ip, pregs, g, reinterpret_cast<const uint8_t*>(img), T, pr, raw, sh_tile, tile_bytes,
-                                   sh_band);
+        tile = stage_tile<NW>(ip, pregs, g, reinterpret_cast<const uint8_t*>(img), T, pr, can, sh_tile, tile_bytes,
+                              sh_band);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         if (l == 0) tile0 = tile, at0 = true;
       }
+      pr.ok = can & (vb != 0);
       float hinv[6];  // fixed H: the lane's row of the level's H^-1
       int hbad = 0;
       if constexpr (FIXED) {
@@ -700,27 +707,53 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
       for (int it = 0; it < ip.max_iters; ++it) {
         uint64_t c0 = 0, c1 = 0, c2 = 0;
         if constexpr (kCycleProfile) c0 = clock64();
-        float acc[NV];
-#pragma unroll
-        for (int j = 0; j < NV; ++j) acc[j] = 0.f;
+        PointSums ps;
         if constexpr (GENERIC)
-          accumulate_point_generic<false, PIX, NV>(a, a.pat, g, img, T, pr, sub, acc);
+          ps = sample_point_generic<false, FIXED, PIX>(a, a.pat, g, img, T, pr, sub);
         else
-          accumulate_point8<false, PR, NV, NS>(ip, pregs, offs, g, reinterpret_cast<const uint8_t*>(img), tile, T,
-                                               pr, acc, sub == 0);
+          ps = sample_point8<false, FIXED, PR, NS>(ip, pregs, offs, g, reinterpret_cast<const uint8_t*>(img), tile, T, pr);
         if constexpr (kCycleProfile) c1 = clock64();
+        if constexpr (FIXED) {
+          // b = -(ju v0 + jv v1) of the thread's samples (of a generic quad: once)
+          const bool use = ps.ok & (!GENERIC | (sub == 0));
+          const float v0 = use ? g.fx * ps.v0 : 0.0f, v1 = use ? g.fy * ps.v1 : 0.0f;
+          float acc[kFixSlots];
+#pragma unroll
+          for (int r = 0; r < kFixSlots; ++r) acc[r] = r < 6 ? -fmaf(ju[min(r, 5)], v0, jv[min(r, 5)] * v1) : 0.0f;
+          acc[kFixPts] = (ps.ok & (sub == 0)) ? 1.0f : 0.0f;
+          wave_reduce16(acc);
+          if ((lane & 15) == 0)
+            *reinterpret_cast<float4*>(sh_red + wave * kWaveWords + 4 * (lane >> 4)) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        } else {
+          float m00 = g.fx * g.fx * ps.m00, m01 = g.fx * g.fy * ps.m01, m11 = g.fy * g.fy * ps.m11;
+          float v0 = g.fx * ps.v0, v1 = g.fy * ps.v1;
+          if constexpr (LPP == 2) {  // the point's sums: both threads' of the pair
+            m00 += dpp_quad<0xB1>(m00), m01 += dpp_quad<0xB1>(m01), m11 += dpp_quad<0xB1>(m11);
+            v0 += dpp_quad<0xB1>(v0), v1 += dpp_quad<0xB1>(v1);
+          }
+          f32x4 D[3] = {};
+          quad_products<QP, 0>(rows, m00, m01, m11, v0, v1, ps.ok ? 1.0f : 0.0f, D);
+          float d[12] = {D[0][0], D[0][1], D[0][2], D[0][3], D[1][0], D[1][1],
+                         D[1][2], D[1][3], D[2][0], D[2][1], D[2][2], D[2][3]};
+          wave_reduce12(d);
+          if ((lane & 12) == 0) {
+            float* o = sh_red + wave * kWaveWords + 24 * (lane >> 5) + 12 * ((lane >> 4) & 1) + (lane & 3);
+            o[0] = d[0], o[4] = d[1], o[8] = d[2];
+          }
+        }
+        __syncthreads();
+        if constexpr (kCycleProfile) c2 = clock64();
         int polls = 0;
-        LaneTotals tot;
-        if (!stream_total<MIXED, NV, GENERIC, CH / 64>(acc, sh_red, sh_tot, place, partials, pl, chunk, nch, tag,
-                                                       spin_limit, sh_grp, tot, &c2, &polls)) {
+        const float mine = wave == 0 ? sum_waves<MIXED, NW>(sh_red, kWaveWords, word) : 0.0f;
+        if (!stream_total<MIXED, NV, GENERIC>(mine, sh_tot, place, partials, pl, chunk, nch, tag, spin_limit, sh_grp, tot,
+                                              &polls)) {
           timed_out = stop = true;
           break;
         }
         uint64_t c3 = 0;
         if constexpr (kCycleProfile) c3 = clock64();
         ++tag;
-        // the 8-pixel kernels count samples as 8 per point outside the final pass
-        samples += GENERIC ? (int64_t)(int)tot.n : 8 * (int64_t)(int)tot.pts;  // counts < 2^24: exact
+        samples += (int64_t)K * (int)tot.pts;  // counts < 2^24: exact
         if (__builtin_expect((int)tot.pts < ip.min_points, 0)) {
           status = 2;  // too few points
           stop = true;
@@ -767,27 +800,28 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
     uint64_t cp0 = 0;
     if constexpr (kCycleProfile) cp0 = clock64();
     if (!timed_out) {  // final cost-only pass at level 0
-      float acc[NV];
-#pragma unroll
-      for (int j = 0; j < NV; ++j) acc[j] = 0.f;
       const LevelGeom g = a.lv[0];
+      PointSums ps;
+      if (GENERIC || !at0) {  // the levels stopped above 0: level 0's registers, taps from global memory
+        pr.ok = can & (gload(a.ref.valid + j0) != 0);
+        if constexpr (GENERIC)
+          pr.s0 = (int64_t)j0 * K;
+        else
+          load_template(a, j0, sub, pr);
+      }
       if constexpr (GENERIC) {
-        load_point_geo(a, 0, i, pr);
-        accumulate_point_generic<true, PIX, NV>(a, a.pat, g, WIN ? cur0 : cur + g.off, T, pr, sub, acc);
+        ps = sample_point_generic<true, FIXED, PIX>(a, a.pat, g, WIN ? cur0 : cur + g.off, T, pr, sub);
+        ps.E = sub == 0 ? ps.E : 0.0f;
       } else {
-        if (!at0) {  // the levels stopped above 0: level 0's registers, taps from global memory
-          if constexpr (LPP == 2)
-            load_point(a, 0, i, sub, pr);
-          else
-            load_point(a, 0, i, pr);
-        }
         int offs[NS];
         lane_offsets<NS>(pregs, g.W, sub, offs);
-        accumulate_point8<true, PR, NV, NS>(ip, pregs, offs, g, WIN ? cur0 : cur + g.off, tile0, T, pr, acc, sub == 0);
+        ps = sample_point8<true, FIXED, PR, NS>(ip, pregs, offs, g, WIN ? cur0 : cur + g.off, tile0, T, pr);
       }
-      LaneTotals tot;
-      if (!stream_total<MIXED, NV, GENERIC, CH / 64>(acc, sh_red, sh_tot, place, partials, pl, chunk, nch, tag,
-                                                     spin_limit, sh_grp, tot))
+      const float E = wave_sum(ps.E), n = wave_sum((ps.ok & (sub == 0)) ? 1.0f : 0.0f);
+      if (lane == 0) *reinterpret_cast<float4*>(sh_red + wave * kWaveWords) = make_float4(E, n, 0.0f, 0.0f);
+      __syncthreads();
+      const float mine = wave == 0 ? sum_waves<MIXED, NW>(sh_red, kWaveWords, word_final) : 0.0f;
+      if (!stream_total<MIXED, NV, GENERIC>(mine, sh_tot, place, partials, pl, chunk, nch, tag, spin_limit, sh_grp, tot))
         timed_out = true;
       ++tag;
     }
@@ -811,13 +845,13 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
           ss.hist[j] = sh_h1[j];
           ss.hist[12 + j] = compose34_elem(Tf, sh_rw, j);
         }
-        o->E = sh_tot[kTotE];
-        o->n = sh_tot[kTotN];
+        o->E = tot.E;
+        o->n = (float)K * tot.pts;
         o->iterations = iterations;
         for (int j = 0; j < kMaxLevels; ++j) o->iters_per_level[j] = ipl[j];
-        o->n_valid_points = (int)sh_tot[kTotPts];
+        o->n_valid_points = (int)tot.pts;
         o->status = timed_out ? kStatusTimeout : status;
-        o->samples = samples + (int64_t)sh_tot[kTotN];
+        o->samples = samples + (int64_t)K * (int)tot.pts;
         // the fields reach the host before the sequence number: a system-scope
         // release (no acquire, so the L2 keeps the reference data it holds)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
@@ -839,13 +873,13 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
           o->T[j] = T[j];
           o->Td[j] = Tf[j];
         }
-        o->E = sh_tot[kTotE];
-        o->n = sh_tot[kTotN];
+        o->E = tot.E;
+        o->n = (float)K * tot.pts;
         o->iterations = iterations;
         for (int j = 0; j < kMaxLevels; ++j) o->iters_per_level[j] = ipl[j];
-        o->n_valid_points = (int)sh_tot[kTotPts];
+        o->n_valid_points = (int)tot.pts;
         o->status = timed_out ? kStatusTimeout : status;
-        o->samples = samples + (int64_t)sh_tot[kTotN];
+        o->samples = samples + (int64_t)K * (int)tot.pts;
         // a chunk gave up: so do the frames after this one
         if (timed_out)
           for (int q = f + 1; q < nf; ++q) out_ring[(size_t)((slot + q) % kRing) * n_out + w.x].status = kStatusTimeout;

@@ -727,7 +727,6 @@ struct PointRegs {
 // 12 registers per point instead of 24.
 struct PointRegsH {
   float X0, Y0, Z0;
-  float iz, xp, yp;
   __half i0_[8];
   __half2 g_[8];
   bool ok;
@@ -740,7 +739,6 @@ struct PointRegsH {
 // threads: samples 4 sub .. 4 sub + 3 of thread `sub` of the pair.
 struct PointRegs4 {
   float X0, Y0, Z0;
-  float iz, xp, yp;
   float i0_[4], gx_[4], gy_[4];
   bool ok;
   __device__ __forceinline__ float i0(int k) const { return i0_[k]; }
@@ -750,7 +748,6 @@ struct PointRegs4 {
 
 struct PointRegsH4 {
   float X0, Y0, Z0;
-  float iz, xp, yp;
   __half i0_[4];
   __half2 g_[4];
   bool ok;
@@ -792,26 +789,7 @@ __device__ __forceinline__ bool load_geometry(const TrackArgs& a, int l, int i, 
   return in & (gload(a.ref.valid + e) != 0);
 }
 
-// A point's geometry as loaded (world point, validity byte, inside the map),
-// before any use of the loaded words.
-struct GeoRaw {
-  float x, y, z;
-  uint32_t valid;
-  bool in;
-};
-
-__device__ __forceinline__ void load_geometry_raw(const TrackArgs& a, int l, int i, GeoRaw& r, int64_t& e) {
-  const int64_t lo = (int64_t)l * a.ref.cap;
-  r.in = i < a.ref.n;
-  const int j = r.in ? i : 0;
-  e = lo + j;
-  const float4 p = gload(a.ref.x0 + j);
-  r.x = p.x, r.y = p.y, r.z = p.z;
-  r.valid = gload(a.ref.valid + e);
-}
-
-template <class PR>
-__device__ __forceinline__ void set_geometry(PR& pr, bool ok, const float4& p) {
+__device__ __forceinline__ void set_geometry(PointRegs& pr, bool ok, const float4& p) {
   pr.ok = ok;
   const float iz = 1.0f / p.z;
   pr.X0 = ok ? p.x : 0.0f;
@@ -883,38 +861,30 @@ __device__ __forceinline__ void load_template(const TrackArgs& a, int64_t e, int
   }
 }
 
-// Point i's registers for level l: one thread per point (sub ignored), or
-// thread `sub` (0 or 1) of the point's pair for the PR4 variants.
-template <class PR>
-__device__ __forceinline__ void load_point(const TrackArgs& a, int l, int i, int sub, PR& pr) {
+// Point i's registers for level l, one thread per point.
+__device__ __forceinline__ void load_point(const TrackArgs& a, int l, int i, PointRegs& pr) {
   float4 p;
   int64_t e;
   const bool ok = load_geometry(a, l, i, p, e);
   set_geometry(pr, ok, p);
-  load_template(a, e, sub, pr);
+  load_template(a, e, 0, pr);
 }
 
+// The cooperative kernel's geometry of map point i, the same for every level
+// and frame of a launch: X0, Y0, Z0 of pr (a point past the map, behind the
+// camera or not finite, which no level holds as valid, becomes (0, 0, 1)).  Returns
+// whether the point can be valid; *j is its entry in a level's cache.
 template <class PR>
-__device__ __forceinline__ void load_point(const TrackArgs& a, int l, int i, PR& pr) {
-  load_point(a, l, i, 0, pr);
-}
-
-// As load_point, with the geometry left as loaded (r): the cooperative kernel
-// issues these loads, then its level tile's copy, and only then waits for them
-// (finish_geometry), so both latencies overlap.
-template <class PR>
-__device__ __forceinline__ void load_point_raw(const TrackArgs& a, int l, int i, int sub, PR& pr, GeoRaw& r) {
-  int64_t e;
-  load_geometry_raw(a, l, i, r, e);
-  load_template(a, e, sub, pr);
-}
-
-// The wait for the geometry words happens here (the empty asm reads them), not
-// earlier: the compiler may not compute with them before this point.
-template <class PR>
-__device__ __forceinline__ void finish_geometry(PR& pr, GeoRaw& r) {
-  asm volatile("" : "+v"(r.x), "+v"(r.y), "+v"(r.z), "+v"(r.valid) : : "memory");
-  set_geometry(pr, r.in & (r.valid != 0), make_float4(r.x, r.y, r.z, 0.0f));
+__device__ __forceinline__ bool load_geometry_once(const TrackArgs& a, int i, PR& pr, int* j) {
+  const bool in = i < a.ref.n;
+  *j = in ? i : 0;
+  const float4 p = gload(a.ref.x0 + *j);
+  const bool can = in && p.z > a.z_min && p.z < __builtin_inff() && fabsf(p.x) < __builtin_inff() &&
+                   fabsf(p.y) < __builtin_inff();
+  pr.X0 = can ? p.x : 0.0f;
+  pr.Y0 = can ? p.y : 0.0f;
+  pr.Z0 = can ? p.z : 1.0f;
+  return can;
 }
 
 // Add one point's normal-equation terms (Eq.(2), Eq.(5)) at relative pose T.
@@ -1047,26 +1017,30 @@ struct IterParams {
       : huber_k(a.huber_k), z_min(a.z_min), step_eps(a.step_eps), max_iters(a.max_iters), min_points(a.min_points) {}
 };
 
-// accumulate_point for the 8-pixel pattern, with the taps read from the
-// workgroup's LDS copy of the level where every point of the wave lies inside
-// it (else from global memory, as accumulate_point).  The pattern offsets are
-// whole pixels, so all 8 samples share the point's bilinear fractions: the
-// weights are formed once per point.  COST_ONLY: only the cost and the counts
-// (the final pass).  Otherwise the Gauss-Newton terms and the point count, no
-// cost (it is read only after the final pass; the sample count is 8 per point).
+// What a thread's samples of its point sum to at a pose: m = sum w g^T g, v =
+// sum w g r and the cost, and whether the point is usable there (else the sums
+// are zero).
+struct PointSums {
+  float m00, m01, m11, v0, v1, E;
+  bool ok;
+};
+
+// The sums of a point's samples for the 8-pixel pattern (Eq.(2), Eq.(5)), with the
+// taps read from the workgroup's LDS copy of the level where every point of the
+// wave lies inside it (else from global memory, as accumulate_point).  The
+// pattern offsets are whole pixels, so all 8 samples share the point's bilinear
+// fractions: the weights are formed once per point.  Branch-free: an unusable
+// point (reference-invalid, behind the camera or a pattern position outside the
+// level) runs the same instructions and its sums are selected to zero.
+// COST_ONLY: only the cost (the final pass).  Otherwise m and v, no cost (it is
+// read only after the final pass).  FIXED: no weights, v only.
 //
-// NS = 4: the point has two threads, this one (first = false for the second of
-// the pair) taking four of its samples with their offsets `off`.  Each adds its
-// own samples' normal-equation terms, which sum to the point's (the terms are
-// linear in m and v); the first thread counts the point.
-template <bool COST_ONLY, class PR, int NV = 32, int NS = 8>
-__device__ __forceinline__ void accumulate_point8(const IterParams& a, const PatRegs& pat, const int (&off)[NS],
-                                                  const LevelGeom& g, const uint8_t* __restrict__ img,
-                                                  const Tile8& tile, const float* T, const PR& pr,
-                                                  float (&acc)[NV], bool first = true) {
-  constexpr bool FIXED = NV == kFixSlots;
-  static_assert(NV == 32 || FIXED, "slot layout");
-  constexpr int sE = FIXED ? kFixE : kSlotE, sN = FIXED ? kFixN : kSlotN, sP = FIXED ? kFixPts : kSlotPts;
+// NS = 4: the point has two threads, each taking four of its samples with
+// their offsets `off`; the point's sums are the two threads' added.
+template <bool COST_ONLY, bool FIXED, class PR, int NS>
+__device__ __forceinline__ PointSums sample_point8(const IterParams& a, const PatRegs& pat, const int (&off)[NS],
+                                                   const LevelGeom& g, const uint8_t* __restrict__ img,
+                                                   const Tile8& tile, const float* T, const PR& pr) {
   const float kH = FIXED ? 0.0f : a.huber_k;
   // Huber weight min(1, k / |r|); without a threshold every weight is 1
   const float kHw = kH > 0.0f ? kH : __builtin_inff();
@@ -1117,7 +1091,8 @@ __device__ __forceinline__ void accumulate_point8(const IterParams& a, const Pat
       t00[k] = gimg[o], t10[k] = gimg[o + 1], t01[k] = gimg[o + W], t11[k] = gimg[o + W + 1];
     }
   }
-  float m00 = 0.f, m01 = 0.f, m11 = 0.f, v0 = 0.f, v1 = 0.f, E = 0.f;
+  PointSums s = {};
+  s.ok = ok;
 #pragma unroll
   for (int k = 0; k < NS; ++k) {
     const float Ic = bilin_mix(q0.w, t00[k], t10[k], t01[k], t11[k]);
@@ -1125,74 +1100,42 @@ __device__ __forceinline__ void accumulate_point8(const IterParams& a, const Pat
     if constexpr (COST_ONLY) {
       const float ar = fabsf(r);
       const bool hub = (kH > 0.f) & (ar > kH);
-      E += hub ? kH * (ar - 0.5f * kH) : 0.5f * r * r;
+      s.E += hub ? kH * (ar - 0.5f * kH) : 0.5f * r * r;
     } else {
       const float gx = pr.gx(k), gy = pr.gy(k);
       if constexpr (FIXED) {
-        v0 = fmaf(gx, r, v0);
-        v1 = fmaf(gy, r, v1);
+        s.v0 = fmaf(gx, r, s.v0);
+        s.v1 = fmaf(gy, r, s.v1);
       } else {
         const float w = fminf(1.0f, kHw * __builtin_amdgcn_rcpf(fabsf(r)));
         const float wgx = w * gx, wgy = w * gy;
-        m00 = fmaf(wgx, gx, m00);
-        m01 = fmaf(wgx, gy, m01);
-        m11 = fmaf(wgy, gy, m11);
-        v0 = fmaf(wgx, r, v0);
-        v1 = fmaf(wgy, r, v1);
+        s.m00 = fmaf(wgx, gx, s.m00);
+        s.m01 = fmaf(wgx, gy, s.m01);
+        s.m11 = fmaf(wgy, gy, s.m11);
+        s.v0 = fmaf(wgx, r, s.v0);
+        s.v1 = fmaf(wgy, r, s.v1);
       }
     }
   }
-  acc[sP] += (ok & first) ? 1.0f : 0.0f;
   if constexpr (COST_ONLY) {
-    acc[sE] += ok ? E : 0.0f;
-    acc[sN] += ok ? (float)NS : 0.0f;
-    return;
-  }
-  v0 = ok ? v0 : 0.0f, v1 = ok ? v1 : 0.0f;
-  const float izr = pr.iz, xp = pr.xp, yp = pr.yp;
-  const float au[6] = {-g.fx * xp * yp, g.fx * fmaf(xp, xp, 1.0f), -g.fx * yp, g.fx * izr, 0.0f, -g.fx * xp * izr};
-  const float av[6] = {-g.fy * fmaf(yp, yp, 1.0f), g.fy * xp * yp, g.fy * xp, 0.0f, g.fy * izr, -g.fy * yp * izr};
-  if constexpr (FIXED) {
-#pragma unroll
-    for (int r = 0; r < 6; ++r) acc[kFixB + r] -= fmaf(au[r], v0, av[r] * v1);
+    s.E = ok ? s.E : 0.0f;
   } else {
-    m00 = ok ? m00 : 0.0f, m01 = ok ? m01 : 0.0f, m11 = ok ? m11 : 0.0f;
-    int q = 0;
-#pragma unroll
-    for (int r = 0; r < 6; ++r) {
-      const float ma = fmaf(m00, au[r], m01 * av[r]);
-      const float mc = fmaf(m01, au[r], m11 * av[r]);
-#pragma unroll
-      for (int c = r; c < 6; ++c) {
-        acc[q] = fmaf(ma, au[c], fmaf(mc, av[c], acc[q]));
-        ++q;
-      }
-      acc[kSlotB + r] -= fmaf(au[r], v0, av[r] * v1);
-    }
+    s.v0 = ok ? s.v0 : 0.0f, s.v1 = ok ? s.v1 : 0.0f;
+    if constexpr (!FIXED) s.m00 = ok ? s.m00 : 0.0f, s.m01 = ok ? s.m01 : 0.0f, s.m11 = ok ? s.m11 : 0.0f;
   }
+  return s;
 }
 
 // ---------------------------------------------------------------- generic-K cooperative accumulation
 
 // Patterns other than the 8-pixel one (p x p patches) and the floating-point
 // pyramid: four lanes share a point, lane `sub` of the quad taking samples
-// sub, sub + 4, ... < K, so a 49-sample patch costs each lane 13 samples.  The
-// quad's partial sums are combined with DPP quad permutations and lane 0 of the
-// quad adds the point's normal-equation terms.
+// sub, sub + 4, ... < K, so a 49-sample patch costs each lane 13 samples.
 struct PointGeo {
   float X0, Y0, Z0;
-  float iz, xp, yp;
   int64_t s0;  // cache index of the point's sample 0 at the level
   bool ok;
 };
-
-__device__ __forceinline__ void load_point_geo(const TrackArgs& a, int l, int i, PointGeo& pg) {
-  float4 p;
-  int64_t e;
-  const bool ok = load_geometry(a, l, i, p, e);
-  set_geometry(pg, ok, p);
-  pg.s0 = e * a.pat.K;
-}
 
 // DPP quad permutation (quad_perm selector), a VALU operand modifier.
 template <int SEL>
@@ -1207,14 +1150,13 @@ __device__ __forceinline__ float quad_sum(float v) {
   return v;
 }
 
-// NV = 32: robust mode; NV = kFixSlots: fixed-H mode (no weights, b only), as
-// accumulate_point.  PIX: uint8 levels or the floating-point Gaussian pyramid.
-template <bool COST_ONLY, class PIX, int NV>
-__device__ __forceinline__ void accumulate_point_generic(const TrackArgs& a, const Pattern& pat, const LevelGeom& g,
-                                                         const PIX* __restrict__ img, const float* T,
-                                                         const PointGeo& pg, int sub, float (&acc)[NV]) {
-  constexpr bool FIXED = NV == kFixSlots;
-  constexpr int sE = FIXED ? kFixE : kSlotE, sN = FIXED ? kFixN : kSlotN, sP = FIXED ? kFixPts : kSlotPts;
+// sample_point8 for any pattern; the sums are those of the quad's point, the
+// same in its four lanes.  PIX: uint8 levels or the floating-point Gaussian
+// pyramid.
+template <bool COST_ONLY, bool FIXED, class PIX>
+__device__ __forceinline__ PointSums sample_point_generic(const TrackArgs& a, const Pattern& pat, const LevelGeom& g,
+                                                          const PIX* __restrict__ img, const float* T,
+                                                          const PointGeo& pg, int sub) {
   const float kH = FIXED ? 0.0f : a.huber_k;
   float X, Y, Z;
   transform(T, pg.X0, pg.Y0, pg.Z0, X, Y, Z);
@@ -1226,7 +1168,8 @@ __device__ __forceinline__ void accumulate_point_generic(const TrackArgs& a, con
   const Cell q0 = cell_of(u, v);
   const int K = pat.K, W = g.W;
   const __attribute__((address_space(1))) PIX* gimg = (const __attribute__((address_space(1))) PIX*)img;
-  float m00 = 0.f, m01 = 0.f, m11 = 0.f, v0 = 0.f, v1 = 0.f, E = 0.f;
+  PointSums s = {};
+  s.ok = ok;
   // Batches of four samples per lane: all their taps and cache entries are
   // issued before any is used.  A slot past the pattern reads sample 0 (always
   // in range) and is weighted by zero.
@@ -1253,52 +1196,137 @@ __device__ __forceinline__ void accumulate_point_generic(const TrackArgs& a, con
       const bool hub = (kH > 0.f) & (ar > kH);
       const float w = (hub ? kH * __builtin_amdgcn_rcpf(ar) : 1.0f) * msk[j];
       const float rho = hub ? kH * (ar - 0.5f * kH) : 0.5f * r * r;
-      E = fmaf(msk[j], rho, E);
+      s.E = fmaf(msk[j], rho, s.E);
       if (!COST_ONLY) {
         const float wgx = w * gxs[j], wgy = w * gys[j];
         if (!FIXED) {
-          m00 = fmaf(wgx, gxs[j], m00);
-          m01 = fmaf(wgx, gys[j], m01);
-          m11 = fmaf(wgy, gys[j], m11);
+          s.m00 = fmaf(wgx, gxs[j], s.m00);
+          s.m01 = fmaf(wgx, gys[j], s.m01);
+          s.m11 = fmaf(wgy, gys[j], s.m11);
         }
-        v0 = fmaf(wgx, r, v0);
-        v1 = fmaf(wgy, r, v1);
+        s.v0 = fmaf(wgx, r, s.v0);
+        s.v1 = fmaf(wgy, r, s.v1);
       }
     }
   }
-  const bool use = ok & (sub == 0);
-  E = quad_sum(E);
-  acc[sE] += use ? E : 0.0f;
-  acc[sN] += use ? (float)K : 0.0f;
-  acc[sP] += use ? 1.0f : 0.0f;
-  if (COST_ONLY) return;
-  v0 = quad_sum(v0);
-  v1 = quad_sum(v1);
-  v0 = use ? v0 : 0.0f, v1 = use ? v1 : 0.0f;
-  const float iz = pg.iz, xp = pg.xp, yp = pg.yp;
-  const float au[6] = {-g.fx * xp * yp, g.fx * fmaf(xp, xp, 1.0f), -g.fx * yp, g.fx * iz, 0.0f, -g.fx * xp * iz};
-  const float av[6] = {-g.fy * fmaf(yp, yp, 1.0f), g.fy * xp * yp, g.fy * xp, 0.0f, g.fy * iz, -g.fy * yp * iz};
-  if constexpr (FIXED) {
-#pragma unroll
-    for (int r = 0; r < 6; ++r) acc[kFixB + r] -= fmaf(au[r], v0, av[r] * v1);
+  if constexpr (COST_ONLY) {
+    s.E = quad_sum(s.E);
+    s.E = ok ? s.E : 0.0f;
   } else {
-    m00 = quad_sum(m00);
-    m01 = quad_sum(m01);
-    m11 = quad_sum(m11);
-    m00 = use ? m00 : 0.0f, m01 = use ? m01 : 0.0f, m11 = use ? m11 : 0.0f;
-    int q = 0;
-#pragma unroll
-    for (int r = 0; r < 6; ++r) {
-      const float ma = fmaf(m00, au[r], m01 * av[r]);
-      const float mc = fmaf(m01, au[r], m11 * av[r]);
-#pragma unroll
-      for (int c = r; c < 6; ++c) {
-        acc[q] = fmaf(ma, au[c], fmaf(mc, av[c], acc[q]));
-        ++q;
-      }
-      acc[kSlotB + r] -= fmaf(au[r], v0, av[r] * v1);
+    s.v0 = quad_sum(s.v0), s.v1 = quad_sum(s.v1);
+    s.v0 = ok ? s.v0 : 0.0f, s.v1 = ok ? s.v1 : 0.0f;
+    if constexpr (!FIXED) {
+      s.m00 = quad_sum(s.m00), s.m01 = quad_sum(s.m01), s.m11 = quad_sum(s.m11);
+      s.m00 = ok ? s.m00 : 0.0f, s.m01 = ok ? s.m01 : 0.0f, s.m11 = ok ? s.m11 : 0.0f;
     }
   }
+  return s;
+}
+
+// ---------------------------------------------------------------- normal equations on the matrix cores
+
+// The warp Jacobian of a point at x0 for unit focal lengths: rows ju, jv over
+// the twist (omega, v), Eq.(6).  They depend on the map alone, not on level or
+// pose: a level's focal lengths scale m and v instead.
+__device__ __forceinline__ void warp_rows(float X, float Y, float Z, float (&ju)[6], float (&jv)[6]) {
+  const float iz = 1.0f / Z, xp = X * iz, yp = Y * iz;
+  ju[0] = -xp * yp, ju[1] = fmaf(xp, xp, 1.0f), ju[2] = -yp, ju[3] = iz, ju[4] = 0.0f, ju[5] = -xp * iz;
+  jv[0] = -fmaf(yp, yp, 1.0f), jv[1] = xp * yp, jv[2] = xp, jv[3] = 0.0f, jv[4] = iz, jv[5] = -yp * iz;
+}
+
+// A quad's P points (4, 2 or 1 threads' worth: 1, 2 or 4 threads per point) with
+// their Jacobian rows laid out for the 4x4x1 matrix product: lane q of the quad
+// holds components q (low) and 4 + q (high) of every point's two rows.  The
+// high components past 5 are the row that counts points: 1 in u, 0 in v, and 0.
+template <int P>
+struct QuadRows {
+  float ul[P], uh[P], vl[P], vh[P];
+};
+
+template <int P, int I>
+__device__ __forceinline__ void quad_rows_of(const float (&ju)[6], const float (&jv)[6], QuadRows<P>& r) {
+  constexpr int S = I * (4 / P);  // the quad lane that holds point I
+  const int q = threadIdx.x & 3;
+  const auto pick = [&](float a, float b, float c, float d) { return q == 0 ? a : q == 1 ? b : q == 2 ? c : d; };
+  r.ul[I] = pick(quad_bcast<S>(ju[0]), quad_bcast<S>(ju[1]), quad_bcast<S>(ju[2]), quad_bcast<S>(ju[3]));
+  r.uh[I] = pick(quad_bcast<S>(ju[4]), quad_bcast<S>(ju[5]), 1.0f, 0.0f);
+  r.vl[I] = pick(quad_bcast<S>(jv[0]), quad_bcast<S>(jv[1]), quad_bcast<S>(jv[2]), quad_bcast<S>(jv[3]));
+  r.vh[I] = pick(quad_bcast<S>(jv[4]), quad_bcast<S>(jv[5]), 0.0f, 0.0f);
+  if constexpr (I + 1 < P) quad_rows_of<P, I + 1>(ju, jv, r);
+}
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Add point I of the quad: D += A B with A = J (rows u and v, one product each)
+// and B = (M J | -v | count), in three 4x4 blocks: low x low, low x high, high x
+// high of the 8 x 8 product (H is symmetric).
+template <int P, int I>
+__device__ __forceinline__ void quad_products(const QuadRows<P>& r, float m00, float m01, float m11, float v0, float v1,
+                                              float cnt, f32x4 (&D)[3]) {
+  constexpr int S = I * (4 / P);
+  const int q = threadIdx.x & 3;
+  const auto at = [](float v) {
+    if constexpr (P == 1) return v;
+    return quad_bcast<S>(v);
+  };
+  const float a00 = at(m00), a01 = at(m01), a11 = at(m11), b0 = at(v0), b1 = at(v1), n = at(cnt);
+  const float lu = fmaf(a01, r.vl[I], a00 * r.ul[I]), lv = fmaf(a11, r.vl[I], a01 * r.ul[I]);
+  float hu = fmaf(a01, r.vh[I], a00 * r.uh[I]), hv = fmaf(a11, r.vh[I], a01 * r.uh[I]);
+  hu = q == 2 ? -b0 : q == 3 ? n : hu;
+  hv = q == 2 ? -b1 : hv;
+  D[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(r.ul[I], lu, D[0], 0, 0, 0);
+  D[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(r.ul[I], hu, D[1], 0, 0, 0);
+  D[2] = __builtin_amdgcn_mfma_f32_4x4x1f32(r.uh[I], hu, D[2], 0, 0, 0);
+  D[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(r.vl[I], lv, D[0], 0, 0, 0);
+  D[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(r.vl[I], hv, D[1], 0, 0, 0);
+  D[2] = __builtin_amdgcn_mfma_f32_4x4x1f32(r.vh[I], hv, D[2], 0, 0, 0);
+  if constexpr (I + 1 < P) quad_products<P, I + 1>(r, m00, m01, m11, v0, v1, cnt, D);
+}
+
+// The quads' normal equations summed over the wave: register 4 k + i of lane q
+// (of any quad) is element (i, q) of block k of the quad's product.  On return
+// d[j], j < 3, in the lanes of 16-lane row r holds register 6 (r / 2) + 3 (r % 2)
+// + j summed over the wave's quads, column q = lane % 4.  Twelve values meet by
+// lane swaps and row rotations, where 28 sums held one per thread took three
+// times the steps.
+__device__ __forceinline__ void wave_reduce12(float (&d)[12]) {
+#pragma unroll
+  for (int j = 0; j < 6; ++j) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(d[j]), __float_as_uint(d[j + 6]), false, false);
+    d[j] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(d[j]), __float_as_uint(d[j + 3]), false, false);
+    float v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    v += dpp_ror<8>(v);
+    v += dpp_ror<4>(v);
+    d[j] = v;
+  }
+}
+
+// Words of a wave's partial sums in LDS: 12 registers x 4 columns in the robust
+// mode, and where reduction slot v (H, b, the point count) lies among them.
+constexpr int kWaveWords = 48;
+__device__ __forceinline__ int wave_word(int v) {
+  const int r = (v >= 6) + (v >= 11) + (v >= 15) + (v >= 18) + (v >= 20);
+  int i = r, c = v - (6 * r - r * (r - 1) / 2) + r;  // H(i, c)
+  if (v >= kSlotB) i = v - kSlotB, c = 6;            // b_i
+  if (v >= kSlotE) i = 6, c = 7;                     // the count (slots without a value read it too)
+  const int blk = i < 4 ? (c < 4 ? 0 : 1) : 2;
+  return 4 * (4 * blk + (i & 3)) + (c & 3);
+}
+
+// The wave totals of the final pass's three sums, in every lane.
+__device__ __forceinline__ float wave_sum(float v) {
+  v += dpp_ror<8>(v);
+  v += dpp_ror<4>(v);
+  v += dpp_ror<2>(v);
+  v += dpp_ror<1>(v);
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 }  // namespace dpt
