@@ -363,49 +363,83 @@ __device__ __forceinline__ double invert34_elem(const double* A, int t) {
   return -(A[r] * A[3] + A[4 + r] * A[7] + A[8 + r] * A[11]);
 }
 
-// Constant-velocity start P1 P0^-1 P1 from the pose history (h0 = P0, h1 = P1
-// in LDS), taken relative to the reference (P T_rw^-1), into T0.  Block-wide.
-__device__ __forceinline__ void const_velocity_start(double* T0, const double* rw, const double* h0,
-                                                     const double* h1, double* m1, double* m2) {
-  const int t = threadIdx.x;
-  if (t < 12) m1[t] = invert34_elem(h0, t);
-  if (t >= 16 && t < 28) m2[t - 16] = invert34_elem(rw, t - 16);
-  __syncthreads();
+// The pose arithmetic between frames runs in one wave, an element per lane
+// (lanes t < 12), its operands in LDS: a wave's LDS accesses keep their order,
+// so the steps need no workgroup barrier.  It runs beside the final pass's
+// exchange (about ten LDS round trips against the exchange's memory round
+// trips); with the start slot and the stream's descriptor read in one go, nine
+// frames of 2000 points take 412 instead of 422 us (two threads per point; one
+// thread 466 instead of 483), one frame of 500 points 51.5 instead of 52.4.
+__device__ __forceinline__ void wave_step() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// IT steps of orthonormalize34 on T across the lanes: the same products and sums
+// per element, so the same result.  M: 12 doubles of scratch.
+template <int IT>
+__device__ __forceinline__ void orthonormalize_wave(double* T, double* M, int t) {
+  const int r = (t >> 2) & 3, c = t & 3;
+  const bool rot = t < 12 && c < 3;
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    wave_step();
+    // 3I - R^T R, element (r, c)
+    const double m = (r == c ? 3.0 : 0.0) - (T[r] * T[c] + T[4 + r] * T[4 + c] + T[8 + r] * T[8 + c]);
+    if (rot) M[t] = m;
+    wave_step();
+    const int q = min(r, 2);
+    const double v = 0.5 * (T[4 * q] * M[c] + T[4 * q + 1] * M[4 + c] + T[4 * q + 2] * M[8 + c]);
+    wave_step();
+    if (rot) T[t] = v;
+  }
+  wave_step();
+}
+
+// Constant-velocity start P1 P0^-1 P1 from the pose history (h1 = P1, h0i =
+// P0^-1, in LDS), taken relative to the reference (P T_rw^-1, rwi = T_rw^-1), into
+// T0: the two products (P1 P0^-1) and (P1 T_rw^-1) side by side, then theirs, and
+// the rotation back on SO(3) (one step: the factors are rotations to FP64
+// rounding, or as good as the caller's first two poses).  One wave, t its lane.
+// m1, m2: 12 doubles of scratch each.
+__device__ __forceinline__ void predict_wave(double* T0, const double* rwi, const double* h0i, const double* h1,
+                                             double* m1, double* m2, int t) {
+  wave_step();
+  const int e = t & 15;
+  if (e < 12 && t < 32) {
+    const double v = compose34_elem(h1, t < 16 ? h0i : rwi, e);
+    (t < 16 ? m1 : m2)[e] = v;
+  }
+  wave_step();
   double v = 0.0;
-  if (t < 12) v = compose34_elem(h1, m1, t);  // P1 P0^-1
-  __syncthreads();
-  if (t < 12) m1[t] = v;
-  __syncthreads();
-  if (t < 12) v = compose34_elem(m1, h1, t);  // (P1 P0^-1) P1
-  __syncthreads();
-  if (t < 12) m1[t] = v;
-  __syncthreads();
-  if (t < 12) T0[t] = compose34_elem(m1, m2, t);  // relative to the reference
-  __syncthreads();
-  if (t == 0) orthonormalize34(T0);
-  __syncthreads();
+  if (t < 12) v = compose34_elem(m1, m2, t);
+  if (t < 12) T0[t] = v;
+  orthonormalize_wave<1>(T0, m2, t);
 }
 
 // Start pose relative to the reference for this launch: the given one, one
 // in device memory (a learned proposal), or the constant-velocity prediction
 // from the stream's pose history.  Block-wide;
 // the result, the reference pose and the history land in LDS.
-__device__ __forceinline__ void start_pose(const StartSlot* __restrict__ st, const double* __restrict__ hist,
-                                           double* T0, double* rw, double* h0, double* h1, double* m1, double* m2,
-                                           const uint8_t** l0, int64_t* l0_stride) {
+__device__ __forceinline__ void start_pose(const StartSlot& st, const double* __restrict__ hist, double* T0, double* rw,
+                                           double* rwi, double* h0, double* h0i, double* h1, double* m1, double* m2) {
   const int t = threadIdx.x;
-  __shared__ int sh_mode;
-  if (t < 12) {
-    // kStartDevice: the proposal an earlier launch on this stream wrote
-    T0[t] = st->mode > 1.5 ? st->dev_rel[t] : st->T_rel[t];
-    rw[t] = st->T_rw[t];
-    h0[t] = hist[t];
-    h1[t] = hist[12 + t];
+  if (t < 64) {
+    const double mode = st.mode;
+    if (t < 12) {
+      const double older = gload(hist + t), newer = gload(hist + 12 + t);
+      // kStartDevice: the proposal an earlier launch on this stream wrote
+      T0[t] = mode > 1.5 ? gload(st.dev_rel + t) : st.T_rel[t];
+      rw[t] = st.T_rw[t];
+      rwi[t] = invert34_elem(st.T_rw, t);
+      h0[t] = older;
+      h1[t] = newer;
+    }
+    wave_step();
+    if (t < 12) h0i[t] = invert34_elem(h0, t);
+    if (mode > 0.5 && mode < 1.5) predict_wave(T0, rwi, h0i, h1, m1, m2, t);
   }
-  if (t == 0) sh_mode = st->mode > 1.5 ? kStartDevice : st->mode > 0.5 ? kStartConstVelocity : kStartGiven;
-  if (t == 32) *l0 = st->l0, *l0_stride = st->l0_stride;
   __syncthreads();
-  if (sh_mode == kStartConstVelocity) const_velocity_start(T0, rw, h0, h1, m1, m2);
 }
 
 // ---------------------------------------------------------------- cycle split (DPT_CYCLE_PROFILE builds)
@@ -584,30 +618,35 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
   constexpr int NS = 8 / LPP;                          // samples per thread (8-pixel kernels)
   constexpr int NV = FIXED ? kFixSlots : 32;
   __shared__ CoopStream ss;
-  __shared__ double sh_T0[12], sh_rw[12], sh_h0[12], sh_h1[12], sh_m1[12], sh_m2[12];
+  __shared__ double sh_T0[12], sh_rw[12], sh_rwi[12], sh_h0[12], sh_h0i[12], sh_h1[12], sh_Tf[12], sh_m1[12], sh_m2[12];
   __shared__ __align__(16) float sh_tot[kTotals];
   constexpr int NW = CH / 64;
   __shared__ __align__(16) float sh_red[NW * kWaveWords];
   __shared__ float sh_grp[GENERIC ? CH : 1];  // the whole-workgroup exchange of many-chunk streams
   __shared__ int sh_band[2 * (CH / 64)];
   extern __shared__ __align__(16) uint8_t sh_tile[];  // tile_bytes + kTilePad for the 8-pixel kernels, else none
-  __shared__ const uint8_t* sh_l0;
-  __shared__ int64_t sh_l0_stride;
+  __shared__ __align__(16) StartSlot sh_start;
   const int2 w = work[blockIdx.x];
   if (w.x < 0) return;  // padding slot of the XCD-aware work list
   {
+    // the stream's descriptor and the start slot, every word requested at once:
+    // the slot lies in host memory, where each dependent read is a round trip of
+    // more than a microsecond
+    if (threadIdx.x < sizeof(StartSlot) / 4)
+      reinterpret_cast<uint32_t*>(&sh_start)[threadIdx.x] = gload(reinterpret_cast<const uint32_t*>(start + w.x) + threadIdx.x);
     const uint32_t* src = reinterpret_cast<const uint32_t*>(streams + w.x);
     for (int j = threadIdx.x; j < (int)(sizeof(CoopStream) / 4); j += blockDim.x)
-      reinterpret_cast<uint32_t*>(&ss)[j] = src[j];
+      reinterpret_cast<uint32_t*>(&ss)[j] = gload(src + j);
   }
   __syncthreads();
-  if (start[w.x].bank) {  // the stream's second reference bank, and its window pyramids
+  if (sh_start.bank) {  // the stream's second reference bank, and its window pyramids
     for (int j = threadIdx.x; j < (int)(sizeof(RefCache) / 4); j += blockDim.x)
       reinterpret_cast<uint32_t*>(&ss.a.ref)[j] = reinterpret_cast<const uint32_t*>(&ss.ref_alt)[j];
     if (threadIdx.x == 0) ss.win = ss.win_alt;
-    __syncthreads();
   }
-  start_pose(start + w.x, ss.hist, sh_T0, sh_rw, sh_h0, sh_h1, sh_m1, sh_m2, &sh_l0, &sh_l0_stride);
+  start_pose(sh_start, ss.hist, sh_T0, sh_rw, sh_rwi, sh_h0, sh_h0i, sh_h1, sh_m1, sh_m2);
+  const uint8_t* const l0 = sh_start.l0;  // level 0 of the window's frames, or null
+  const int64_t l0_stride = sh_start.l0_stride;
   const TrackArgs& a = ss.a;
   const IterParams ip(a);
   const PatRegs pregs = pattern_regs(a.pat);
@@ -644,17 +683,17 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
   // WIN: the frames of the launch in order, each from the constant-velocity
   // prediction of the history the previous one extended.  Every chunk keeps its
   // own copy of the history in LDS: the poses are bitwise identical in all
-  // chunks of a stream, so no exchange is needed between frames.
+  // chunks of a stream, so no exchange is needed between frames.  Each start is
+  // computed beside the previous frame's final pass.
   for (int f = 0; f < nf; ++f) {
     uint64_t cf0 = 0;
     if constexpr (kCycleProfile) cf0 = clock64();
-    if (WIN && f > 0) const_velocity_start(sh_T0, sh_rw, sh_h0, sh_h1, sh_m1, sh_m2);
     const PIX* cur = WIN        ? reinterpret_cast<const PIX*>(ss.win + f * ss.win_stride)
                      : FLOAT_PYR ? reinterpret_cast<const PIX*>(a.curf)
                                  : reinterpret_cast<const PIX*>(a.cur);
     // level 0 of the frame: from the source frames themselves when the window
     // pyramids were built without it
-    const PIX* cur0 = WIN && sh_l0 ? reinterpret_cast<const PIX*>(sh_l0 + f * sh_l0_stride) : cur + a.lv[0].off;
+    const PIX* cur0 = WIN && l0 ? reinterpret_cast<const PIX*>(l0 + f * l0_stride) : cur + a.lv[0].off;
     // pose state, identical in every 16-lane row of every chunk of the stream:
     // one element per lane, and every element for the points' transforms
     Pose Tl = (Pose)sh_T0[min(li, 11)];
@@ -799,6 +838,16 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
     }
     uint64_t cp0 = 0;
     if constexpr (kCycleProfile) cp0 = clock64();
+    // What follows a frame's last update, in one wave while wave 0 exchanges the
+    // final cost: the pose's rotation back on SO(3), the history extended by the
+    // frame's estimate T_cw = T_rel T_rw, and the next frame's start.
+    const auto finish_pose = [&] {
+      if (lane < 12) sh_Tf[lane] = (double)Tl, sh_h0i[lane] = invert34_elem(sh_h1, lane), sh_h0[lane] = sh_h1[lane];
+      orthonormalize_wave<2>(sh_Tf, sh_m2, lane);
+      if (lane < 12) sh_h1[lane] = compose34_elem(sh_Tf, sh_rw, lane);
+      if (WIN && f + 1 < nf) predict_wave(sh_T0, sh_rwi, sh_h0i, sh_h1, sh_m1, sh_m2, lane);
+      wave_step();
+    };
     if (!timed_out) {  // final cost-only pass at level 0
       const LevelGeom g = a.lv[0];
       PointSums ps;
@@ -820,59 +869,26 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
       const float E = wave_sum(ps.E), n = wave_sum((ps.ok & (sub == 0)) ? 1.0f : 0.0f);
       if (lane == 0) *reinterpret_cast<float4*>(sh_red + wave * kWaveWords) = make_float4(E, n, 0.0f, 0.0f);
       __syncthreads();
+      if (wave == NW - 1) finish_pose();
       const float mine = wave == 0 ? sum_waves<MIXED, NW>(sh_red, kWaveWords, word_final) : 0.0f;
       if (!stream_total<MIXED, NV, GENERIC>(mine, sh_tot, place, partials, pl, chunk, nch, tag, spin_limit, sh_grp, tot))
         timed_out = true;
       ++tag;
     }
-    if constexpr (kCycleProfile) cy_fr[2] += clock64() - cp0;
-    // the pose in FP64 where thread 0 finishes it (sh_m1 is free between frames)
-    if (threadIdx.x < 12) sh_m1[threadIdx.x] = (double)Tl;
-    __syncthreads();
-    if constexpr (!WIN) {
-      if (chunk == 0 && threadIdx.x == 0) {
-        TrackOut* o = out_ring + (size_t)slot * n_out + w.x;
-        double Tf[12];
-        for (int j = 0; j < 12; ++j) Tf[j] = sh_m1[j];
-        orthonormalize34(Tf);
-        for (int j = 0; j < 12; ++j) {
-          o->T[j] = T[j];
-          o->Td[j] = Tf[j];
-        }
-        // the pose history gains this track's estimate T_cw = T_rel T_rw (every
-        // chunk read the history at its start, before its first exchange)
-        for (int j = 0; j < 12; ++j) {
-          ss.hist[j] = sh_h1[j];
-          ss.hist[12 + j] = compose34_elem(Tf, sh_rw, j);
-        }
-        o->E = tot.E;
-        o->n = (float)K * tot.pts;
-        o->iterations = iterations;
-        for (int j = 0; j < kMaxLevels; ++j) o->iters_per_level[j] = ipl[j];
-        o->n_valid_points = (int)tot.pts;
-        o->status = timed_out ? kStatusTimeout : status;
-        o->samples = samples + (int64_t)K * (int)tot.pts;
-        // the fields reach the host before the sequence number: a system-scope
-        // release (no acquire, so the L2 keeps the reference data it holds)
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
-        o->seq = seq0;
-      }
-      if constexpr (kCycleProfile) cycles_flush(cy, cy_iters, cy_t0, cy_rt0, cy_polls, cy_fr);
-      return;
+    else {
+      if (wave == NW - 1) finish_pose();
+      __syncthreads();
     }
     uint64_t ct0 = 0;
-    if constexpr (kCycleProfile) ct0 = clock64();
-    if (threadIdx.x == 0) {
-      double Tf[12];
-      for (int j = 0; j < 12; ++j) Tf[j] = sh_m1[j];
-      orthonormalize34(Tf);
-      for (int j = 0; j < 12; ++j) sh_m1[j] = Tf[j];
-      if (chunk == 0) {
-        TrackOut* o = out_ring + (size_t)((slot + f) % kRing) * n_out + w.x;
-        for (int j = 0; j < 12; ++j) {
-          o->T[j] = T[j];
-          o->Td[j] = Tf[j];
-        }
+    if constexpr (kCycleProfile) ct0 = clock64(), cy_fr[2] += ct0 - cp0;
+    // the results, written by a wave that no exchange waits for first
+    if (chunk == 0 && wave == NW - 1) {
+      TrackOut* o = out_ring + (size_t)(WIN ? (slot + f) % kRing : slot) * n_out + w.x;
+      if (lane < 12) {
+        o->T[lane] = (float)Tl;
+        o->Td[lane] = sh_Tf[lane];
+      }
+      if (lane == 16) {
         o->E = tot.E;
         o->n = (float)K * tot.pts;
         o->iterations = iterations;
@@ -881,28 +897,24 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
         o->status = timed_out ? kStatusTimeout : status;
         o->samples = samples + (int64_t)K * (int)tot.pts;
         // a chunk gave up: so do the frames after this one
-        if (timed_out)
+        if (WIN && timed_out)
           for (int q = f + 1; q < nf; ++q) out_ring[(size_t)((slot + q) % kRing) * n_out + w.x].status = kStatusTimeout;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");  // the fields reach the host before the sequence numbers
+      }
+      // the fields reach the host before the sequence number: a system-scope
+      // release (no acquire, so the L2 keeps the reference data it holds)
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+      if (lane == 16) {
         o->seq = seq0 + f;
-        if (timed_out)
+        if (WIN && timed_out)
           for (int q = f + 1; q < nf; ++q) out_ring[(size_t)((slot + q) % kRing) * n_out + w.x].seq = seq0 + q;
       }
     }
-    __syncthreads();
-    // the history gains this frame's estimate T_cw = T_rel T_rw
-    if (threadIdx.x < 12) {
-      const double v = compose34_elem(sh_m1, sh_rw, threadIdx.x);
-      sh_h0[threadIdx.x] = sh_h1[threadIdx.x];
-      sh_h1[threadIdx.x] = v;
-    }
-    __syncthreads();
     if constexpr (kCycleProfile) cy_fr[4] += clock64() - ct0;
     if (timed_out) break;
   }
   // the stream's history for the next launch (every chunk read it at its start,
   // before its first exchange)
-  if (WIN && chunk == 0 && threadIdx.x < 12) {
+  if (chunk == 0 && threadIdx.x < 12) {
     ss.hist[threadIdx.x] = sh_h0[threadIdx.x];
     ss.hist[12 + threadIdx.x] = sh_h1[threadIdx.x];
   }
