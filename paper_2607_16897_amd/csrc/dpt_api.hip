@@ -1028,7 +1028,9 @@ int coop_variant(const dpt_params& p, int mode) {
   const int pairs = pair_track(p, mode) ? kCoopPairs : 0;
   if (p.precision == DPT_PREC_MIXED) return kCoopMixed | pairs;
   int v = (p.flags & DPT_FLAG_FIXED_H) ? kCoopFixedH : kCoopFP32;
-  if (generic_track(p)) v |= kCoopGeneric | ((p.flags & DPT_FLAG_GAUSS_F32) ? kCoopFloatPyr : 0);
+  if (generic_track(p))
+    v |= kCoopGeneric | ((p.flags & DPT_FLAG_GAUSS_F32) ? kCoopFloatPyr : 0) |
+         (p.n_pattern <= kMaxSlotPattern ? kCoopSlots : 0);
   return v | pairs;
 }
 

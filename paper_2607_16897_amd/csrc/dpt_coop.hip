@@ -500,10 +500,11 @@ hipError_t read_cycle_profile(uint64_t* host, int n_slots, bool reset) {
 
 // ---------------------------------------------------------------- LDS tiles of the current level
 
-// Bytes of a level a workgroup of the 8-pixel kernels stages in LDS: levels of
-// up to this size whole, larger ones as the band of rows its points' taps span.
+// Bytes of a level a workgroup stages in LDS (every kernel with its templates in
+// registers): levels of up to this size whole, larger ones as the band of rows
+// its points' taps span.
 // Launches of many workgroups (two per compute unit, 160 KB of LDS each) take
-// the small tile: with the kernel's own ~2 KB a workgroup stays within 64 KB.
+// the small tile: with the kernel's own ~3 KB a workgroup stays within 64 KB.
 // A launch small enough to run one workgroup per compute unit (the plain-launch
 // path) takes the large one, which holds a 752x480 frame's second level whole
 // and ~190 rows of its first.
@@ -523,12 +524,12 @@ constexpr int kBandMargin = 4;
 // Block-wide (NW waves); the caller has finished every read of the previous
 // tile.  can: the thread's point may be valid (its validity at this level is
 // still being loaded with its template: the band does not wait for it).
-template <int NW, class PR>
+template <int NW, class PIX, class PR>
 __device__ __forceinline__ Tile8 stage_tile(const IterParams& a, const PatRegs& pat, const LevelGeom& g,
-                                            const uint8_t* img, const float* T, const PR& pr, bool can,
+                                            const PIX* img, const float* T, const PR& pr, bool can,
                                             uint8_t* tile_mem, int tile_bytes, int* sh_band) {
-  const int W = g.W, H = g.H;
-  const int rows_fit = (tile_bytes - 32) / W;
+  const int W = g.W, H = g.H, row = W * (int)sizeof(PIX);
+  const int rows_fit = (tile_bytes - 32) / row;
   int lo = 0, hi = H - 1;
   if (rows_fit < H) {
     float X, Y, Z;
@@ -553,7 +554,7 @@ __device__ __forceinline__ Tile8 stage_tile(const IterParams& a, const PatRegs& 
   }
   const uintptr_t sa = reinterpret_cast<uintptr_t>(img + (int64_t)lo * W), s0 = sa & ~(uintptr_t)15;
   const int delta = (int)(sa - s0);
-  const int ng = (delta + (hi - lo + 1) * W + 15) >> 4;
+  const int ng = (delta + (hi - lo + 1) * row + 15) >> 4;
   // Global memory straight into LDS (global_load_lds_dwordx4): each wave moves
   // 64 consecutive granules per instruction, every load in flight at once and
   // no registers held.  The caller waits for all of them (s_waitcnt 0, then a
@@ -595,11 +596,14 @@ __device__ __forceinline__ Tile8 no_tile(uint8_t* tile_mem) {
 // counts are reduced and exchanged (16 slots), and each level's constant H
 // comes factored from the precompute.
 // GENERIC: any pattern K (four lanes per point, CH / 4 points per chunk) on
-// uint8 levels or (PIX = float) the floating-point Gaussian pyramid.
+// uint8 levels or (PIX = float) the floating-point Gaussian pyramid; 2: K up to
+// kMaxSlotPattern, the templates in registers and the levels in LDS tiles like
+// the 8-pixel kernels'; 1: larger patterns, both read from global memory in
+// every iteration.
 //
 // LPP = 2 (8-pixel pattern only): two threads per point, four samples each;
 // a chunk of CH threads holds CH / 2 points.
-template <int CH, bool MIXED, bool FIXED, bool GENERIC = false, class PIX = uint8_t, bool WIN = false, int LPP = 1>
+template <int CH, bool MIXED, bool FIXED, int GENERIC = 0, class PIX = uint8_t, bool WIN = false, int LPP = 1>
 __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __restrict__ streams,
                                                            const int2* __restrict__ work,
                                                            const StartSlot* __restrict__ start,
@@ -611,11 +615,14 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
   static_assert(LPP == 1 || (LPP == 2 && !GENERIC), "two threads per point: the 8-pixel kernels");
   using PR8 = typename std::conditional<MIXED, PointRegsH, PointRegs>::type;
   using PR4 = typename std::conditional<MIXED, PointRegsH4, PointRegs4>::type;
-  using PR = typename std::conditional<GENERIC, PointGeo, typename std::conditional<LPP == 2, PR4, PR8>::type>::type;
+  using PR = typename std::conditional<
+      GENERIC == 1, PointGeo,
+      typename std::conditional<GENERIC == 2, PointRegsQ, typename std::conditional<LPP == 2, PR4, PR8>::type>::type>::type;
+  constexpr bool TILED = GENERIC != 1;  // templates in registers, levels in LDS tiles
   constexpr bool FLOAT_PYR = std::is_same<PIX, float>::value;
   constexpr int TPP = GENERIC ? kLanesPerPoint : LPP;  // threads per point
   constexpr int PPC = CH / TPP;                        // points per chunk
-  constexpr int NS = 8 / LPP;                          // samples per thread (8-pixel kernels)
+  constexpr int NS = GENERIC ? kQuadSlots : 8 / LPP;   // samples per thread (TILED)
   constexpr int NV = FIXED ? kFixSlots : 32;
   __shared__ CoopStream ss;
   __shared__ double sh_T0[12], sh_rw[12], sh_rwi[12], sh_h0[12], sh_h0i[12], sh_h1[12], sh_Tf[12], sh_m1[12], sh_m2[12];
@@ -624,7 +631,7 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
   __shared__ __align__(16) float sh_red[NW * kWaveWords];
   __shared__ float sh_grp[GENERIC ? CH : 1];  // the whole-workgroup exchange of many-chunk streams
   __shared__ int sh_band[2 * (CH / 64)];
-  extern __shared__ __align__(16) uint8_t sh_tile[];  // tile_bytes + kTilePad for the 8-pixel kernels, else none
+  extern __shared__ __align__(16) uint8_t sh_tile[];  // tile_bytes + kTilePad (TILED), else none
   __shared__ __align__(16) StartSlot sh_start;
   const int2 w = work[blockIdx.x];
   if (w.x < 0) return;  // padding slot of the XCD-aware work list
@@ -672,6 +679,30 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
   const bool can = load_geometry_once(a, i, pr, &j0);
   float ju[6], jv[6];
   warp_rows(pr.X0, pr.Y0, pr.Z0, ju, jv);
+  const auto sample_offsets = [&](int W, int(&off)[NS]) {
+    if constexpr (GENERIC)
+      quad_offsets(a.pat, W, sub, off);
+    else
+      lane_offsets<NS>(pregs, W, sub, off);
+  };
+  // this thread's sums at pose T: its slots of the point, or the quad's all
+  const int filled = GENERIC ? (K - sub + kLanesPerPoint - 1) / kLanesPerPoint : NS;
+  const auto sample = [&](auto cost_only, const LevelGeom& g, const PIX* img, const Tile8& tile, const int(&off)[NS],
+                          const float(&T)[12]) {
+    constexpr bool C = decltype(cost_only)::value;
+    PointSums ps;
+    if constexpr (GENERIC == 2) {
+      // up to 28 samples (a 5x5 patch) fill seven slots
+      ps = K <= 7 * kLanesPerPoint ? sample_point<C, FIXED, PIX, 7>(ip, pregs, off, g, img, tile, T, pr, filled)
+                                   : sample_point<C, FIXED, PIX, NS>(ip, pregs, off, g, img, tile, T, pr, filled);
+    } else if constexpr (GENERIC == 1) {
+      ps = sample_point_generic<C, FIXED, PIX>(a, a.pat, g, img, T, pr, sub);
+    } else {
+      ps = sample_point<C, FIXED, PIX, NS>(ip, pregs, off, g, img, tile, T, pr);
+    }
+    if constexpr (GENERIC) quad_sums<C, FIXED>(ps);
+    return ps;
+  };
   constexpr int QP = 4 / TPP;  // points per quad
   QuadRows<FIXED ? 1 : QP> rows;
   if constexpr (!FIXED) quad_rows_of<QP, 0>(ju, jv, rows);
@@ -720,13 +751,12 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
       int offs[NS];
       const int64_t e = (int64_t)l * a.ref.cap + j0;
       const uint8_t vb = gload(a.ref.valid + e);
-      if constexpr (GENERIC) {
+      if constexpr (!TILED) {
         pr.s0 = e * K;
       } else {
         load_template(a, e, sub, pr);
-        lane_offsets<NS>(pregs, g.W, sub, offs);
-        tile = stage_tile<NW>(ip, pregs, g, reinterpret_cast<const uint8_t*>(img), T, pr, can, sh_tile, tile_bytes,
-                              sh_band);
+        sample_offsets(g.W, offs);
+        tile = stage_tile<NW>(ip, pregs, g, img, T, pr, can, sh_tile, tile_bytes, sh_band);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         if (l == 0) tile0 = tile, at0 = true;
@@ -746,11 +776,7 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
       for (int it = 0; it < ip.max_iters; ++it) {
         uint64_t c0 = 0, c1 = 0, c2 = 0;
         if constexpr (kCycleProfile) c0 = clock64();
-        PointSums ps;
-        if constexpr (GENERIC)
-          ps = sample_point_generic<false, FIXED, PIX>(a, a.pat, g, img, T, pr, sub);
-        else
-          ps = sample_point8<false, FIXED, PR, NS>(ip, pregs, offs, g, reinterpret_cast<const uint8_t*>(img), tile, T, pr);
+        const PointSums ps = sample(std::false_type{}, g, img, tile, offs, T);
         if constexpr (kCycleProfile) c1 = clock64();
         if constexpr (FIXED) {
           // b = -(ju v0 + jv v1) of the thread's samples (of a generic quad: once)
@@ -784,7 +810,7 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
         if constexpr (kCycleProfile) c2 = clock64();
         int polls = 0;
         const float mine = wave == 0 ? sum_waves<MIXED, NW>(sh_red, kWaveWords, word) : 0.0f;
-        if (!stream_total<MIXED, NV, GENERIC>(mine, sh_tot, place, partials, pl, chunk, nch, tag, spin_limit, sh_grp, tot,
+        if (!stream_total<MIXED, NV, GENERIC != 0>(mine, sh_tot, place, partials, pl, chunk, nch, tag, spin_limit, sh_grp, tot,
                                               &polls)) {
           timed_out = stop = true;
           break;
@@ -850,28 +876,21 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
     };
     if (!timed_out) {  // final cost-only pass at level 0
       const LevelGeom g = a.lv[0];
-      PointSums ps;
-      if (GENERIC || !at0) {  // the levels stopped above 0: level 0's registers, taps from global memory
+      if (!at0) {  // the levels stopped above 0: level 0's registers, taps from global memory
         pr.ok = can & (gload(a.ref.valid + j0) != 0);
-        if constexpr (GENERIC)
-          pr.s0 = (int64_t)j0 * K;
-        else
-          load_template(a, j0, sub, pr);
+        if constexpr (TILED) load_template(a, j0, sub, pr);
       }
-      if constexpr (GENERIC) {
-        ps = sample_point_generic<true, FIXED, PIX>(a, a.pat, g, WIN ? cur0 : cur + g.off, T, pr, sub);
-        ps.E = sub == 0 ? ps.E : 0.0f;
-      } else {
-        int offs[NS];
-        lane_offsets<NS>(pregs, g.W, sub, offs);
-        ps = sample_point8<true, FIXED, PR, NS>(ip, pregs, offs, g, WIN ? cur0 : cur + g.off, tile0, T, pr);
-      }
+      if constexpr (!TILED) pr.s0 = (int64_t)j0 * K, pr.ok = can & (gload(a.ref.valid + j0) != 0);
+      int offs[NS];
+      if constexpr (TILED) sample_offsets(g.W, offs);
+      PointSums ps = sample(std::true_type{}, g, WIN ? cur0 : cur + g.off, tile0, offs, T);
+      if (GENERIC) ps.E = sub == 0 ? ps.E : 0.0f;
       const float E = wave_sum(ps.E), n = wave_sum((ps.ok & (sub == 0)) ? 1.0f : 0.0f);
       if (lane == 0) *reinterpret_cast<float4*>(sh_red + wave * kWaveWords) = make_float4(E, n, 0.0f, 0.0f);
       __syncthreads();
       if (wave == NW - 1) finish_pose();
       const float mine = wave == 0 ? sum_waves<MIXED, NW>(sh_red, kWaveWords, word_final) : 0.0f;
-      if (!stream_total<MIXED, NV, GENERIC>(mine, sh_tot, place, partials, pl, chunk, nch, tag, spin_limit, sh_grp, tot))
+      if (!stream_total<MIXED, NV, GENERIC != 0>(mine, sh_tot, place, partials, pl, chunk, nch, tag, spin_limit, sh_grp, tot))
         timed_out = true;
       ++tag;
     }
@@ -929,33 +948,46 @@ static const void* coop_fn(int variant) {
   if (variant & kCoopGeneric) {
     if (CH != kGenericThreads) return nullptr;
     constexpr int G = kGenericThreads;
-    switch (variant & (kCoopFixedH | kCoopFloatPyr)) {
-      case 0: return reinterpret_cast<const void*>(&coop_track_kernel<G, false, false, true, uint8_t, WIN>);
-      case kCoopFixedH: return reinterpret_cast<const void*>(&coop_track_kernel<G, false, true, true, uint8_t, WIN>);
-      case kCoopFloatPyr:
-        return WIN ? nullptr : reinterpret_cast<const void*>(&coop_track_kernel<G, false, false, true, float>);
-      default: return WIN ? nullptr : reinterpret_cast<const void*>(&coop_track_kernel<G, false, true, true, float>);
+    switch (variant & (kCoopFixedH | kCoopFloatPyr | kCoopSlots)) {
+      case 0: return reinterpret_cast<const void*>(&coop_track_kernel<G, false, false, 1, uint8_t, WIN>);
+      case kCoopFixedH: return reinterpret_cast<const void*>(&coop_track_kernel<G, false, true, 1, uint8_t, WIN>);
+      case kCoopSlots: return reinterpret_cast<const void*>(&coop_track_kernel<G, false, false, 2, uint8_t, WIN>);
+      case kCoopSlots | kCoopFixedH:
+        return reinterpret_cast<const void*>(&coop_track_kernel<G, false, true, 2, uint8_t, WIN>);
+      default: break;
     }
+    if constexpr (!WIN) {  // no window tracking of the floating-point pyramid
+      switch (variant & (kCoopFixedH | kCoopSlots)) {
+        case 0: return reinterpret_cast<const void*>(&coop_track_kernel<G, false, false, 1, float>);
+        case kCoopFixedH: return reinterpret_cast<const void*>(&coop_track_kernel<G, false, true, 1, float>);
+        case kCoopSlots: return reinterpret_cast<const void*>(&coop_track_kernel<G, false, false, 2, float>);
+        default: return reinterpret_cast<const void*>(&coop_track_kernel<G, false, true, 2, float>);
+      }
+    }
+    return nullptr;
   }
   if (variant & kCoopPairs) {
     if (CH == 64) return nullptr;  // a pair chunk holds 64 or 128 points
     switch (variant & ~kCoopPairs) {
       case kCoopFP32:
-        return reinterpret_cast<const void*>(&coop_track_kernel<CH, false, false, false, uint8_t, WIN, 2>);
+        return reinterpret_cast<const void*>(&coop_track_kernel<CH, false, false, 0, uint8_t, WIN, 2>);
       case kCoopMixed:
-        return reinterpret_cast<const void*>(&coop_track_kernel<CH, true, false, false, uint8_t, WIN, 2>);
+        return reinterpret_cast<const void*>(&coop_track_kernel<CH, true, false, 0, uint8_t, WIN, 2>);
       case kCoopFixedH:
-        return reinterpret_cast<const void*>(&coop_track_kernel<CH, false, true, false, uint8_t, WIN, 2>);
+        return reinterpret_cast<const void*>(&coop_track_kernel<CH, false, true, 0, uint8_t, WIN, 2>);
       default: return nullptr;
     }
   }
   switch (variant) {
-    case kCoopFP32: return reinterpret_cast<const void*>(&coop_track_kernel<CH, false, false, false, uint8_t, WIN>);
-    case kCoopMixed: return reinterpret_cast<const void*>(&coop_track_kernel<CH, true, false, false, uint8_t, WIN>);
-    case kCoopFixedH: return reinterpret_cast<const void*>(&coop_track_kernel<CH, false, true, false, uint8_t, WIN>);
+    case kCoopFP32: return reinterpret_cast<const void*>(&coop_track_kernel<CH, false, false, 0, uint8_t, WIN>);
+    case kCoopMixed: return reinterpret_cast<const void*>(&coop_track_kernel<CH, true, false, 0, uint8_t, WIN>);
+    case kCoopFixedH: return reinterpret_cast<const void*>(&coop_track_kernel<CH, false, true, 0, uint8_t, WIN>);
     default: return nullptr;
   }
 }
+
+// Whether a variant stages its levels in LDS tiles.
+static bool tiled(int variant) { return !(variant & kCoopGeneric) || (variant & kCoopSlots); }
 
 // Co-resident workgroups per CU: the least over every variant at this chunk size.
 template <int CH>
@@ -971,13 +1003,17 @@ static int coop_blocks_per_cu() {
                       kCoopGeneric,
                       kCoopGeneric | kCoopFixedH,
                       kCoopGeneric | kCoopFloatPyr,
-                      kCoopGeneric | kCoopFixedH | kCoopFloatPyr};
+                      kCoopGeneric | kCoopFixedH | kCoopFloatPyr,
+                      kCoopGeneric | kCoopSlots,
+                      kCoopGeneric | kCoopSlots | kCoopFixedH,
+                      kCoopGeneric | kCoopSlots | kCoopFloatPyr,
+                      kCoopGeneric | kCoopSlots | kCoopFixedH | kCoopFloatPyr};
     int best = 1 << 30;
     for (int v : vs)
       for (const void* f : {coop_fn<CH, false>(v), coop_fn<CH, true>(v)}) {
         if (!f) continue;
         int k = 0;
-        const size_t dyn = (v & kCoopGeneric) ? 0 : kTileBytesSmall + kTilePad;
+        const size_t dyn = tiled(v) ? kTileBytesSmall + kTilePad : 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&k, f, CH, dyn) != hipSuccess) {
           (void)hipGetLastError();
           k = 0;
@@ -1028,13 +1064,13 @@ static hipError_t coop_launch_k(const CoopStream* d_streams, const int2* d_work,
   const void* fn = n_frames > 0 ? coop_fn<CH, true>(variant) : coop_fn<CH, false>(variant);
   if (!fn) return hipErrorInvalidValue;
   const bool plain = 4 * n_work <= coop_max_blocks(CH);
-  // the 8-pixel kernels' level tile: large where the launch is small enough for
-  // one workgroup per compute unit, else small (two per compute unit)
-  int tile_bytes = (variant & kCoopGeneric) ? 0 : plain ? kTileBytesLarge : kTileBytesSmall;
+  // the level tile: large where the launch is small enough for one workgroup per
+  // compute unit, else small (two per compute unit)
+  int tile_bytes = !tiled(variant) ? 0 : plain ? kTileBytesLarge : kTileBytesSmall;
   const size_t dyn = tile_bytes ? (size_t)tile_bytes + kTilePad : 0;
   if (dyn > 64 * 1024) {
-    static bool raised[2][32] = {};  // per window form and variant: the attribute is set once
-    bool& r = raised[n_frames > 0][variant & 31];
+    static bool raised[2][64] = {};  // per window form and variant: the attribute is set once
+    bool& r = raised[n_frames > 0][variant & 63];
     if (!r) {
       const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
       if (e != hipSuccess) return e;

@@ -992,6 +992,24 @@ __device__ __forceinline__ void accumulate_point(const TrackArgs& a, const PatRe
 
 // ---------------------------------------------------------------- LDS-staged accumulation (K = 8)
 
+// Two neighbouring pixels, read in one go from any address.
+template <class PIX>
+struct __attribute__((packed)) PixPair {
+  uint16_t w;
+  __device__ __forceinline__ void load(const __attribute__((address_space(1))) PIX* p) {
+    w = ((const __attribute__((address_space(1))) PixPair*)p)->w;
+  }
+  __device__ __forceinline__ float left() const { return (float)(w & 0xffu); }
+  __device__ __forceinline__ float right() const { return (float)(w >> 8); }
+};
+template <>
+struct __attribute__((packed)) PixPair<float> {
+  float a, b;
+  __device__ __forceinline__ void load(const __attribute__((address_space(1))) float* p) { a = p[0], b = p[1]; }
+  __device__ __forceinline__ float left() const { return a; }
+  __device__ __forceinline__ float right() const { return b; }
+};
+
 // The bytes of the current level a workgroup holds in LDS: rows lo..hi
 // (inclusive), each W bytes, byte (r, x) of the level at offset
 // delta + (r - lo) * W + x.  `bytes` is how many are valid from the start.
@@ -1025,22 +1043,30 @@ struct PointSums {
   bool ok;
 };
 
-// The sums of a point's samples for the 8-pixel pattern (Eq.(2), Eq.(5)), with the
-// taps read from the workgroup's LDS copy of the level where every point of the
-// wave lies inside it (else from global memory, as accumulate_point).  The
-// pattern offsets are whole pixels, so all 8 samples share the point's bilinear
-// fractions: the weights are formed once per point.  Branch-free: an unusable
+// The sums of a point's samples with their templates in registers (Eq.(2),
+// Eq.(5)), with the taps read from the workgroup's LDS copy of the level where
+// every point of the wave lies inside it (else from global memory, as
+// accumulate_point).  The pattern offsets are whole pixels, so all samples share
+// the point's bilinear fractions: the weights are formed once per point.  Branch-free: an unusable
 // point (reference-invalid, behind the camera or a pattern position outside the
-// level) runs the same instructions and its sums are selected to zero.
+// level) runs the same instructions and its sums are selected to zero.  Taps
+// from global memory are read two pixels at a time, all of a batch in flight
+// (one at a time: 397 against 386 us for a window of 9 frames).
 // COST_ONLY: only the cost (the final pass).  Otherwise m and v, no cost (it is
 // read only after the final pass).  FIXED: no weights, v only.
 //
-// NS = 4: the point has two threads, each taking four of its samples with
-// their offsets `off`; the point's sums are the two threads' added.
-template <bool COST_ONLY, bool FIXED, class PR, int NS>
-__device__ __forceinline__ PointSums sample_point8(const IterParams& a, const PatRegs& pat, const int (&off)[NS],
-                                                   const LevelGeom& g, const uint8_t* __restrict__ img,
-                                                   const Tile8& tile, const float* T, const PR& pr) {
+// The point has one thread (all 8 samples), two (NS = 4, each taking four of the
+// samples with their offsets `off`) or, for other patterns, four (NS = 13 or 7
+// slots, of which the lane fills `filled`); the point's sums are its threads'
+// added.  A slot past `filled` has a zero gradient and repeats a sample of the
+// pattern, so only the cost has to leave it out.  PIX: uint8 levels or the
+// floating-point Gaussian pyramid.
+template <bool COST_ONLY, bool FIXED, class PIX, int NS, class PR>
+__device__ __forceinline__ PointSums sample_point(const IterParams& a, const PatRegs& pat, const int* off,
+                                                  const LevelGeom& g, const PIX* __restrict__ img, const Tile8& tile,
+                                                  const float* T, const PR& pr, int filled = NS) {
+  constexpr bool BYTES = std::is_same<PIX, uint8_t>::value;
+  constexpr bool QUAD = NS != 8 && NS != 4;
   const float kH = FIXED ? 0.0f : a.huber_k;
   // Huber weight min(1, k / |r|); without a threshold every weight is 1
   const float kHw = kH > 0.0f ? kH : __builtin_inff();
@@ -1053,67 +1079,97 @@ __device__ __forceinline__ PointSums sample_point8(const IterParams& a, const Pa
   v = ok ? v : 0.0f;
   const Cell q0 = cell_of(u, v);
   const int iu = q0.iu, iv = q0.iv, W = g.W;
-  float t00[NS], t10[NS], t01[NS], t11[NS];
+  // Every usable point of the wave inside the tile?  An unusable one reads from
+  // the tile position of a pattern whose top-left sample sits at the tile's first
+  // byte: a few rows, inside the allocation whatever the level, and masked below.
+  // Other patterns may span more rows than the tile holds: their unusable points
+  // read its first bytes.
   const bool in_tile = !ok | ((iv + (int)pat.dy_min >= tile.lo) & (iv + (int)pat.dy_max + 1 <= tile.hi));
-  if (__all(in_tile)) {
-    // Every usable point of the wave lies inside the tile.  An unusable one
-    // reads from the tile position of a pattern whose top-left sample sits at
-    // the tile's first byte: a few rows, inside the allocation whatever the
-    // level, and masked below.  All 16 pairs of words are requested before any
-    // is used (one LDS round trip per point).
-    const uint32_t lb = (uint32_t)(uintptr_t)tile.lds;
-    const int base = (int)lb + tile.delta +
-                     (ok ? (iv - tile.lo) * W + iu : -((int)pat.dy_min * W + (int)pat.dx_min));
-    uint32_t w[NS][4];
-    int bt[NS];
-#pragma unroll
-    for (int k = 0; k < NS; ++k) {
-      bt[k] = base + off[k];
-      const __attribute__((address_space(3))) uint32_t* p =
-          (const __attribute__((address_space(3))) uint32_t*)(uintptr_t)(uint32_t)(bt[k] & ~3);
-      const __attribute__((address_space(3))) uint32_t* q =
-          (const __attribute__((address_space(3))) uint32_t*)(uintptr_t)(uint32_t)((bt[k] + W) & ~3);
-      w[k][0] = p[0], w[k][1] = p[1], w[k][2] = q[0], w[k][3] = q[1];
-    }
-#pragma unroll
-    for (int k = 0; k < NS; ++k) {
-      const uint32_t top = __builtin_amdgcn_alignbyte(w[k][1], w[k][0], (uint32_t)bt[k]);
-      const uint32_t bot = __builtin_amdgcn_alignbyte(w[k][3], w[k][2], (uint32_t)(bt[k] + W));
-      t00[k] = (float)(top & 0xffu), t10[k] = (float)((top >> 8) & 0xffu);
-      t01[k] = (float)(bot & 0xffu), t11[k] = (float)((bot >> 8) & 0xffu);
-    }
-  } else {
-    const __attribute__((address_space(1))) uint8_t* gimg = (const __attribute__((address_space(1))) uint8_t*)img;
-    const int base = iv * W + iu;
-#pragma unroll
-    for (int k = 0; k < NS; ++k) {
-      const int o = ok ? base + off[k] : 0;  // an unusable point reads the level's first pixels
-      t00[k] = gimg[o], t10[k] = gimg[o + 1], t01[k] = gimg[o + W], t11[k] = gimg[o + W + 1];
-    }
-  }
   PointSums s = {};
   s.ok = ok;
+  // Up to eight samples at a time: all their taps are requested before any is
+  // used (one LDS round trip); 13 at once would not fit the registers.
+  constexpr int B = NS > 8 ? 7 : NS;
 #pragma unroll
-  for (int k = 0; k < NS; ++k) {
-    const float Ic = bilin_mix(q0.w, t00[k], t10[k], t01[k], t11[k]);
-    const float r = pr.i0(k) - Ic;
-    if constexpr (COST_ONLY) {
-      const float ar = fabsf(r);
-      const bool hub = (kH > 0.f) & (ar > kH);
-      s.E += hub ? kH * (ar - 0.5f * kH) : 0.5f * r * r;
-    } else {
-      const float gx = pr.gx(k), gy = pr.gy(k);
-      if constexpr (FIXED) {
-        s.v0 = fmaf(gx, r, s.v0);
-        s.v1 = fmaf(gy, r, s.v1);
+  for (int k0 = 0; k0 < NS; k0 += B) {
+    float t00[B], t10[B], t01[B], t11[B];
+    if (__all(in_tile)) {
+      const int lb = (int)(uint32_t)(uintptr_t)tile.lds;
+      const int lbase = lb + tile.delta +
+                        (int)sizeof(PIX) * (ok ? (iv - tile.lo) * W + iu : -((int)pat.dy_min * W + (int)pat.dx_min));
+      const int Wt = QUAD && !ok ? 0 : W;
+      if constexpr (BYTES) {
+        uint32_t w[B][4];
+        int bt[B];
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+          if (k0 + k >= NS) continue;
+          bt[k] = QUAD && !ok ? lb : lbase + off[k0 + k];
+          const __attribute__((address_space(3))) uint32_t* p =
+              (const __attribute__((address_space(3))) uint32_t*)(uintptr_t)(uint32_t)(bt[k] & ~3);
+          const __attribute__((address_space(3))) uint32_t* q =
+              (const __attribute__((address_space(3))) uint32_t*)(uintptr_t)(uint32_t)((bt[k] + Wt) & ~3);
+          w[k][0] = p[0], w[k][1] = p[1], w[k][2] = q[0], w[k][3] = q[1];
+        }
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+          if (k0 + k >= NS) continue;
+          const uint32_t top = __builtin_amdgcn_alignbyte(w[k][1], w[k][0], (uint32_t)bt[k]);
+          const uint32_t bot = __builtin_amdgcn_alignbyte(w[k][3], w[k][2], (uint32_t)(bt[k] + Wt));
+          t00[k] = (float)(top & 0xffu), t10[k] = (float)((top >> 8) & 0xffu);
+          t01[k] = (float)(bot & 0xffu), t11[k] = (float)((bot >> 8) & 0xffu);
+        }
       } else {
-        const float w = fminf(1.0f, kHw * __builtin_amdgcn_rcpf(fabsf(r)));
-        const float wgx = w * gx, wgy = w * gy;
-        s.m00 = fmaf(wgx, gx, s.m00);
-        s.m01 = fmaf(wgx, gy, s.m01);
-        s.m11 = fmaf(wgy, gy, s.m11);
-        s.v0 = fmaf(wgx, r, s.v0);
-        s.v1 = fmaf(wgy, r, s.v1);
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+          if (k0 + k >= NS) continue;
+          const __attribute__((address_space(3))) float* p =
+              (const __attribute__((address_space(3))) float*)(uintptr_t)(uint32_t)(ok ? lbase + 4 * off[k0 + k] : lb);
+          t00[k] = p[0], t10[k] = p[1], t01[k] = p[Wt], t11[k] = p[Wt + 1];
+        }
+      }
+    } else {
+      const __attribute__((address_space(1))) PIX* gimg = (const __attribute__((address_space(1))) PIX*)img;
+      const int gbase = iv * W + iu;
+      PixPair<PIX> r[B][2];
+#pragma unroll
+      for (int k = 0; k < B; ++k) {
+        if (k0 + k >= NS) continue;
+        const uint32_t o = ok ? gbase + off[k0 + k] : 0, q = o + W;  // an unusable point: the level's first pixels
+        r[k][0].load(gimg + o), r[k][1].load(gimg + q);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = 0; k < B; ++k) {
+        if (k0 + k >= NS) continue;
+        t00[k] = r[k][0].left(), t10[k] = r[k][0].right(), t01[k] = r[k][1].left(), t11[k] = r[k][1].right();
+      }
+    }
+#pragma unroll
+    for (int kk = 0; kk < B; ++kk) {
+      const int k = k0 + kk;
+      if (k >= NS) continue;
+      const float Ic = bilin_mix(q0.w, t00[kk], t10[kk], t01[kk], t11[kk]);
+      const float r = pr.i0(k) - Ic;
+      if constexpr (COST_ONLY) {
+        const float ar = fabsf(r);
+        const bool hub = (kH > 0.f) & (ar > kH);
+        const float rho = hub ? kH * (ar - 0.5f * kH) : 0.5f * r * r;
+        s.E += k < filled ? rho : 0.0f;
+      } else {
+        const float gx = pr.gx(k), gy = pr.gy(k);
+        if constexpr (FIXED) {
+          s.v0 = fmaf(gx, r, s.v0);
+          s.v1 = fmaf(gy, r, s.v1);
+        } else {
+          const float w = fminf(1.0f, kHw * __builtin_amdgcn_rcpf(fabsf(r)));
+          const float wgx = w * gx, wgy = w * gy;
+          s.m00 = fmaf(wgx, gx, s.m00);
+          s.m01 = fmaf(wgx, gy, s.m01);
+          s.m11 = fmaf(wgy, gy, s.m11);
+          s.v0 = fmaf(wgx, r, s.v0);
+          s.v1 = fmaf(wgy, r, s.v1);
+        }
       }
     }
   }
@@ -1137,6 +1193,48 @@ struct PointGeo {
   bool ok;
 };
 
+// Patterns of up to 4 x kQuadSlots samples keep their templates in registers
+// like the 8-pixel one: slot j of lane `sub` is sample sub + 4 j, a slot past
+// the pattern has zero gradients.  Reading them again in every iteration put 91
+// loads per lane of a 7x7 patch on the address units, the path's bound; with
+// templates in registers and taps in LDS the track of 2000 7x7 points at 752x480
+// went from 191 to 153 us, of a 5x5-patch window of 9 frames from 771 to 594 us.
+// 13 slots (K <= 52) are what fits beside the loop's own state without spills
+// inside it.
+constexpr int kQuadSlots = 13;
+struct PointRegsQ {
+  float X0, Y0, Z0;
+  float i0_[kQuadSlots], gx_[kQuadSlots], gy_[kQuadSlots];
+  bool ok;
+  __device__ __forceinline__ float i0(int k) const { return i0_[k]; }
+  __device__ __forceinline__ float gx(int k) const { return gx_[k]; }
+  __device__ __forceinline__ float gy(int k) const { return gy_[k]; }
+};
+
+__device__ __forceinline__ void load_template(const TrackArgs& a, int64_t e, int sub, PointRegsQ& pr) {
+  const int K = a.pat.K;
+#pragma unroll
+  for (int j = 0; j < kQuadSlots; ++j) {
+    const int k = sub + kLanesPerPoint * j;
+    const int64_t o = e * K + (k < K ? k : 0);
+    pr.i0_[j] = gload(a.ref.I0 + o), pr.gx_[j] = gload(a.ref.gx + o), pr.gy_[j] = gload(a.ref.gy + o);
+  }
+#pragma unroll
+  for (int j = 0; j < kQuadSlots; ++j) {
+    const bool has = sub + kLanesPerPoint * j < K;
+    pr.gx_[j] = has ? pr.gx_[j] : 0.0f, pr.gy_[j] = has ? pr.gy_[j] : 0.0f;
+  }
+}
+
+// Their pixel offsets at a level of width W (a slot past the pattern: sample 0).
+__device__ __forceinline__ void quad_offsets(const Pattern& pat, int W, int sub, int (&off)[kQuadSlots]) {
+#pragma unroll
+  for (int j = 0; j < kQuadSlots; ++j) {
+    const int k = sub + kLanesPerPoint * j, kk = k < pat.K ? k : 0;
+    off[j] = (int)pat.dy[kk] * W + (int)pat.dx[kk];
+  }
+}
+
 // DPP quad permutation (quad_perm selector), a VALU operand modifier.
 template <int SEL>
 __device__ __forceinline__ float dpp_quad(float v) {
@@ -1150,9 +1248,19 @@ __device__ __forceinline__ float quad_sum(float v) {
   return v;
 }
 
-// sample_point8 for any pattern; the sums are those of the quad's point, the
-// same in its four lanes.  PIX: uint8 levels or the floating-point Gaussian
-// pyramid.
+// Sums over the quad's lanes, the same in each.
+template <bool COST_ONLY, bool FIXED>
+__device__ __forceinline__ void quad_sums(PointSums& s) {
+  if constexpr (COST_ONLY) {
+    s.E = quad_sum(s.E);
+  } else {
+    s.v0 = quad_sum(s.v0), s.v1 = quad_sum(s.v1);
+    if constexpr (!FIXED) s.m00 = quad_sum(s.m00), s.m01 = quad_sum(s.m01), s.m11 = quad_sum(s.m11);
+  }
+}
+
+// sample_point for patterns past the register slots, this lane's share of the
+// quad's point: taps and templates from global memory.
 template <bool COST_ONLY, bool FIXED, class PIX>
 __device__ __forceinline__ PointSums sample_point_generic(const TrackArgs& a, const Pattern& pat, const LevelGeom& g,
                                                           const PIX* __restrict__ img, const float* T,
@@ -1210,15 +1318,10 @@ __device__ __forceinline__ PointSums sample_point_generic(const TrackArgs& a, co
     }
   }
   if constexpr (COST_ONLY) {
-    s.E = quad_sum(s.E);
     s.E = ok ? s.E : 0.0f;
   } else {
-    s.v0 = quad_sum(s.v0), s.v1 = quad_sum(s.v1);
     s.v0 = ok ? s.v0 : 0.0f, s.v1 = ok ? s.v1 : 0.0f;
-    if constexpr (!FIXED) {
-      s.m00 = quad_sum(s.m00), s.m01 = quad_sum(s.m01), s.m11 = quad_sum(s.m11);
-      s.m00 = ok ? s.m00 : 0.0f, s.m01 = ok ? s.m01 : 0.0f, s.m11 = ok ? s.m11 : 0.0f;
-    }
+    if constexpr (!FIXED) s.m00 = ok ? s.m00 : 0.0f, s.m01 = ok ? s.m01 : 0.0f, s.m11 = ok ? s.m11 : 0.0f;
   }
   return s;
 }

@@ -227,7 +227,9 @@ struct PyrJob {
 // lanes per point, kGenericThreads-thread chunks of kGenericThreads / 4 points;
 // kCoopFloatPyr (with kCoopGeneric): the floating-point Gaussian pyramid;
 // kCoopPairs (8-pixel pattern): two threads per point, chunks of threads / 2 points.
-enum { kCoopFP32 = 0, kCoopMixed = 1, kCoopFixedH = 2, kCoopGeneric = 4, kCoopFloatPyr = 8, kCoopPairs = 16 };
+// kCoopSlots (with kCoopGeneric): a pattern whose templates fit the lanes' registers.
+enum { kCoopFP32 = 0, kCoopMixed = 1, kCoopFixedH = 2, kCoopGeneric = 4, kCoopFloatPyr = 8, kCoopPairs = 16, kCoopSlots = 32 };
+constexpr int kMaxSlotPattern = 52;  // samples of a pattern held in registers, four lanes per point
 constexpr int kGenericThreads = 256;
 constexpr int kLanesPerPoint = 4;
 
