@@ -636,8 +636,10 @@ int dpt_build_pyramid(dpt_ctx* c, int32_t slot, const uint8_t* img, int64_t pitc
   int ps = -1;
   const bool prof = c->prof && st == c->stream;  // the profile ring times the context's stream
   if (prof) HIP_TRY(c->prof_pyr.begin(c->stream, &ps));
-  HIP_TRY(launch_pyramid(src, sp, c->pyr[slot], c->pg, st));
-  if (c->pyrf[slot]) HIP_TRY(launch_pyramid_gauss(src, sp, c->pyrf[slot], c->pg, st));
+  if (c->pyrf[slot])
+    HIP_TRY(launch_pyramid_gauss(src, sp, c->pyr[slot], c->pyrf[slot], c->pg, st));
+  else
+    HIP_TRY(launch_pyramid(src, sp, c->pyr[slot], c->pg, st));
   if (prof) HIP_TRY(c->prof_pyr.end(c->stream, ps));
   c->have_pyr[slot] = true;
   if (slot == DPT_SLOT_REF) c->have_ref = false;
@@ -2222,7 +2224,7 @@ int dpt_batch_build_pyramids(dpt_batch* b, int32_t slot, const uint8_t* const* i
   HIP_TRY(launch_pyramid_batch(d_jobs, b->n, max_w, max_h, b->ctx[0]->prm.levels, st));
   for (int s = 0; s < b->n; ++s)
     if (b->ctx[s]->pyrf[slot])
-      HIP_TRY(launch_pyramid_gauss(h_jobs[s].src, h_jobs[s].pitch, b->ctx[s]->pyrf[slot], b->ctx[s]->pg, st));
+      HIP_TRY(launch_pyramid_gauss(h_jobs[s].src, h_jobs[s].pitch, nullptr, b->ctx[s]->pyrf[slot], b->ctx[s]->pg, st));
   // after the launches that read the table: the tables alternate between the two streams' builds
   HIP_TRY(hipEventRecord(b->ev_jobs[jt], st));
   if (prof) HIP_TRY(b->prof_pyr.end(b->stream, ps));

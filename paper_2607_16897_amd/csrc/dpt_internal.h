@@ -304,8 +304,10 @@ int cnn_propose(struct ::dpt_cnn* c, const uint8_t* const* d_lv, int B, hipStrea
 
 // Launchers (kernels.hip, coop.hip).  Each returns the hipError_t of the launch.
 hipError_t launch_pyramid(const uint8_t* src, int64_t pitch, uint8_t* dst, const PyrGeom& g, hipStream_t s);
-// Floating-point Gaussian pyramid of a uint8 frame (levels at the offsets of g, in floats).
-hipError_t launch_pyramid_gauss(const uint8_t* src, int64_t pitch, float* dst, const PyrGeom& g, hipStream_t s);
+// Floating-point Gaussian pyramid of a uint8 frame (levels at the offsets of g,
+// in floats) and, with u8, its uint8 pyramid.
+hipError_t launch_pyramid_gauss(const uint8_t* src, int64_t pitch, uint8_t* u8, float* dst, const PyrGeom& g,
+                                hipStream_t s);
 // Point selection; `scratch` holds select_scratch_ints(W, H) ints of device memory.
 int64_t select_scratch_ints(int32_t W, int32_t H);
 hipError_t launch_select(const uint8_t* img, int32_t W, int32_t H, int32_t margin, int32_t n, int32_t* idx,
