@@ -2288,11 +2288,14 @@ int dpt_batch_set_reference_from_depth_all(dpt_batch* b, const int32_t* n_points
   HIP_TRY(b->pre_args.acquire(&hp, &wp));
   int G_max = 0, max_n = 0, max_samples = 0, max_levels = 0;
   bool any_empty = false;
+  int64_t pixels = 0;
+  for (const dpt_ctx* c : b->ctx) pixels += (int64_t)c->cam.width * c->cam.height;
+  const int chunk = select_chunk(pixels);
   for (int s = 0; s < b->n; ++s) {
     dpt_ctx* c = b->ctx[s];
     const int n = n_points[s];
     hs[s] = make_sel_job(c->pyr[DPT_SLOT_REF], c->cam.width, c->cam.height, margin, n, c->sel_idx, c->sel_count,
-                         c->sel_scratch);
+                         c->sel_scratch, chunk);
     BackprojectArgs& bp = hb[s];
     bp.idx = c->sel_idx;
     bp.count = c->sel_count;
@@ -2316,7 +2319,7 @@ int dpt_batch_set_reference_from_depth_all(dpt_batch* b, const int32_t* n_points
   HIP_TRY(b->sel_jobs.upload(ws, b->n, rs, &ds));
   HIP_TRY(b->bp_args.upload(wb, b->n, rs, &db));
   HIP_TRY(b->pre_args.upload(wp, b->n, rs, &dp));
-  HIP_TRY(launch_select_batch(ds, b->n, G_max, any_empty, rs));
+  HIP_TRY(launch_select_batch(ds, b->n, G_max, chunk, any_empty, rs));
   HIP_TRY(launch_backproject_batch(db, b->n, max_n, rs));
   HIP_TRY(launch_precompute_batch(dp, b->n, max_samples, max_levels, rs));
   if (b->ctx[0]->prm.flags & DPT_FLAG_FIXED_H) HIP_TRY(launch_fixed_h_batch(dp, b->n, max_n, max_levels, rs));

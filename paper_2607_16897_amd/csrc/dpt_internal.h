@@ -139,7 +139,7 @@ struct SelGeom {
 };
 
 // One image's selection: geometry, its scratch (select_scratch_ints ints), the
-// output indices and count, and its number of 4096-candidate chunks G.
+// output indices and count, and its number of chunks G.
 struct SelJob {
   SelGeom g;
   int32_t* sc;
@@ -312,12 +312,14 @@ hipError_t launch_pyramid_gauss(const uint8_t* src, int64_t pitch, uint8_t* u8, 
 int64_t select_scratch_ints(int32_t W, int32_t H);
 hipError_t launch_select(const uint8_t* img, int32_t W, int32_t H, int32_t margin, int32_t n, int32_t* idx,
                          int32_t* count, int32_t* scratch, hipStream_t s);
+// Candidates per chunk of a launch over images of `pixels` pixels together (every job of it alike).
+int select_chunk(int64_t pixels);
 SelJob make_sel_job(const uint8_t* img, int32_t W, int32_t H, int32_t margin, int32_t n, int32_t* idx,
-                    int32_t* count, int32_t* scratch);
+                    int32_t* count, int32_t* scratch, int chunk);
 // Selections of n_img images in one launch sequence; d_jobs in device memory,
 // G_max = the largest chunk count among them, any_empty: one has none.  The
 // scratch of every image must start zeroed (a fresh one: hipMemset).
-hipError_t launch_select_batch(const SelJob* d_jobs, int n_img, int G_max, bool any_empty, hipStream_t s);
+hipError_t launch_select_batch(const SelJob* d_jobs, int n_img, int G_max, int chunk, bool any_empty, hipStream_t s);
 // The selection of one device image with its scratch in the library's static
 // device array (nothing allocated): images of at most kNoAllocSelectPixels.
 constexpr int64_t kNoAllocSelectPixels = 4096 * 4096;
