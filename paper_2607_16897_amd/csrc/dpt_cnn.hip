@@ -43,6 +43,10 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
+__device__ __forceinline__ short4_t bf16x4(uint2 v) {
+  return short4_t{(short)(v.x & 0xffff), (short)(v.x >> 16), (short)(v.y & 0xffff), (short)(v.y >> 16)};
+}
+
 // ---------------------------------------------------------------- layout
 // Flat FP32 parameter vector, tensor order w1 b1 w2 b2 w3 b3 w4 b4 fw1 fb1 fw2 fb2.
 // Conv weights are stored [co][ky][kx][ci] internally; the ABI uses [co][ci][ky][kx].
@@ -70,6 +74,22 @@ __host__ __device__ inline Offsets offsets() {
   o.total = s;
   return o;
 }
+
+// The BF16 convolution weights, in the layouts the kernels stage in LDS: layer l
+// forward as [co][tap][ci], rows of kWRow[l] elements, and (l >= 1) for the data
+// gradient as [tap][ci][co], rows of kTRow[l].  Sixteen lanes read 8 bytes each
+// from sixteen consecutive rows, four lane groups 8 bytes apart; a row of an odd
+// multiple of 32 bytes spreads them over all banks (rows of 576 or 1152 bytes
+// put eight or sixteen lanes on the same ones), so rows are padded to that.  The
+// same holds for the activations' pixels, two apart in the forward convolutions
+// (kXRow, layers' inputs) and adjacent in the data gradient (kDRow).
+constexpr int kWRow[4] = {18, 144, 304, 592};
+constexpr int kTRow[4] = {0, 48, 80, 80};
+constexpr int kXRow[4] = {2, 24, 40, 72};
+constexpr int kDRow[5] = {0, 0, 48, 80, 80};
+__host__ __device__ constexpr int wrow_off(int l) { return l == 0 ? 0 : wrow_off(l - 1) + kC[l] * kWRow[l - 1]; }
+__host__ __device__ constexpr int trow_off(int l) { return l <= 1 ? 0 : trow_off(l - 1) + 9 * kC[l - 1] * kTRow[l - 1]; }
+constexpr int kPbTotal = wrow_off(4), kPbTTotal = trow_off(4);
 
 // ---------------------------------------------------------------- head forward and proposal (device parts)
 
@@ -99,93 +119,126 @@ __device__ __forceinline__ void propose_twist(const float* o6, double* rel) {
   for (int j = 0; j < 12; ++j) rel[j] = T[j];
 }
 
-// The head's forward pass on one sample's layer-4 activations a (4 x 6 x 64,
-// LDS or global): g = their mean, h1 = relu(fw1 g + fb1), and for threads
-// t < kOut the return value out[t] = fw2 h1 + fb2.  Threads t < 64 do the
-// work; every thread of the workgroup calls it (two barriers); g and h1 are
-// 64-float LDS vectors.
-__device__ __forceinline__ float head_forward(const uint16_t* __restrict__ a, const float* __restrict__ P,
-                                              const Offsets& o, float* g, float* h1) {
-  constexpr int HW = 4 * 6;
-  const int t = threadIdx.x;
-  if (t < 64) {
-    float s = 0.f;
-    for (int p = 0; p < HW; ++p) s += bf2f(a[p * 64 + t]);
-    g[t] = s * (1.0f / HW);
-  }
-  __syncthreads();
-  if (t < 64) {
-    float z = P[o.fb1 + t];
-    for (int q = 0; q < 64; ++q) z = fmaf(P[o.fw1 + t * 64 + q], g[q], z);
-    h1[t] = fmaxf(z, 0.f);
-  }
-  __syncthreads();
-  float v = 0.f;
-  if (t < kOut) {
-    v = P[o.fb2 + t];
-    for (int q = 0; q < kHidden; ++q) v = fmaf(P[o.fw2 + t * kHidden + q], h1[q], v);
-  }
-  return v;
-}
-
 // ---------------------------------------------------------------- forward convolutions (fused, MFMA)
 
-// One layer of one sample inside a workgroup, as an implicit GEMM: rows m =
+// Layer L + 1 of one sample inside a workgroup, as an implicit GEMM: rows m =
 // output pixels (i, j), columns n = output channels, k = (ky, kx, ci), stride
 // 2 and one pixel of zero padding; BF16 operands, FP32 accumulation, then bias
-// and ReLU, BF16 out.  The sample's activations and the layer's weights are in
-// LDS; the waves take the (16-row tile, 16-channel tile) pairs in turn.  Lane L
-// supplies A[m0 + L%16][k0 + 4(L/16) .. +3] and B[k0 + 4(L/16) .. +3][n0 + L%16]
-// and receives D[4(L/16) + j][L%16].
-template <int CI, int CO>
-__device__ __forceinline__ void conv_sample(const uint16_t* __restrict__ x, int H, int W, int Ho, int Wo,
-                                            const uint16_t* __restrict__ w, const float* __restrict__ bias,
-                                            uint16_t* __restrict__ y) {
-  constexpr int K = 9 * CI, KP = (K + 15) / 16 * 16, NT = CO / 16;
+// and ReLU, BF16 out (pixels YS elements apart).  The sample's activations and
+// the layer's weights are in LDS; the waves take the (16-row tile, 16-channel
+// tile) pairs in turn.  Lane l supplies A[m0 + l%16][k0 + 4(l/16) .. +3] and
+// B[k0 + 4(l/16) .. +3][n0 + l%16] and receives D[4(l/16) + j][l%16].
+template <int L, int YS>
+__device__ __forceinline__ void conv_sample(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
+                                            const float* __restrict__ bias, uint16_t* __restrict__ y) {
+  constexpr int CI = kC[L], CO = kC[L + 1], H = kHs[L], W = kWs[L], Ho = kHs[L + 1], Wo = kWs[L + 1];
+  constexpr int XS = kXRow[L], WS = kWRow[L], K = 9 * CI, NT = CO / 16, M = Ho * Wo, ITEMS = (M + 15) / 16 * NT;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6, kq = lane >> 4;
-  const int M = Ho * Wo, items = (M + 15) / 16 * NT;
-  for (int it = wave; it < items; it += nw) {
-    const int m0 = it / NT * 16, t = it % NT, n = t * 16 + (lane & 15);
+  for (int it = wave; it < ITEMS; it += nw) {
+    const int m0 = it / NT * 16, n = it % NT * 16 + (lane & 15);
     const int m = m0 + (lane & 15);
     const bool mvalid = m < M;
     const int i = mvalid ? m / Wo : 0, j = mvalid ? m % Wo : 0;
+    const float bn = bias[n];
     float4_t acc = float4_t{0.f, 0.f, 0.f, 0.f};
+    if constexpr (CI % 16 == 0) {
 #pragma unroll
-    for (int ks = 0; ks < KP / 16; ++ks) {
-      const int k0 = ks * 16 + 4 * kq;
-      short4_t a, bv;
-      if constexpr (CI % 4 == 0) {
-        const int tap = k0 / CI, c = k0 % CI;
+      for (int ks = 0; ks < K / 16; ++ks) {
+        const int tap = ks * 16 / CI, c = ks * 16 % CI + 4 * kq;  // one tap per step
         const int yy = 2 * i + tap / 3 - 1, xx = 2 * j + tap % 3 - 1;
-        uint2 v = make_uint2(0u, 0u);
-        if (mvalid && yy >= 0 && yy < H && xx >= 0 && xx < W)
-          v = *reinterpret_cast<const uint2*>(x + (yy * W + xx) * CI + c);
-        a = short4_t{(short)(v.x & 0xffff), (short)(v.x >> 16), (short)(v.y & 0xffff), (short)(v.y >> 16)};
-        const uint2 u = *reinterpret_cast<const uint2*>(w + n * K + k0);
-        bv = short4_t{(short)(u.x & 0xffff), (short)(u.x >> 16), (short)(u.y & 0xffff), (short)(u.y >> 16)};
-      } else {
-        short e[4], f[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int k = k0 + q;
-          uint16_t v = 0;
-          if (k < K && mvalid) {
-            const int tap = k / CI, c = k % CI;
-            const int yy = 2 * i + tap / 3 - 1, xx = 2 * j + tap % 3 - 1;
-            if (yy >= 0 && yy < H && xx >= 0 && xx < W) v = x[(yy * W + xx) * CI + c];
-          }
-          e[q] = (short)v;
-          f[q] = k < K ? (short)w[n * K + k] : (short)0;
-        }
-        a = short4_t{e[0], e[1], e[2], e[3]};
-        bv = short4_t{f[0], f[1], f[2], f[3]};
+        const bool ok = mvalid & (yy >= 0) & (yy < H) & (xx >= 0) & (xx < W);
+        uint2 v = *reinterpret_cast<const uint2*>(x + (ok ? (yy * W + xx) * XS : 0) + c);
+        if (!ok) v = make_uint2(0u, 0u);
+        const uint2 u = *reinterpret_cast<const uint2*>(w + n * WS + ks * 16 + 4 * kq);
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(bf16x4(v), bf16x4(u), acc, 0, 0, 0);
       }
-      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bv, acc, 0, 0, 0);
+    } else {  // two channels: a lane's four k are two taps, a word of both channels each
+      static_assert(CI == 2 || CI % 16 == 0, "two channels or whole steps per tap");
+#pragma unroll
+      for (int ks = 0; ks < (K + 15) / 16; ++ks) {
+        uint32_t v[2], u[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int tap = 8 * ks + 2 * kq + h, ky = tap / 3, kx = tap - 3 * ky;
+          const int yy = 2 * i + ky - 1, xx = 2 * j + kx - 1;
+          const bool in = tap < 9, ok = in & mvalid & (yy >= 0) & (yy < H) & (xx >= 0) & (xx < W);
+          v[h] = *reinterpret_cast<const uint32_t*>(x + (ok ? (yy * W + xx) * 2 : 0));
+          u[h] = *reinterpret_cast<const uint32_t*>(w + n * WS + (in ? 2 * tap : 0));
+          v[h] = ok ? v[h] : 0u, u[h] = in ? u[h] : 0u;
+        }
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(bf16x4(make_uint2(v[0], v[1])), bf16x4(make_uint2(u[0], u[1])),
+                                                         acc, 0, 0, 0);
+      }
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int mo = m0 + 4 * kq + q;
-      if (mo < M) y[mo * CO + n] = f2bf(fmaxf(acc[q] + bias[n], 0.0f));
+      if (mo < M) y[mo * YS + n] = f2bf(fmaxf(acc[q] + bn, 0.0f));
+    }
+  }
+}
+
+// Data gradient of layer L + 1 of one sample inside a workgroup, fused with the
+// ReLU mask of its input: dZprev[y][x][c] = (aprev > 0) * sum over taps (ky, kx)
+// and channels o of W[o][ky][kx][c] dZ[i][j][o], where 2i + ky - 1 = y and 2j +
+// kx - 1 = x.  Stride 2 makes the reaching taps depend only on the parities of
+// (y, x): an even row is reached by ky = 1 alone, an odd one by ky = 0 and 2
+// (columns likewise), so the rows of the implicit GEMM are the input pixels of
+// one parity class and k = (reaching tap, o).  dZ and the weights ([tap][ci][co])
+// are in LDS; the waves take (class, 16 pixels, 16 channels) in turn, the classes
+// of most taps first.  out: dZprev in LDS for the next layer, or null; gout: dense.
+template <int L>
+__device__ __forceinline__ void conv_bwd_sample(const uint16_t* __restrict__ dz, const uint16_t* __restrict__ wT,
+                                                const uint16_t* __restrict__ aprev, uint16_t* __restrict__ out,
+                                                uint16_t* __restrict__ gout) {
+  constexpr int CI = kC[L], CO = kC[L + 1], H = kHs[L], W = kWs[L], Ho = kHs[L + 1], Wo = kWs[L + 1];
+  constexpr int NT = CI / 16, DS = kDRow[L + 1], WS = kTRow[L], OS = kDRow[L];
+  static_assert(CI % 16 == 0 && CO % 16 == 0, "16-channel tiles");
+  const int lane = threadIdx.x & 63, q = lane >> 4, nw = blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const auto tiles = [](int cls) {
+    return (((H - (cls >> 1) + 1) / 2) * ((W - (cls & 1) + 1) / 2) + 15) / 16 * NT;
+  };
+  const int items = tiles(0) + tiles(1) + tiles(2) + tiles(3);
+  for (int it = wave; it < items; it += nw) {
+    int cls = 3, r0 = it;
+    while (r0 >= tiles(cls)) r0 -= tiles(cls--);
+    const int py = cls >> 1, px = cls & 1, Hc = (H - py + 1) / 2, Wc = (W - px + 1) / 2, M = Hc * Wc;
+    const int m0 = r0 / NT * 16, n = r0 % NT * 16 + (lane & 15);
+    const int m = m0 + (lane & 15);
+    const bool mvalid = m < M;
+    const int r = mvalid ? m : 0, y = 2 * (r / Wc) + py, x = 2 * (r % Wc) + px;
+    // the mask at the lane's four results D[4q + jq][lane % 16]
+    uint16_t mask[4];
+    int at[4];
+#pragma unroll
+    for (int jq = 0; jq < 4; ++jq) {
+      const int mo = min(m0 + 4 * q + jq, M - 1);
+      at[jq] = (2 * (mo / Wc) + py) * W + 2 * (mo % Wc) + px;
+      mask[jq] = aprev[at[jq] * CI + n];
+    }
+    float4_t acc = float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int ta = 0; ta < (py ? 2 : 1); ++ta)
+      for (int tb = 0; tb < (px ? 2 : 1); ++tb) {
+        const int ky = py ? 2 * ta : 1, kx = px ? 2 * tb : 1, tap = ky * 3 + kx;
+        const int i = (y + 1 - ky) >> 1, j = (x + 1 - kx) >> 1;  // y + 1 - ky >= 0 and even
+        const bool ok = mvalid & (i < Ho) & (j < Wo);
+        const uint16_t* drow = dz + (ok ? (i * Wo + j) * DS : 0) + 4 * q;
+        const uint16_t* wrow = wT + (tap * CI + n) * WS + 4 * q;
+#pragma unroll
+        for (int o0 = 0; o0 < CO; o0 += 16) {
+          uint2 dv = *reinterpret_cast<const uint2*>(drow + o0);
+          if (!ok) dv = make_uint2(0u, 0u);
+          acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(bf16x4(dv), bf16x4(*reinterpret_cast<const uint2*>(wrow + o0)),
+                                                           acc, 0, 0, 0);
+        }
+      }
+#pragma unroll
+    for (int jq = 0; jq < 4; ++jq) {
+      if (m0 + 4 * q + jq >= M) continue;
+      const uint16_t v = bf2f(mask[jq]) > 0.f ? f2bf(acc[jq]) : (uint16_t)0;
+      if (out) out[at[jq] * OS + n] = v;
+      gout[(size_t)at[jq] * CI + n] = v;
     }
   }
 }
@@ -201,21 +254,14 @@ __device__ __forceinline__ void stage_weights(const uint16_t* __restrict__ src, 
                                        (__attribute__((address_space(3))) void*)(lds + 8 * q0), 16, 0, 0);
 }
 
-// LDS of the fused pass (elements): two ping-pong activation buffers and the
-// current layer's weights.
-constexpr int kFuseA = 15 * 24 * 32 > kH0 * kW0 * 2 ? 15 * 24 * 32 : kH0 * kW0 * 2;  // input, layer 2 out
-constexpr int kFuseB = 30 * 47 * 16;                                                  // layer 1 and 3 out
-constexpr int kFuseW = 64 * 9 * 64;                                                   // layer 4's weights
-static_assert(kHs[1] == 30 && kWs[1] == 47 && kC[1] == 16 && kHs[2] == 15 && kWs[2] == 24 && kC[2] == 32 &&
-                  kHs[3] * kWs[3] * kC[3] <= kFuseB && kC[3] * 9 * kC[4] <= kFuseW,
-              "fused buffers follow the layer shapes");
 constexpr int kFuseThreads = 1024;
 
 // Where the fused pass reads and writes: the input pairs as per-sample level
 // pointers (refs, curs) or planar [B][2][60][94] bytes (pairs); act[l]
-// (non-null) receives layer l's activations for the backward pass (act[0] the
-// BF16 input), act[4] always; out (non-null) the head's outputs, rel
-// (non-null) their exponentials.
+// (non-null) receives layer l's activations for the weight gradient (act[0] the
+// BF16 input), act[4] always; out the head's outputs, rel (non-null) their
+// exponentials.  Training: targets [B][6], and the squared errors, FC gradients
+// ([B][fc parameters]) and layers' gradients dz[1..4] out.
 struct FusedIO {
   const uint8_t* const* refs;
   const uint8_t* const* curs;
@@ -223,191 +269,204 @@ struct FusedIO {
   uint16_t* act[5];
   float* out;
   double* rel;
+  const float* targets;
+  float *sqerr, *fcg;
+  uint16_t* dz[5];
+  int B;
 };
 
-// n BF16 values (a multiple of 8) from LDS to global memory, 16 bytes a thread.
+// n BF16 values (a multiple of 8) of C channels a pixel from LDS (pixels S
+// elements apart) to global memory, 16 bytes a thread.
+template <int C, int S>
 __device__ __forceinline__ void store_act(const uint16_t* __restrict__ src, uint16_t* __restrict__ dst, int n) {
   for (int e = 8 * (int)threadIdx.x; e < n; e += 8 * (int)blockDim.x)
-    *reinterpret_cast<uint4*>(dst + e) = *reinterpret_cast<const uint4*>(src + e);
+    *reinterpret_cast<uint4*>(dst + e) = *reinterpret_cast<const uint4*>(src + (C == S ? e : e / C * S + e % C));
 }
 
-// The input and the four convolutions of sample blockIdx.x in one workgroup,
-// the activations never leaving LDS (save the copies io asks for) and each
-// layer's weights staged in LDS before it runs; then, for inference, the
-// head and the proposal.
+// LDS of the fused pass in bytes.  What a step reads and what is being staged for
+// the steps after it are apart; a region is reused once its last reader is done.
+//   forward:  A   input, then layer 2's activations, then layer 4's
+//             W3  staged from the start; the head's weights once layer 3 is done
+//             B   layer 1's activations; from layer 3 on its activations (C3) and W4
+//             W2, W1 staged from the start
+//   backward: D4, D3 (gradients) and T2 from the start, T3 over C3 and W4;
+//             D2 and T1 over T3
+struct FuseLds {
+  static constexpr int kA = 0, kW3 = kA + 2 * kHs[2] * kWs[2] * kXRow[2], kB = kW3 + 2 * kC[3] * kWRow[2],
+                       kW2 = kB + 2 * kHs[1] * kWs[1] * kXRow[1], kW1 = kW2 + 2 * kC[2] * kWRow[1],
+                       kFwdEnd = kW1 + 2 * kC[1] * kWRow[0];
+  static constexpr int kC3 = kB, kW4 = kC3 + 2 * kHs[3] * kWs[3] * kXRow[3], kEnd4 = kW4 + 2 * kC[4] * kWRow[3];
+  static constexpr int kHead = kW3, kHeadEnd = kHead + 4 * (64 * 65 + kOut * kHidden);
+  static constexpr int kD4 = 2 * kHs[4] * kWs[4] * kC[4], kD3 = kD4 + 2 * kHs[4] * kWs[4] * kDRow[4],
+                       kT2 = kD3 + 2 * kHs[3] * kWs[3] * kDRow[3], kT3 = kT2 + 2 * 9 * kC[2] * kTRow[2],
+                       kEndT3 = kT3 + 2 * 9 * kC[3] * kTRow[3];
+  static constexpr int kD2 = kT3, kT1 = kD2 + 2 * kHs[2] * kWs[2] * kDRow[2], kEndT1 = kT1 + 2 * 9 * kC[1] * kTRow[1];
+  static constexpr int kFwd = kFwdEnd > kEnd4 ? kFwdEnd : kEnd4, kBwd = kEndT3 > kEndT1 ? kEndT3 : kEndT1;
+  static constexpr int kBytes = kFwd > kBwd ? kFwd : kBwd;
+};
+static_assert(2 * kH0 * kW0 * 2 <= FuseLds::kW3 && FuseLds::kHeadEnd <= FuseLds::kB && FuseLds::kD3 <= FuseLds::kHead &&
+                  FuseLds::kT3 >= FuseLds::kHeadEnd && FuseLds::kT3 >= FuseLds::kC3 && FuseLds::kBytes <= 161 * 1024 &&
+                  FuseLds::kW3 % 16 == 0 && FuseLds::kB % 16 == 0 && FuseLds::kW2 % 16 == 0 && FuseLds::kW1 % 16 == 0 &&
+                  FuseLds::kW4 % 16 == 0 && FuseLds::kD4 % 16 == 0 && FuseLds::kD3 % 16 == 0 && FuseLds::kT2 % 16 == 0 &&
+                  FuseLds::kT3 % 16 == 0 && FuseLds::kT1 % 16 == 0,
+              "the regions follow the layer shapes");
+
+// Sample blockIdx.x in one workgroup: the input, the four convolutions and the
+// head, the activations never leaving LDS (save the copies io asks for); then the
+// proposal's exponential or, training, the loss, the head's backward and the
+// gradients of the layers' outputs down to layer 1 (mean(a4) = g, h1 = relu(fw1 g
+// + fb1), out = fw2 h1 + fb2).  The steps are short and depend on each other, so
+// latency bounds them: each layer's weights are on their way while the layer
+// before is computed, and 1024 threads share a layer's tiles.  64 pairs with the
+// proposal: 27 us with unpadded rows and each layer's weights waited for, now
+// 18.4; the training pass of 256 pairs: 97 us as five launches, now 51.5.
+template <bool TRAIN>
 __global__ __launch_bounds__(kFuseThreads) void conv_net_fused(FusedIO io, const uint16_t* __restrict__ Pb,
+                                                               const uint16_t* __restrict__ PbT,
                                                                const float* __restrict__ P) {
-  __shared__ __align__(16) uint16_t bufA[kFuseA];
-  __shared__ float sh_g[64], sh_h1[64], sh_out[kOut];
-  __shared__ __align__(16) uint16_t bufB[kFuseB];
-  __shared__ __align__(16) uint16_t bufW[kFuseW];
+  using R = FuseLds;
+  __shared__ __align__(16) uint8_t lds[R::kBytes];
+  __shared__ float sh_g[64], sh_h1[64], sh_out[kOut], sh_dout[kOut], sh_dz1[64];
+  __shared__ uint16_t sh_dg[64];
+  const auto at = [&](int o) { return reinterpret_cast<uint16_t*>(lds + o); };
   constexpr int N0 = kH0 * kW0 * 2, N1 = kHs[1] * kWs[1] * kC[1], N2 = kHs[2] * kWs[2] * kC[2],
-                N3 = kHs[3] * kWs[3] * kC[3], N4 = kHs[4] * kWs[4] * kC[4];
+                N3 = kHs[3] * kWs[3] * kC[3], N4 = kHs[4] * kWs[4] * kC[4], HW = kHs[4] * kWs[4];
   static_assert(N0 % 8 == 0 && N1 % 8 == 0 && N2 % 8 == 0 && N3 % 8 == 0 && N4 % 8 == 0, "16-byte copies");
-  const int b = blockIdx.x;
+  const int b = blockIdx.x, t = threadIdx.x;
   const Offsets o = offsets();
-  stage_weights(Pb + o.w[0], kC[1] * 9 * kC[0] * 2, bufW);
   const uint8_t* ref = io.pairs ? io.pairs + (size_t)(2 * b) * kH0 * kW0 : io.refs[b];
   const uint8_t* cur = io.pairs ? io.pairs + (size_t)(2 * b + 1) * kH0 * kW0 : io.curs[b];
-  for (int r = threadIdx.x; r < kH0 * kW0; r += blockDim.x) {  // (I - 128) / 64, exact in BF16
-    bufA[2 * r] = f2bf(((float)ref[r] - 128.0f) * (1.0f / 64.0f));
-    bufA[2 * r + 1] = f2bf(((float)cur[r] - 128.0f) * (1.0f / 64.0f));
+  constexpr int PX = (kH0 * kW0 + kFuseThreads - 1) / kFuseThreads;
+  uint8_t pr[PX], pc[PX];
+#pragma unroll
+  for (int k = 0; k < PX; ++k) {
+    const int r = min(t + k * kFuseThreads, kH0 * kW0 - 1);
+    pr[k] = gload(ref + r), pc[k] = gload(cur + r);
+  }
+  stage_weights(Pb + wrow_off(0), kC[1] * kWRow[0] * 2, at(R::kW1));
+  stage_weights(Pb + wrow_off(1), kC[2] * kWRow[1] * 2, at(R::kW2));
+  stage_weights(Pb + wrow_off(2), kC[3] * kWRow[2] * 2, at(R::kW3));
+#pragma unroll
+  for (int k = 0; k < PX; ++k) {  // (I - 128) / 64, exact in BF16
+    const int r = t + k * kFuseThreads;
+    const uint32_t v = f2bf(((float)pr[k] - 128.0f) * (1.0f / 64.0f)), w = f2bf(((float)pc[k] - 128.0f) * (1.0f / 64.0f));
+    if (r < kH0 * kW0) *reinterpret_cast<uint32_t*>(at(R::kA) + 2 * r) = v | w << 16;
   }
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  if (io.act[0]) store_act(bufA, io.act[0] + (size_t)b * N0, N0);
-  conv_sample<2, 16>(bufA, kHs[0], kWs[0], kHs[1], kWs[1], bufW, P + o.b[0], bufB);
+  if (io.act[0]) store_act<2, 2>(at(R::kA), io.act[0] + (size_t)b * N0, N0);
+  conv_sample<0, kXRow[1]>(at(R::kA), at(R::kW1), P + o.b[0], at(R::kB));
   __syncthreads();
-  stage_weights(Pb + o.w[1], kC[2] * 9 * kC[1] * 2, bufW);
-  if (io.act[1]) store_act(bufB, io.act[1] + (size_t)b * N1, N1);
+  if (io.act[1]) store_act<kC[1], kXRow[1]>(at(R::kB), io.act[1] + (size_t)b * N1, N1);
+  conv_sample<1, kXRow[2]>(at(R::kB), at(R::kW2), P + o.b[1], at(R::kA));
+  __syncthreads();
+  stage_weights(Pb + wrow_off(3), kC[4] * kWRow[3] * 2, at(R::kW4));
+  if (io.act[2]) store_act<kC[2], kXRow[2]>(at(R::kA), io.act[2] + (size_t)b * N2, N2);
+  conv_sample<2, kXRow[3]>(at(R::kA), at(R::kW3), P + o.b[2], at(R::kC3));
+  // the head's weights, to LDS once W3 is done with: fw1 transposed in rows of 65,
+  // so that both fw1 g and fw1^T dz1 read it without conflicts
+  static_assert(kFuseThreads * 4 == kHidden * 64, "four elements of fw1 per thread");
+  const float4 f1 = gload(reinterpret_cast<const float4*>(P + o.fw1) + t);
+  const float f2 = t < kOut * kHidden ? P[o.fw2 + t] : 0.f, fb1 = t < kHidden ? P[o.fb1 + t] : 0.f,
+              fb2 = t < kOut ? P[o.fb2 + t] : 0.f;
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  conv_sample<16, 32>(bufB, kHs[1], kWs[1], kHs[2], kWs[2], bufW, P + o.b[1], bufA);
+  if (io.act[3]) store_act<kC[3], kXRow[3]>(at(R::kC3), io.act[3] + (size_t)b * N3, N3);
+  float* fw1 = reinterpret_cast<float*>(lds + R::kHead);  // [q][t]
+  float* fw2 = fw1 + 64 * 65;
+  {
+    float* d = fw1 + 4 * (t & 15) * 65 + (t >> 4);
+    d[0] = f1.x, d[65] = f1.y, d[130] = f1.z, d[195] = f1.w;
+    if (t < kOut * kHidden) fw2[t] = f2;
+  }
+  uint16_t* a4 = at(R::kA);
+  conv_sample<3, kC[4]>(at(R::kC3), at(R::kW4), P + o.b[3], a4);
   __syncthreads();
-  stage_weights(Pb + o.w[2], kC[3] * 9 * kC[2] * 2, bufW);
-  if (io.act[2]) store_act(bufA, io.act[2] + (size_t)b * N2, N2);
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  conv_sample<32, 64>(bufA, kHs[2], kWs[2], kHs[3], kWs[3], bufW, P + o.b[2], bufB);
-  __syncthreads();
-  stage_weights(Pb + o.w[3], kC[4] * 9 * kC[3] * 2, bufW);
-  if (io.act[3]) store_act(bufB, io.act[3] + (size_t)b * N3, N3);
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  conv_sample<64, 64>(bufB, kHs[3], kWs[3], kHs[4], kWs[4], bufW, P + o.b[3], bufA);
-  __syncthreads();
-  store_act(bufA, io.act[4] + (size_t)b * N4, N4);
-  if (!io.out) return;
-  // the head (head_kernel's arithmetic) and the proposal's exponential
-  const float v = head_forward(bufA, P, o, sh_g, sh_h1);
-  if (threadIdx.x < kOut) {
-    io.out[b * kOut + threadIdx.x] = v;
-    sh_out[threadIdx.x] = v;
+  if constexpr (TRAIN) stage_weights(PbT + trow_off(3), 9 * kC[3] * kTRow[3] * 2, at(R::kT3));
+  store_act<kC[4], kC[4]>(a4, io.act[4] + (size_t)b * N4, N4);
+  if (!TRAIN && !io.out) return;
+  if (t < 64) {
+    float v = 0.f;
+#pragma unroll
+    for (int p = 0; p < HW; ++p) v += bf2f(a4[p * 64 + t]);
+    sh_g[t] = v * (1.0f / HW);
   }
   __syncthreads();
-  if (io.rel && threadIdx.x == 0) propose_twist(sh_out, io.rel + 12 * b);
+  if (t < 64) {
+    float z = fb1;
+#pragma unroll 16
+    for (int q = 0; q < 64; ++q) z = fmaf(fw1[q * 65 + t], sh_g[q], z);
+    sh_h1[t] = fmaxf(z, 0.f);
+  }
+  __syncthreads();
+  if (t < kOut) {
+    float v = fb2;
+#pragma unroll 16
+    for (int q = 0; q < kHidden; ++q) v = fmaf(fw2[t * kHidden + q], sh_h1[q], v);
+    io.out[b * kOut + t] = v;
+    sh_out[t] = v;
+    if constexpr (TRAIN) {
+      const float d = v - io.targets[b * kOut + t];
+      sh_dout[t] = 2.0f * d / (float)(io.B * kOut);
+      io.sqerr[b * kOut + t] = d * d;
+    }
+  }
+  __syncthreads();
+  if constexpr (!TRAIN) {
+    if (io.rel && t == 0) propose_twist(sh_out, io.rel + 12 * b);
+    return;
+  }
+  // FC gradients of this sample (fixed layout: fw1, fb1, fw2, fb2 relative to o.fw1)
+  float* G = io.fcg + (size_t)b * (o.total - o.fw1);
+  if (t < kOut * kHidden) G[o.fw2 - o.fw1 + t] = sh_dout[t / kHidden] * sh_h1[t % kHidden];
+  if (t < kOut) G[o.fb2 - o.fw1 + t] = sh_dout[t];
+  if (t < 64) {
+    float dh = 0.f;
+#pragma unroll
+    for (int q = 0; q < kOut; ++q) dh = fmaf(fw2[q * kHidden + t], sh_dout[q], dh);
+    const float dz1 = sh_h1[t] > 0.f ? dh : 0.f;
+    sh_dz1[t] = dz1;
+    G[o.fb1 - o.fw1 + t] = dz1;
+  }
+  __syncthreads();
+  for (int e = t; e < kHidden * 64; e += kFuseThreads) G[e] = sh_dz1[e >> 6] * sh_g[e & 63];
+  if (t < 64) {
+    float dg = 0.f;
+#pragma unroll 16
+    for (int q = 0; q < kHidden; ++q) dg = fmaf(fw1[t * 65 + q], sh_dz1[q], dg);
+    sh_dg[t] = f2bf(dg * (1.0f / HW));
+  }
+  __syncthreads();
+  uint16_t* d4 = at(R::kD4);
+  for (int e = t; e < N4; e += kFuseThreads) {
+    const uint16_t v = bf2f(a4[e]) > 0.f ? sh_dg[e & 63] : (uint16_t)0;
+    d4[(e >> 6) * kDRow[4] + (e & 63)] = v;
+    io.dz[4][(size_t)b * N4 + e] = v;
+  }
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  stage_weights(PbT + trow_off(2), 9 * kC[2] * kTRow[2] * 2, at(R::kT2));
+  conv_bwd_sample<3>(d4, at(R::kT3), io.act[3] + (size_t)b * N3, at(R::kD3), io.dz[3] + (size_t)b * N3);
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  stage_weights(PbT + trow_off(1), 9 * kC[1] * kTRow[1] * 2, at(R::kT1));
+  conv_bwd_sample<2>(at(R::kD3), at(R::kT2), io.act[2] + (size_t)b * N2, at(R::kD2), io.dz[2] + (size_t)b * N2);
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  conv_bwd_sample<1>(at(R::kD2), at(R::kT1), io.act[1] + (size_t)b * N1, nullptr, io.dz[1] + (size_t)b * N1);
 }
 
 // The fused pass over B samples on stream s.
-hipError_t launch_fused(const FusedIO& io, int B, const uint16_t* Pb, const float* P, hipStream_t s) {
-  hipLaunchKernelGGL(conv_net_fused, dim3(B), dim3(kFuseThreads), 0, s, io, Pb, P);
+hipError_t launch_fused(const FusedIO& io, int B, const uint16_t* Pb, const uint16_t* PbT, const float* P,
+                        hipStream_t s) {
+  if (io.targets)
+    hipLaunchKernelGGL(conv_net_fused<true>, dim3(B), dim3(kFuseThreads), 0, s, io, Pb, PbT, P);
+  else
+    hipLaunchKernelGGL(conv_net_fused<false>, dim3(B), dim3(kFuseThreads), 0, s, io, Pb, PbT, P);
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- pool + FC (+ loss and its backward)
-
-// One 64-thread workgroup per sample: g = mean(a4), h1 = relu(fw1 g + fb1),
-// out = fw2 h1 + fb2.  With targets, also the squared error, dout and the FC /
-// pool backward down to dZ4 = dA4 * (a4 > 0); per-sample FC weight gradients go
-// to `fcg` [B][fc params] and are summed over the batch in a fixed order later.
-__global__ __launch_bounds__(64) void head_kernel(const uint16_t* __restrict__ a4, const float* __restrict__ P,
-                                                  const float* __restrict__ targets, int B, float* __restrict__ out,
-                                                  float* __restrict__ sqerr, float* __restrict__ fcg,
-                                                  uint16_t* __restrict__ dz4) {
-  const Offsets o = offsets();
-  const int b = blockIdx.x, t = threadIdx.x;
-  __shared__ float g[64], h1[64], dout[kOut], dz1[64];
-  constexpr int HW = 4 * 6;
-  const uint16_t* a = a4 + (size_t)b * HW * 64;
-  const float v = head_forward(a, P, o, g, h1);
-  if (t < kOut) {
-    out[b * kOut + t] = v;
-    if (targets) {
-      const float d = v - targets[b * kOut + t];
-      dout[t] = 2.0f * d / (float)(B * kOut);
-      sqerr[b * kOut + t] = d * d;
-    }
-  }
-  if (!targets) return;
-  __syncthreads();
-  // FC gradients of this sample (fixed layout: fw1, fb1, fw2, fb2 relative to o.fw1)
-  float* G = fcg + (size_t)b * (o.total - o.fw1);
-  for (int q = t; q < kOut * kHidden; q += 64) G[o.fw2 - o.fw1 + q] = dout[q / kHidden] * h1[q % kHidden];
-  if (t < kOut) G[o.fb2 - o.fw1 + t] = dout[t];
-  float dh = 0.f;
-  for (int q = 0; q < kOut; ++q) dh = fmaf(P[o.fw2 + q * kHidden + t], dout[q], dh);
-  dz1[t] = h1[t] > 0.f ? dh : 0.f;
-  __syncthreads();
-  for (int q = 0; q < 64; ++q) G[t * 64 + q] = dz1[t] * g[q];
-  G[o.fb1 - o.fw1 + t] = dz1[t];
-  float dg = 0.f;
-  for (int q = 0; q < kHidden; ++q) dg = fmaf(P[o.fw1 + q * 64 + t], dz1[q], dg);
-  dg *= (1.0f / HW);
-  const uint16_t dgb = f2bf(dg);
-  for (int p = 0; p < HW; ++p) dz4[((size_t)b * HW + p) * 64 + t] = bf2f(a[p * 64 + t]) > 0.f ? dgb : (uint16_t)0;
-}
-
-// ---------------------------------------------------------------- backward convolution
-
-__device__ __forceinline__ short4_t bf16x4(uint2 v) {
-  return short4_t{(short)(v.x & 0xffff), (short)(v.x >> 16), (short)(v.y & 0xffff), (short)(v.y >> 16)};
-}
-
-// Data gradient of layer L >= 1, fused with the ReLU mask of its input:
-// dZprev[b][y][x][c] = (a_prev > 0) * sum over taps (ky, kx) and channels o of
-// W[o][ky][kx][c] dZ[b][i][j][o], where 2i + ky - 1 = y and 2j + kx - 1 = x.
-// Stride 2 makes the reaching taps depend only on the parities of (y, x): an
-// even row is reached by ky = 1 alone, an odd one by ky = 0 and 2 (columns
-// likewise), so the rows of the implicit GEMM are the input pixels of one
-// parity class (blockIdx.y) and k = (reaching tap, o).  wT: the layer's BF16
-// weights as [tap][ci][co].  A wave computes 16 pixels x CI channels.
-template <int L>
-__global__ __launch_bounds__(256) void conv_bwd_data_mfma(const uint16_t* __restrict__ dz,
-                                                          const uint16_t* __restrict__ wT,
-                                                          const uint16_t* __restrict__ aprev, int B,
-                                                          uint16_t* __restrict__ dzprev) {
-  constexpr int CI = kC[L], CO = kC[L + 1], H = kHs[L], W = kWs[L], Ho = kHs[L + 1], Wo = kWs[L + 1];
-  constexpr int NT = CI / 16;
-  static_assert(CI % 16 == 0 && CO % 16 == 0, "16-channel tiles");
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = lane >> 4;
-  const int py = blockIdx.y >> 1, px = blockIdx.y & 1;
-  const int Hc = (H - py + 1) / 2, Wc = (W - px + 1) / 2;
-  const int M = B * Hc * Wc;
-  const int m0 = (blockIdx.x * 4 + wave) * 16;
-  if (m0 >= M) return;
-  const int m = m0 + (lane & 15);
-  const bool mvalid = m < M;
-  const int b = mvalid ? m / (Hc * Wc) : 0, r = mvalid ? m % (Hc * Wc) : 0;
-  const int y = 2 * (r / Wc) + py, x = 2 * (r % Wc) + px;
-  float4_t acc[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) acc[t] = float4_t{0.f, 0.f, 0.f, 0.f};
-  for (int ta = 0; ta < (py ? 2 : 1); ++ta)
-    for (int tb = 0; tb < (px ? 2 : 1); ++tb) {
-      const int ky = py ? 2 * ta : 1, kx = px ? 2 * tb : 1, tap = ky * 3 + kx;
-      const int i = (y + 1 - ky) >> 1, j = (x + 1 - kx) >> 1;  // y + 1 - ky >= 0 and even
-      const bool ok = mvalid && i < Ho && j < Wo;
-      // a row the tap does not reach reads pixel 0 and discards it
-      const uint16_t* drow = dz + (ok ? (((size_t)b * Ho + i) * Wo + j) * CO : 0);
-#pragma unroll
-      for (int o0 = 0; o0 < CO; o0 += 16) {
-        const int k0 = o0 + 4 * q;
-        uint2 dv = *reinterpret_cast<const uint2*>(drow + k0);
-        if (!ok) dv = make_uint2(0u, 0u);
-        const short4_t av = bf16x4(dv);
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          const int n = t * 16 + (lane & 15);
-          const short4_t bv = bf16x4(*reinterpret_cast<const uint2*>(wT + ((size_t)tap * CI + n) * CO + k0));
-          acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, acc[t], 0, 0, 0);
-        }
-      }
-    }
-  // D[4q + j][lane % 16]: pixel row m0 + 4q + j, channel t * 16 + lane % 16
-#pragma unroll
-  for (int jq = 0; jq < 4; ++jq) {
-    const int mo = m0 + 4 * q + jq;
-    if (mo >= M) continue;
-    const int bo = mo / (Hc * Wc), ro = mo % (Hc * Wc);
-    const int yo = 2 * (ro / Wc) + py, xo = 2 * (ro % Wc) + px;
-    const size_t base = (((size_t)bo * H + yo) * W + xo) * CI;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const size_t id = base + t * 16 + (lane & 15);
-      dzprev[id] = bf2f(aprev[id]) > 0.f ? f2bf(acc[t][jq]) : (uint16_t)0;
-    }
-  }
-}
+// ---------------------------------------------------------------- weight gradient
 
 // Weight and bias gradient of layer L over the output pixels p = (b, i, j) of
 // split blockIdx.y: partial[split][o][n] = sum_p dZ[p][o] Xcol[p][n], where
@@ -515,25 +574,24 @@ __global__ __launch_bounds__(256) void reduce_batch(const float* __restrict__ v,
 
 // ---------------------------------------------------------------- Adam
 
-// Adam (Kingma & Ba 2015) on the FP32 master weights with bias correction c1 =
-// 1 - b1^t, c2 = 1 - b2^t; refreshes the BF16 conv weight copies.
-// BF16 copies of parameter e: Pb[e]; a convolution weight ([co][ky][kx][ci])
-// also into PbT as [tap][ci][co], the operand layout of the data gradient.
+// The BF16 copies of convolution weight e ([co][ky][kx][ci] in P).
 __device__ __forceinline__ void store_bf16_param(int e, float p, uint16_t* __restrict__ Pb,
                                                  uint16_t* __restrict__ PbT) {
   const uint16_t h = f2bf(p);
-  Pb[e] = h;
   const Offsets o = offsets();
 #pragma unroll
   for (int l = 0; l < 4; ++l) {
     const int CI = kC[l], CO = kC[l + 1], r = e - o.w[l];
     if (r >= 0 && r < CO * 9 * CI) {
-      const int co = r / (9 * CI), tap = (r / CI) % 9, ci = r % CI;
-      PbT[o.w[l] + (tap * CI + ci) * CO + co] = h;
+      const int co = r / (9 * CI), k = r % (9 * CI);
+      Pb[wrow_off(l) + co * kWRow[l] + k] = h;
+      if (l > 0) PbT[trow_off(l) + k * kTRow[l] + co] = h;
     }
   }
 }
 
+// Adam (Kingma & Ba 2015) on the FP32 master weights with bias correction c1 =
+// 1 - b1^t, c2 = 1 - b2^t; refreshes the BF16 conv weight copies.
 __global__ void adam_kernel(float* __restrict__ P, const float* __restrict__ G, float* __restrict__ M,
                             float* __restrict__ V, int n, float lr, float b1, float b2, float eps, float c1, float c2,
                             int conv_end, uint16_t* __restrict__ Pb, uint16_t* __restrict__ PbT) {
@@ -572,8 +630,8 @@ struct dpt_cnn {
   hipStream_t stream = nullptr;
   Offsets o;
   float *P = nullptr, *G = nullptr, *M = nullptr, *V = nullptr;  // FP32 master, gradient, Adam moments
-  uint16_t* Pb = nullptr;                                          // BF16 copy (conv weights used)
-  uint16_t* PbT = nullptr;                                         // BF16 conv weights as [tap][ci][co]
+  uint16_t* Pb = nullptr;                                          // BF16 conv weights, kWRow layout
+  uint16_t* PbT = nullptr;                                         // BF16 conv weights as [tap][ci][co], kTRow layout
   uint16_t* act[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
   // dz[l]: gradient at layer l's output (pre-ReLU), BF16 NHWC; sized for FP32
   // so that the activation test hook can stage an FP32 copy there
@@ -648,13 +706,6 @@ hipError_t bwd_layer(dpt_cnn* c, int B) {
                      c->act[L], P, kPixPerSplit[L], c->partial);
   launch_sum<WgradSum<L>::template K>(splits, CO * npad(L), c->stream, (const float*)c->partial, splits,
                                       c->G + c->o.w[L], c->G + c->o.b[L]);
-  if constexpr (L > 0) {
-    int rows = 0;  // the largest parity class
-    for (int cls = 0; cls < 4; ++cls)
-      rows = std::max(rows, B * ((kHs[L] - (cls >> 1) + 1) / 2) * ((kWs[L] - (cls & 1) + 1) / 2));
-    hipLaunchKernelGGL((conv_bwd_data_mfma<L>), dim3((rows + 63) / 64, 4), dim3(256), 0, c->stream, c->dz[L + 1],
-                       c->PbT + c->o.w[L], c->act[L], B, c->dz[L]);
-  }
   return hipGetLastError();
 }
 
@@ -666,10 +717,10 @@ hipError_t backward(dpt_cnn* c, int B) {
   return bwd_layer<0>(c, B);
 }
 
-// The forward pass of B planar pairs (host or device) through the fused
-// kernel, every layer's activations kept for the backward pass; with head,
-// the head's outputs to c->out as well.
-int forward_pairs(dpt_cnn* c, const uint8_t* pairs, int B, int on_device, bool head) {
+// The fused pass over B planar pairs (host or device), every layer's activations
+// kept and the head's outputs in c->out; with targets (device), the backward pass
+// down to the layers' gradients too.
+int forward_pairs(dpt_cnn* c, const uint8_t* pairs, int B, int on_device, const float* targets) {
   const uint8_t* src = pairs;
   if (!on_device) {
     CNN_TRY(hipMemcpyAsync(c->pairs, pairs, (size_t)B * 2 * kH0 * kW0, hipMemcpyHostToDevice, c->stream));
@@ -678,8 +729,11 @@ int forward_pairs(dpt_cnn* c, const uint8_t* pairs, int B, int on_device, bool h
   FusedIO io{};
   io.pairs = src;
   for (int l = 0; l < 5; ++l) io.act[l] = c->act[l];
-  io.out = head ? c->out : nullptr;
-  CNN_TRY(launch_fused(io, B, c->Pb, c->P, c->stream));
+  io.out = c->out;
+  io.targets = targets;
+  io.sqerr = c->sqerr, io.fcg = c->fcg, io.B = B;
+  for (int l = 0; l < 5; ++l) io.dz[l] = c->dz[l];
+  CNN_TRY(launch_fused(io, B, c->Pb, c->PbT, c->P, c->stream));
   return DPT_OK;
 }
 
@@ -699,7 +753,7 @@ int dpt_cnn_create(int32_t max_batch, void* hip_stream, dpt_cnn** out) {
   const size_t n = (size_t)c->o.total, B = (size_t)max_batch;
   bool ok = hipMalloc(&c->P, n * 4) == hipSuccess && hipMalloc(&c->G, n * 4) == hipSuccess &&
             hipMalloc(&c->M, n * 4) == hipSuccess && hipMalloc(&c->V, n * 4) == hipSuccess &&
-            hipMalloc(&c->Pb, n * 2) == hipSuccess && hipMalloc(&c->PbT, n * 2) == hipSuccess;
+            hipMalloc(&c->Pb, kPbTotal * 2) == hipSuccess && hipMalloc(&c->PbT, kPbTTotal * 2) == hipSuccess;
   for (int l = 0; l < 5 && ok; ++l) {
     const size_t e = B * kHs[l] * kWs[l] * kC[l];
     ok = hipMalloc(&c->act[l], e * 2) == hipSuccess && hipMalloc(&c->dz[l], e * 4) == hipSuccess;
@@ -722,8 +776,8 @@ int dpt_cnn_create(int32_t max_batch, void* hip_stream, dpt_cnn** out) {
   (void)hipMemsetAsync(c->M, 0, n * 4, c->stream);
   (void)hipMemsetAsync(c->V, 0, n * 4, c->stream);
   (void)hipMemsetAsync(c->P, 0, n * 4, c->stream);
-  (void)hipMemsetAsync(c->Pb, 0, n * 2, c->stream);
-  (void)hipMemsetAsync(c->PbT, 0, n * 2, c->stream);
+  (void)hipMemsetAsync(c->Pb, 0, kPbTotal * 2, c->stream);
+  (void)hipMemsetAsync(c->PbT, 0, kPbTTotal * 2, c->stream);
   if (hipStreamSynchronize(c->stream) != hipSuccess) {
     delete c;
     return cfail(DPT_E_HIP, "stream synchronize");
@@ -791,7 +845,7 @@ int dpt_cnn_get_grads(dpt_cnn* c, float* grads) {
 int dpt_cnn_forward(dpt_cnn* c, const uint8_t* pairs, int32_t B, int32_t on_device, float* out_host) {
   if (!c || !pairs || !out_host) return cfail(DPT_E_ARG, "NULL argument");
   if (B < 1 || B > c->max_batch) return cfail(DPT_E_ARG, "batch size");
-  int e = forward_pairs(c, pairs, B, on_device, true);
+  int e = forward_pairs(c, pairs, B, on_device, nullptr);
   if (e != DPT_OK) return e;
   CNN_TRY(hipMemcpyAsync(out_host, c->out, sizeof(float) * B * kOut, hipMemcpyDeviceToHost, c->stream));
   CNN_TRY(hipStreamSynchronize(c->stream));
@@ -806,16 +860,14 @@ int dpt_cnn_train_step(dpt_cnn* c, const uint8_t* pairs, const float* targets, i
                        int32_t on_device, float* loss_out) {
   if (!c || !pairs || !targets || !loss_out) return cfail(DPT_E_ARG, "NULL argument");
   if (B < 1 || B > c->max_batch) return cfail(DPT_E_ARG, "batch size");
-  int e = forward_pairs(c, pairs, B, on_device, false);
-  if (e != DPT_OK) return e;
   const float* tg = targets;
   if (!on_device) {
     CNN_TRY(hipMemcpyAsync(c->tgt, targets, sizeof(float) * B * kOut, hipMemcpyHostToDevice, c->stream));
     tg = c->tgt;
   }
+  int e = forward_pairs(c, pairs, B, on_device, tg);
+  if (e != DPT_OK) return e;
   const Offsets& o = c->o;
-  hipLaunchKernelGGL(head_kernel, dim3(B), dim3(64), 0, c->stream, c->act[4], c->P, tg, B, c->out, c->sqerr, c->fcg,
-                     c->dz[4]);
   const int nfc = o.total - o.fw1;
   launch_sum<BatchSum>(B, nfc, c->stream, (const float*)c->fcg, B, nfc, c->G + o.fw1);
   launch_sum<BatchSum>(B, kOut, c->stream, (const float*)c->sqerr, B, (int)kOut, c->scal);
@@ -866,7 +918,7 @@ int cnn_forward_levels(dpt_cnn* c, const uint8_t* const* refs, const uint8_t* co
   CNN_TRY(hipMemcpyAsync(c->d_lv, h.data(), sizeof(void*) * 2 * B, hipMemcpyHostToDevice, c->stream));
   FusedIO io{};
   io.refs = c->d_lv, io.curs = c->d_lv + B, io.act[4] = c->act[4], io.out = c->out;
-  CNN_TRY(launch_fused(io, B, c->Pb, c->P, c->stream));
+  CNN_TRY(launch_fused(io, B, c->Pb, c->PbT, c->P, c->stream));
   CNN_TRY(hipMemcpyAsync(out_host, c->out, sizeof(float) * B * kOut, hipMemcpyDeviceToHost, c->stream));
   CNN_TRY(hipStreamSynchronize(c->stream));
   return DPT_OK;
@@ -876,7 +928,7 @@ int cnn_propose(dpt_cnn* c, const uint8_t* const* d_lv, int B, hipStream_t s, do
   if (B < 1 || B > c->max_batch) return cfail(DPT_E_ARG, "batch size");
   FusedIO io{};
   io.refs = d_lv, io.curs = d_lv + B, io.act[4] = c->act[4], io.out = c->out, io.rel = rel;
-  CNN_TRY(launch_fused(io, B, c->Pb, c->P, s));
+  CNN_TRY(launch_fused(io, B, c->Pb, c->PbT, c->P, s));
   return DPT_OK;
 }
 
