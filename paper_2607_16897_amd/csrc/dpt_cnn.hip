@@ -10,12 +10,13 @@
 // the epilogue.  The backward convolutions are implicit GEMMs on the same
 // instruction: the data gradient per stride-parity class of the input pixels
 // (only the taps that reach a class), the weight gradient as dZ^T Xcol split
-// over output pixels, with the bias gradient as a column of ones; gradients
+// over samples, with the bias gradient as a column of ones; gradients
 // flowing between layers are stored in BF16, split reductions are summed in a
 // fixed order.  Pooling, the FC layers, the loss and Adam run on the vector
 // units; master weights and Adam moments are FP32.
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/dptrack.h"
@@ -468,111 +469,190 @@ hipError_t launch_fused(const FusedIO& io, int B, const uint16_t* Pb, const uint
 
 // ---------------------------------------------------------------- weight gradient
 
-// Weight and bias gradient of layer L over the output pixels p = (b, i, j) of
-// split blockIdx.y: partial[split][o][n] = sum_p dZ[p][o] Xcol[p][n], where
-// Xcol[p][tap * CI + c] = X[b][2i + ky - 1][2j + kx - 1][c] (zero outside the
+// Weight and bias gradient of layer L + 1 over the samples b0 .. b1 - 1, in one
+// workgroup of sixteen waves: dW[o][n] = sum over pixels p of dZ[p][o] Xcol[p][n],
+// where Xcol[p][tap * CI + c] = X[2i + ky - 1][2j + kx - 1][c] (zero outside the
 // image) and column n = 9 CI is all ones (the bias); columns up to the next
-// multiple of 16 are zero.  One wave per 16 x 16 output tile (blockIdx.x * 4 +
-// wave over CO / 16 x NPAD / 16 tiles), 16 pixels per MFMA step.
+// multiple of 16 are zero.  v_mfma_f32_16x16x32_bf16 over four groups of eight
+// pixels of a row.
+//
+// A lane's operand is eight pixels of one channel, so a sample is transposed into
+// LDS: dZ as [o][i][j] and X by the parities of its pixels, [c][row][kx][j], where
+// row i of the first Ho is y = 2i (ky = 1), row i of the rest y = 2i - 1 (ky = 0;
+// ky = 2 one on), and column j of variant kx is x = 2j + kx - 1: each tap of eight
+// output pixels is eight consecutive elements, whatever the stride.  Rows are
+// padded to groups of eight, channels so that sixteen lanes' 16-byte reads fall on
+// different banks.  The products are few (a 16x16 tile takes 1 to 45 steps a
+// sample): the transposition and its latency bound it, so the next sample is read
+// while one is multiplied and each element is read once per layer, where a wave
+// per output tile that gathers from global memory reads it 37 to 148 times.
 template <int L>
-__global__ __launch_bounds__(256) void conv_bwd_weight_mfma(const uint16_t* __restrict__ dz,
-                                                            const uint16_t* __restrict__ x, int P, int per_split,
-                                                            float* __restrict__ partial) {
-  constexpr int CI = kC[L], CO = kC[L + 1], H = kHs[L], W = kWs[L], Ho = kHs[L + 1], Wo = kWs[L + 1];
-  constexpr int NPAD = (9 * CI + 1 + 15) / 16 * 16, MT = CO / 16, NT = NPAD / 16;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = lane >> 4;
-  const int tile = blockIdx.x * 4 + wave;
-  if (tile >= MT * NT) return;
-  const int mt = tile / NT, nt = tile % NT, split = blockIdx.y;
-  const int p0 = split * per_split, p1 = min(P, p0 + per_split);
-  const int o = mt * 16 + (lane & 15), n = nt * 16 + (lane & 15);
-  const bool real = n < 9 * CI, ones = n == 9 * CI;
-  const int tap = real ? n / CI : 0, c = real ? n % CI : 0, ky = tap / 3, kx = tap % 3;
-  // the lane's four rows of the step at pb: dZ and the im2col column
-  auto operands = [&](int pb, short (&a)[4], short (&bb)[4]) {
+struct Wgrad {
+  static constexpr int CI = kC[L], CO = kC[L + 1], H = kHs[L], W = kWs[L], Ho = kHs[L + 1], Wo = kWs[L + 1];
+  static constexpr int Wp = (Wo + 7) / 8 * 8, GR = Wp / 8, NG = Ho * GR, STEPS = (NG + 3) / 4;
+  static constexpr int MT = CO / 16, NT = (9 * CI + 1 + 15) / 16, NPAD = 16 * NT;
+  // waves: MT x NGRP groups of NTW column tiles x KG shares of the steps
+  static constexpr int NTW = L == 3 ? 10 : L == 0 ? 2 : 5, NGRP = (NT + NTW - 1) / NTW, KG = 16 / (MT * NGRP);
+  static_assert(MT * NGRP * KG == 16, "sixteen waves");
+  static constexpr int XROW = 3 * Wp, XP = (2 * Ho + 1) * XROW + (L == 2 ? 8 : 0), DP = STEPS * 32 + 8;
+  static constexpr int XN = CI * XP, DN = CO * DP, BYTES = 2 * (XN + DN);
+  static_assert(XP % 8 == 0 && BYTES >= (KG > 1 ? KG * MT * NT * 1024 : 0), "16-byte rows; room for the shares' sums");
+  // what a thread moves of a sample: pixels of eight channels (X of layer 1: of two)
+  static constexpr int XG = CI == 2 ? 1 : CI / 8, DG = CO / 8;
+  static constexpr int XI = (H * W * XG + kFuseThreads - 1) / kFuseThreads, DI = (Ho * Wo * DG + kFuseThreads - 1) / kFuseThreads;
+};
+
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+
+template <int L>
+__device__ __forceinline__ void wgrad_layer(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dz, int b0,
+                                            int b1, uint16_t* lds, float* __restrict__ out) {
+  using C = Wgrad<L>;
+  using XV = typename std::conditional<C::CI == 2, uint32_t, uint4>::type;
+  constexpr int XC = C::CI == 2 ? 2 : 8;  // channels of an X item
+  const int t = threadIdx.x, lane = t & 63, q = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  uint16_t* xt = lds;
+  uint16_t* dt = lds + C::XN;
+  XV xr[C::XI];
+  uint4 dr[C::DI];
+  const auto load = [&](int b) {
+    const uint16_t* xs = x + (size_t)b * C::H * C::W * C::CI;
+    const uint16_t* ds = dz + (size_t)b * C::Ho * C::Wo * C::CO;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int p = pb + 4 * q + t;
-      uint16_t av = 0, bv = 0;
-      if (p < p1) {
-        av = dz[(size_t)p * CO + o];
-        if (ones) {
-          bv = 0x3f80;  // 1.0
-        } else if (real) {
-          const int b = p / (Ho * Wo), ij = p % (Ho * Wo);
-          const int yy = 2 * (ij / Wo) + ky - 1, xx = 2 * (ij % Wo) + kx - 1;
-          if (yy >= 0 && yy < H && xx >= 0 && xx < W) bv = x[(((size_t)b * H + yy) * W + xx) * CI + c];
-        }
-      }
-      a[t] = (short)av;
-      bb[t] = (short)bv;
+    for (int k = 0; k < C::XI; ++k) {  // consecutive threads: consecutive pixels of a channel group
+      const int e = min(t + k * kFuseThreads, C::H * C::W * C::XG - 1), px = e % (C::H * C::W), g = e / (C::H * C::W);
+      xr[k] = gload(reinterpret_cast<const XV*>(xs + px * C::CI + XC * g));
+    }
+#pragma unroll
+    for (int k = 0; k < C::DI; ++k) {
+      const int e = min(t + k * kFuseThreads, C::Ho * C::Wo * C::DG - 1), px = e % (C::Ho * C::Wo), g = e / (C::Ho * C::Wo);
+      dr[k] = gload(reinterpret_cast<const uint4*>(ds + px * C::CO + 8 * g));
     }
   };
-  float4_t acc = float4_t{0.f, 0.f, 0.f, 0.f};
-  short a[4], bb[4];
-  operands(p0, a, bb);
-  for (int pb = p0; pb < p1; pb += 16) {  // the next step's loads in flight during this step's product
-    short a2[4], b2[4];
-    operands(pb + 16, a2, b2);
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(short4_t{a[0], a[1], a[2], a[3]},
-                                                     short4_t{bb[0], bb[1], bb[2], bb[3]}, acc, 0, 0, 0);
+  load(b0);
+  for (int e = t; e < C::BYTES / 16; e += kFuseThreads) reinterpret_cast<uint4*>(lds)[e] = make_uint4(0u, 0u, 0u, 0u);
+  // this wave's tiles: row tile mt, column tiles nt0 .. nt0 + NTW - 1, steps kg, kg + KG, ...
+  const int mt = wave % C::MT, nt0 = wave / C::MT % C::NGRP * C::NTW, kg = wave / (C::MT * C::NGRP);
+  int col[C::NTW];  // where column n's taps start in xt
+  bool real[C::NTW], ones[C::NTW];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) a[t] = a2[t], bb[t] = b2[t];
+  for (int k = 0; k < C::NTW; ++k) {
+    const int n = (nt0 + k) * 16 + (lane & 15);
+    real[k] = n < 9 * C::CI, ones[k] = n == 9 * C::CI;
+    const int tap = real[k] ? n / C::CI : 0, c = real[k] ? n % C::CI : 0, ky = tap / 3, kx = tap % 3;
+    col[k] = c * C::XP + ((ky == 1 ? 0 : C::Ho) + (ky == 2)) * C::XROW + kx * C::Wp;
   }
-  float* out = partial + (size_t)split * CO * NPAD;
+  float4_t acc[C::NTW];
 #pragma unroll
-  for (int jq = 0; jq < 4; ++jq) out[(size_t)(mt * 16 + 4 * q + jq) * NPAD + n] = acc[jq];
-}
-
-// sum_k v[k * n + e] for the n elements e of a block's share, in a fixed
-// order: the PARTS threads of an element (threads el, el + 256 / PARTS, ...)
-// sum k = part, part + PARTS, ... in order, and the parts meet in a fixed
-// pairwise tree in LDS.  The result goes to out(e, sum) (part 0's thread).
-template <int PARTS, class Out>
-__device__ __forceinline__ void sum_slices(const float* __restrict__ v, int K, int n, Out out) {
-  constexpr int EPB = 256 / PARTS;  // elements per block
-  __shared__ float sh[256];
-  const int el = (int)threadIdx.x % EPB, part = (int)threadIdx.x / EPB;
-  const int e = (int)blockIdx.x * EPB + el;
-  float s = 0.f;
-  if (e < n)
-    for (int k = part; k < K; k += PARTS) s += v[(size_t)k * n + e];
-  sh[threadIdx.x] = s;
-  __syncthreads();
+  for (int k = 0; k < C::NTW; ++k) acc[k] = float4_t{0.f, 0.f, 0.f, 0.f};
+  for (int b = b0; b < b1; ++b) {
+    __syncthreads();  // the previous sample's products (first: the zeros) are done
 #pragma unroll
-  for (int w = PARTS / 2; w > 0; w >>= 1) {
-    if (part < w) sh[threadIdx.x] += sh[threadIdx.x + w * EPB];
+    for (int k = 0; k < C::XI; ++k) {
+      const int e = t + k * kFuseThreads, px = e % (C::H * C::W), g = e / (C::H * C::W);
+      if (e >= C::H * C::W * C::XG) continue;
+      const int y = px / C::W, xx = px % C::W;
+      uint16_t* r = xt + XC * g * C::XP + ((y & 1) ? C::Ho + (y + 1) / 2 : y / 2) * C::XROW;
+      const uint32_t* v = reinterpret_cast<const uint32_t*>(&xr[k]);
+      if (xx & 1) {
+        uint16_t *r2 = r + 2 * C::Wp + (xx - 1) / 2, *r0 = r + (xx + 1) / 2;
+#pragma unroll
+        for (int c = 0; c < XC; ++c) {
+          const uint16_t h = (uint16_t)(v[c / 2] >> (16 * (c & 1)));
+          r2[c * C::XP] = h, r0[c * C::XP] = h;
+        }
+      } else {
+        uint16_t* r1 = r + C::Wp + xx / 2;
+#pragma unroll
+        for (int c = 0; c < XC; ++c) r1[c * C::XP] = (uint16_t)(v[c / 2] >> (16 * (c & 1)));
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < C::DI; ++k) {
+      const int e = t + k * kFuseThreads, px = e % (C::Ho * C::Wo), g = e / (C::Ho * C::Wo);
+      if (e >= C::Ho * C::Wo * C::DG) continue;
+      uint16_t* r = dt + 8 * g * C::DP + px / C::Wo * C::Wp + px % C::Wo;
+      const uint32_t* v = reinterpret_cast<const uint32_t*>(&dr[k]);
+#pragma unroll
+      for (int c = 0; c < 8; ++c) r[c * C::DP] = (uint16_t)(v[c / 2] >> (16 * (c & 1)));
+    }
+    if (b + 1 < b1) load(b + 1);
     __syncthreads();
+    for (int s = kg; s < C::STEPS; s += C::KG) {
+      const int grp = 4 * s + q, gx = grp < C::NG ? grp : 0;  // past the last group: zeros in dt
+      const int xo = gx / C::GR * C::XROW + gx % C::GR * 8;
+      const bf16x8_t av = *reinterpret_cast<const bf16x8_t*>(dt + (mt * 16 + (lane & 15)) * C::DP + 8 * grp);
+#pragma unroll
+      for (int k = 0; k < C::NTW; ++k) {
+        uint4 u = *reinterpret_cast<const uint4*>(xt + col[k] + xo);
+        const uint32_t fill = ones[k] ? 0x3f803f80u : 0u;  // 1.0 twice
+        u = make_uint4(real[k] ? u.x : fill, real[k] ? u.y : fill, real[k] ? u.z : fill, real[k] ? u.w : fill);
+        acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8_t, u), acc[k], 0, 0, 0);
+      }
+    }
   }
-  if (part == 0 && e < n) out(e, sh[el]);
+  if constexpr (C::KG > 1) {  // the shares of the steps, summed in order
+    float* sh = reinterpret_cast<float*>(lds);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < C::NTW; ++k)
+      *reinterpret_cast<float4_t*>(sh + (((kg * C::MT + mt) * C::NT + nt0 + k) * 64 + lane) * 4) = acc[k];
+    __syncthreads();
+    for (int e = t; e < C::MT * C::NT * 256; e += kFuseThreads) {
+      float v = 0.f;
+#pragma unroll
+      for (int g = 0; g < C::KG; ++g) v += sh[g * C::MT * C::NT * 256 + e];
+      const int tile = e >> 8, l = e >> 2 & 63;
+      out[(tile / C::NT * 16 + 4 * (l >> 4) + (e & 3)) * C::NPAD + tile % C::NT * 16 + (l & 15)] = v;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < C::NTW; ++k)
+      if (nt0 + k < C::NT)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          out[(mt * 16 + 4 * q + j) * C::NPAD + (nt0 + k) * 16 + (lane & 15)] = acc[k][j];
+  }
 }
 
-// Threads per element for a sum over K slices: about sixteen slices each.
-inline int parts_for(int K) { return K > 1024 ? 256 : K > 256 ? 64 : K > 64 ? 16 : K > 16 ? 4 : 1; }
+// Samples per workgroup of layer l for B samples, in 1/256 of B: the workgroups of
+// all layers together are at most 246, one turn of the chip.
+constexpr int kWgradShare[4] = {4, 3, 4, 8};
+constexpr int wgrad_samples(int l, int B) { return (int)(((int64_t)B * kWgradShare[l] + 255) / 256); }
+constexpr int wgrad_slots(int l, int B) { return (B + wgrad_samples(l, B) - 1) / wgrad_samples(l, B); }
+constexpr int npad(int l) { return (9 * kC[l] + 1 + 15) / 16 * 16; }
 
-// Sum of the splits of conv_bwd_weight_mfma into the gradient vector: weights
-// at w_off + o * 9 CI + n ([co][ky][kx][ci]), bias at b_off + o.
-template <int L, int PARTS>
-__global__ __launch_bounds__(256) void reduce_wgrad(const float* __restrict__ partial, int splits,
-                                                    float* __restrict__ gw, float* __restrict__ gb) {
-  constexpr int CI = kC[L], CO = kC[L + 1], NPAD = (9 * CI + 1 + 15) / 16 * 16;
-  sum_slices<PARTS>(partial, splits, CO * NPAD, [&](int e, float s) {
-    const int o = e / NPAD, n = e % NPAD;
-    if (n < 9 * CI)
-      gw[o * 9 * CI + n] = s;
-    else if (n == 9 * CI)
-      gb[o] = s;
-  });
+struct WgradIO {
+  const uint16_t* act[4];  // layer inputs
+  const uint16_t* dz[4];   // layer output gradients
+  float* partial[4];       // [slot][CO][NPAD]
+  int B;
+};
+
+// The weight gradients of all layers' slots, a workgroup each.  256 pairs: four
+// launches of 99 us together with a wave per output tile, now 18.
+__global__ __launch_bounds__(kFuseThreads) void conv_bwd_weight(WgradIO io) {
+  __shared__ __align__(16) uint16_t lds[Wgrad<1>::BYTES / 2];
+  static_assert(Wgrad<0>::BYTES <= Wgrad<1>::BYTES && Wgrad<2>::BYTES <= Wgrad<1>::BYTES &&
+                    Wgrad<3>::BYTES <= Wgrad<1>::BYTES && Wgrad<1>::BYTES <= 160 * 1024,
+                "the largest layer's LDS");
+  int slot = blockIdx.x;
+  const auto run = [&](auto layer) {
+    constexpr int L = decltype(layer)::value;
+    const int n = wgrad_slots(L, io.B), S = wgrad_samples(L, io.B);
+    if (slot >= 0 && slot < n)
+      wgrad_layer<L>(io.act[L], io.dz[L], slot * S, min(io.B, (slot + 1) * S), lds,
+                     io.partial[L] + (size_t)slot * kC[L + 1] * Wgrad<L>::NPAD);
+    slot -= n;
+  };
+  run(std::integral_constant<int, 1>{});
+  run(std::integral_constant<int, 0>{});
+  run(std::integral_constant<int, 2>{});
+  run(std::integral_constant<int, 3>{});
 }
 
-// Sum over the batch of the per-sample FC gradients, and of the squared errors.
-template <int PARTS>
-__global__ __launch_bounds__(256) void reduce_batch(const float* __restrict__ v, int B, int n,
-                                                    float* __restrict__ out) {
-  sum_slices<PARTS>(v, B, n, [&](int e, float s) { out[e] = s; });
-}
-
-// ---------------------------------------------------------------- Adam
+// ---------------------------------------------------------------- sums over slots, Adam
 
 // The BF16 copies of convolution weight e ([co][ky][kx][ci] in P).
 __device__ __forceinline__ void store_bf16_param(int e, float p, uint16_t* __restrict__ Pb,
@@ -590,21 +670,70 @@ __device__ __forceinline__ void store_bf16_param(int e, float p, uint16_t* __res
   }
 }
 
-// Adam (Kingma & Ba 2015) on the FP32 master weights with bias correction c1 =
-// 1 - b1^t, c2 = 1 - b2^t; refreshes the BF16 conv weight copies.
-__global__ void adam_kernel(float* __restrict__ P, const float* __restrict__ G, float* __restrict__ M,
-                            float* __restrict__ V, int n, float lr, float b1, float b2, float eps, float c1, float c2,
-                            int conv_end, uint16_t* __restrict__ Pb, uint16_t* __restrict__ PbT) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  const float g = G[e];
-  const float m = b1 * M[e] + (1.0f - b1) * g;
-  const float v = b2 * V[e] + (1.0f - b2) * g * g;
-  M[e] = m;
-  V[e] = v;
-  const float p = P[e] - lr * (m / c1) / (sqrtf(v / c2) + eps);
-  P[e] = p;
-  if (e < conv_end) store_bf16_param(e, p, Pb, PbT);
+// Where the gradient's sums come from and what they update.
+struct UpdateIO {
+  const float* partial[4];  // weight gradients per slot
+  int slots[4];
+  const float *fcg, *sqerr;  // per sample: FC gradients, squared errors
+  int B;
+  float *G, *loss;  // the gradient; the squared errors' sums (pinned host memory)
+  float *P, *M, *V;
+  uint16_t *Pb, *PbT;
+  float lr, c1, c2;  // lr = 0: the gradient only
+};
+
+// Every element of the gradient (weights at [co][ky][kx][ci]) and the six squared
+// errors: the sum of its slots or samples in a fixed order, sixteen threads to an
+// element (each sums every sixteenth in order, then a pairwise tree), and Adam
+// (Kingma & Ba 2015) on the FP32 master weights, beta 0.9 / 0.999, eps 1e-8, with
+// bias correction c1 = 1 - b1^t, c2 = 1 - b2^t, refreshing the BF16 weights.  One
+// launch for all of them: each of seven took its launch and little more (50 us
+// for 256 pairs), now 8.8.
+__global__ __launch_bounds__(256) void update_kernel(UpdateIO io) {
+  constexpr int PARTS = 16, EPB = 256 / PARTS;
+  __shared__ float sh[256];
+  const Offsets o = offsets();
+  const int el = (int)threadIdx.x % EPB, part = (int)threadIdx.x / EPB;
+  const int e = (int)blockIdx.x * EPB + el;
+  const float* v = io.sqerr + (e - o.total);
+  int stride = kOut, K = e < o.total + kOut ? io.B : 0;
+  if (e < o.fw1) {
+#pragma unroll
+    for (int l = 0; l < 4; ++l) {
+      const int CI = kC[l], CO = kC[l + 1], r = e - o.w[l], rb = e - o.b[l];
+      if (r < 0 || rb >= CO) continue;
+      const int co = rb < 0 ? r / (9 * CI) : rb, n = rb < 0 ? r % (9 * CI) : 9 * CI;
+      v = io.partial[l] + co * npad(l) + n, stride = CO * npad(l), K = io.slots[l];
+    }
+  } else if (e < o.total) {
+    v = io.fcg + (e - o.fw1), stride = o.total - o.fw1;
+  }
+  float s = 0.f;
+#pragma unroll 4
+  for (int k = part; k < K; k += PARTS) s += gload(v + (size_t)k * stride);
+  sh[threadIdx.x] = s;
+  __syncthreads();
+#pragma unroll
+  for (int w = PARTS / 2; w > 0; w >>= 1) {
+    if (part < w) sh[threadIdx.x] += sh[threadIdx.x + w * EPB];
+    __syncthreads();
+  }
+  if (part != 0 || e >= o.total + kOut) return;
+  const float g = sh[el];
+  if (e >= o.total) {
+    io.loss[e - o.total] = g;
+    return;
+  }
+  io.G[e] = g;
+  if (!(io.lr > 0.f)) return;
+  const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+  const float m = b1 * io.M[e] + (1.0f - b1) * g;
+  const float w = b2 * io.V[e] + (1.0f - b2) * g * g;
+  io.M[e] = m;
+  io.V[e] = w;
+  const float p = io.P[e] - io.lr * (m / io.c1) / (sqrtf(w / io.c2) + eps);
+  io.P[e] = p;
+  if (e < o.fw1) store_bf16_param(e, p, io.Pb, io.PbT);
 }
 
 __global__ void to_bf16(const float* __restrict__ P, int n, uint16_t* __restrict__ Pb, uint16_t* __restrict__ PbT) {
@@ -636,15 +765,16 @@ struct dpt_cnn {
   // dz[l]: gradient at layer l's output (pre-ReLU), BF16 NHWC; sized for FP32
   // so that the activation test hook can stage an FP32 copy there
   uint16_t* dz[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
-  float *out = nullptr, *tgt = nullptr, *sqerr = nullptr, *fcg = nullptr, *partial = nullptr, *scal = nullptr;
+  float *out = nullptr, *tgt = nullptr, *sqerr = nullptr, *fcg = nullptr, *partial = nullptr;
   uint8_t* pairs = nullptr;
   const uint8_t** d_lv = nullptr;  // [2][max_batch] level pointers
   int step = 0;
   float* h_buf = nullptr;  // pinned
+  float* h_buf_dev = nullptr;  // its address on the device
   size_t partial_floats = 0;
   ~dpt_cnn() {
     for (void* p : {(void*)P, (void*)G, (void*)M, (void*)V, (void*)Pb, (void*)PbT, (void*)out, (void*)tgt, (void*)sqerr,
-                    (void*)fcg, (void*)partial, (void*)scal, (void*)pairs, (void*)d_lv})
+                    (void*)fcg, (void*)partial, (void*)pairs, (void*)d_lv})
       if (p) (void)hipFree(p);
     for (int l = 0; l < 5; ++l) {
       if (act[l]) (void)hipFree(act[l]);
@@ -664,57 +794,43 @@ int cfail(int code, const char* msg) { return set_error(code, msg); }
     if (e_ != hipSuccess) return cfail(DPT_E_HIP, #expr);      \
   } while (0)
 
-// Output pixels per split of the weight gradient, per layer: 8-16 MFMA steps
-// per wave and a few thousand waves, so the loads of many waves overlap (the
-// first and last layers have the fewest tiles, so the shortest splits).
-constexpr int kPixPerSplit[4] = {128, 256, 256, 128};
+// Room for them at any B: at most 256 / share slots a layer.
+constexpr size_t max_partial() {
+  size_t n = 0;
+  for (int l = 0; l < 4; ++l) n += (size_t)((256 + kWgradShare[l] - 1) / kWgradShare[l]) * kC[l + 1] * npad(l);
+  return n;
+}
+constexpr size_t kMaxPartial = max_partial();
 
-int splits_for(int l, int B) { return (B * kHs[l + 1] * kWs[l + 1] + kPixPerSplit[l] - 1) / kPixPerSplit[l]; }
-
-// Launch of a sum over K slices with the PARTS that parts_for(K) picks.
-template <template <int> class Kernel, class... Args>
-void launch_sum(int K, int n, hipStream_t s, Args... args) {
-  switch (parts_for(K)) {
-    case 256: hipLaunchKernelGGL(Kernel<256>::fn, dim3(n), dim3(256), 0, s, args...); break;
-    case 64: hipLaunchKernelGGL(Kernel<64>::fn, dim3((n + 3) / 4), dim3(256), 0, s, args...); break;
-    case 16: hipLaunchKernelGGL(Kernel<16>::fn, dim3((n + 15) / 16), dim3(256), 0, s, args...); break;
-    case 4: hipLaunchKernelGGL(Kernel<4>::fn, dim3((n + 63) / 64), dim3(256), 0, s, args...); break;
-    default: hipLaunchKernelGGL(Kernel<1>::fn, dim3((n + 255) / 256), dim3(256), 0, s, args...); break;
+// The weight gradients' slots for B samples, one layer after the other in `partial`.
+size_t partial_floats(int B, size_t (&at)[4]) {
+  size_t n = 0;
+  for (int l = 0; l < 4; ++l) {
+    at[l] = n;
+    n += (size_t)wgrad_slots(l, B) * kC[l + 1] * npad(l);
   }
+  return n;
 }
 
-template <int L>
-struct WgradSum {
-  template <int PARTS>
-  struct K {
-    static constexpr auto fn = reduce_wgrad<L, PARTS>;
-  };
-};
-template <int PARTS>
-struct BatchSum {
-  static constexpr auto fn = reduce_batch<PARTS>;
-};
-
-constexpr int npad(int l) { return (9 * kC[l] + 1 + 15) / 16 * 16; }
-
-template <int L>
-hipError_t bwd_layer(dpt_cnn* c, int B) {
-  constexpr int CO = kC[L + 1];
-  const int P = B * kHs[L + 1] * kWs[L + 1], splits = splits_for(L, B);
-  const int tiles = (CO / 16) * (npad(L) / 16);
-  hipLaunchKernelGGL((conv_bwd_weight_mfma<L>), dim3((tiles + 3) / 4, splits), dim3(256), 0, c->stream, c->dz[L + 1],
-                     c->act[L], P, kPixPerSplit[L], c->partial);
-  launch_sum<WgradSum<L>::template K>(splits, CO * npad(L), c->stream, (const float*)c->partial, splits,
-                                      c->G + c->o.w[L], c->G + c->o.b[L]);
+// Weight gradients, their sums with the FC gradients' and the loss's, and (lr > 0) Adam.
+hipError_t update(dpt_cnn* c, int B, float lr, float c1, float c2) {
+  size_t at[4];
+  partial_floats(B, at);
+  WgradIO w{};
+  UpdateIO u{};
+  int blocks = 0;
+  for (int l = 0; l < 4; ++l) {
+    w.act[l] = c->act[l], w.dz[l] = c->dz[l + 1], w.partial[l] = c->partial + at[l];
+    u.partial[l] = c->partial + at[l], u.slots[l] = wgrad_slots(l, B);
+    blocks += u.slots[l];
+  }
+  w.B = B;
+  hipLaunchKernelGGL(conv_bwd_weight, dim3(blocks), dim3(kFuseThreads), 0, c->stream, w);
+  u.fcg = c->fcg, u.sqerr = c->sqerr, u.B = B, u.G = c->G, u.loss = c->h_buf_dev;
+  u.P = c->P, u.M = c->M, u.V = c->V, u.Pb = c->Pb, u.PbT = c->PbT;
+  u.lr = lr, u.c1 = c1, u.c2 = c2;
+  hipLaunchKernelGGL(update_kernel, dim3((c->o.total + kOut + 15) / 16), dim3(256), 0, c->stream, u);
   return hipGetLastError();
-}
-
-hipError_t backward(dpt_cnn* c, int B) {
-  hipError_t e;
-  if ((e = bwd_layer<3>(c, B)) != hipSuccess) return e;
-  if ((e = bwd_layer<2>(c, B)) != hipSuccess) return e;
-  if ((e = bwd_layer<1>(c, B)) != hipSuccess) return e;
-  return bwd_layer<0>(c, B);
 }
 
 // The fused pass over B planar pairs (host or device), every layer's activations
@@ -758,16 +874,14 @@ int dpt_cnn_create(int32_t max_batch, void* hip_stream, dpt_cnn** out) {
     const size_t e = B * kHs[l] * kWs[l] * kC[l];
     ok = hipMalloc(&c->act[l], e * 2) == hipSuccess && hipMalloc(&c->dz[l], e * 4) == hipSuccess;
   }
-  size_t maxsplit = 0;
-  for (int l = 0; l < 4; ++l)
-    maxsplit = std::max(maxsplit, (size_t)splits_for(l, max_batch) * kC[l + 1] * npad(l));
-  c->partial_floats = maxsplit;
+  c->partial_floats = kMaxPartial;
   ok = ok && hipMalloc(&c->out, B * kOut * 4) == hipSuccess && hipMalloc(&c->tgt, B * kOut * 4) == hipSuccess &&
        hipMalloc(&c->sqerr, B * kOut * 4) == hipSuccess &&
        hipMalloc(&c->fcg, B * (size_t)(c->o.total - c->o.fw1) * 4) == hipSuccess &&
-       hipMalloc(&c->partial, c->partial_floats * 4) == hipSuccess && hipMalloc(&c->scal, 64) == hipSuccess &&
+       hipMalloc(&c->partial, c->partial_floats * 4) == hipSuccess &&
        hipMalloc(&c->pairs, B * 2 * kH0 * kW0) == hipSuccess && hipMalloc(&c->d_lv, 2 * B * sizeof(void*)) == hipSuccess &&
-       hipHostMalloc(&c->h_buf, std::max(n, B * kOut) * 4 + 64) == hipSuccess;
+       hipHostMalloc(&c->h_buf, std::max(n, B * kOut) * 4 + 64) == hipSuccess &&
+       hipHostGetDevicePointer((void**)&c->h_buf_dev, c->h_buf, 0) == hipSuccess;
   if (!ok) {
     (void)hipGetLastError();
     delete c;
@@ -867,20 +981,12 @@ int dpt_cnn_train_step(dpt_cnn* c, const uint8_t* pairs, const float* targets, i
   }
   int e = forward_pairs(c, pairs, B, on_device, tg);
   if (e != DPT_OK) return e;
-  const Offsets& o = c->o;
-  const int nfc = o.total - o.fw1;
-  launch_sum<BatchSum>(B, nfc, c->stream, (const float*)c->fcg, B, nfc, c->G + o.fw1);
-  launch_sum<BatchSum>(B, kOut, c->stream, (const float*)c->sqerr, B, (int)kOut, c->scal);
-  CNN_TRY(hipGetLastError());
-  CNN_TRY(backward(c, B));
+  float c1 = 1.f, c2 = 1.f;
   if (lr > 0.f) {
     c->step += 1;
-    const float c1 = 1.0f - std::pow(0.9f, (float)c->step), c2 = 1.0f - std::pow(0.999f, (float)c->step);
-    hipLaunchKernelGGL(adam_kernel, dim3((o.total + 255) / 256), dim3(256), 0, c->stream, c->P, c->G, c->M, c->V,
-                       o.total, lr, 0.9f, 0.999f, 1e-8f, c1, c2, o.fw1, c->Pb, c->PbT);
-    CNN_TRY(hipGetLastError());
+    c1 = 1.0f - std::pow(0.9f, (float)c->step), c2 = 1.0f - std::pow(0.999f, (float)c->step);
   }
-  CNN_TRY(hipMemcpyAsync(c->h_buf, c->scal, sizeof(float) * kOut, hipMemcpyDeviceToHost, c->stream));
+  CNN_TRY(update(c, B, lr, c1, c2));
   CNN_TRY(hipStreamSynchronize(c->stream));
   float s = 0.f;
   for (int q = 0; q < kOut; ++q) s += c->h_buf[q];
