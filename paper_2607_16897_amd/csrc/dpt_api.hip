@@ -2321,7 +2321,7 @@ int dpt_batch_set_reference_from_depth_all(dpt_batch* b, const int32_t* n_points
   HIP_TRY(b->pre_args.upload(wp, b->n, rs, &dp));
   HIP_TRY(launch_select_batch(ds, b->n, G_max, chunk, any_empty, rs));
   HIP_TRY(launch_backproject_batch(db, b->n, max_n, rs));
-  HIP_TRY(launch_precompute_batch(dp, b->n, max_samples, max_levels, rs));
+  HIP_TRY(launch_precompute_batch(dp, b->n, max_samples, b->ctx[0]->prm.n_pattern, max_levels, rs));
   if (b->ctx[0]->prm.flags & DPT_FLAG_FIXED_H) HIP_TRY(launch_fixed_h_batch(dp, b->n, max_n, max_levels, rs));
   for (int s = 0; s < b->n; ++s) {
     if (b->ctx[s]->n_points != n_points[s]) b->groups_dirty = true;

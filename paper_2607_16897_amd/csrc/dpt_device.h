@@ -2,6 +2,8 @@
 // workgroup reductions and the 6x6 solve with the SE(3) update.
 #pragma once
 
+#include <type_traits>
+
 #include "dpt_internal.h"
 
 namespace dpt {
@@ -93,22 +95,34 @@ __device__ __forceinline__ float sample_cell(const PIX* img, int W, int x, int y
   return bilin_mix(w, (float)p[0], (float)p[1], (float)p[W], (float)p[W + 1]);
 }
 
-// Reference-side gradient in the same cell: central differences / 2 at its
-// four corners, blended with the same weights.
+// Intensity in the cell with corner (x, y) as sample_cell, and the reference-side
+// gradient: central differences / 2 at its four corners, blended with the same
+// weights.  The 4 x 4 pixels around the cell, all inside the level, are read a
+// row at a time from any address.
 template <class PIX>
-__device__ __forceinline__ void gradient_cell(const PIX* img, int W, int x, int y, const Bilin& w, float& gx,
-                                              float& gy) {
-  const PIX* p = img + y * W + x;
-  const float gx00 = 0.5f * ((float)p[1] - (float)p[-1]);
-  const float gx10 = 0.5f * ((float)p[2] - (float)p[0]);
-  const float gx01 = 0.5f * ((float)p[W + 1] - (float)p[W - 1]);
-  const float gx11 = 0.5f * ((float)p[W + 2] - (float)p[W]);
-  const float gy00 = 0.5f * ((float)p[W] - (float)p[-W]);
-  const float gy10 = 0.5f * ((float)p[W + 1] - (float)p[1 - W]);
-  const float gy01 = 0.5f * ((float)p[2 * W] - (float)p[0]);
-  const float gy11 = 0.5f * ((float)p[2 * W + 1] - (float)p[1]);
-  gx = bilin_mix(w, gx00, gx10, gx01, gx11);
-  gy = bilin_mix(w, gy00, gy10, gy01, gy11);
+__device__ __forceinline__ void reference_cell(const PIX* img, int W, int x, int y, const Bilin& w, float& I0, float& gx,
+                                               float& gy) {
+  float r[4][4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const PIX* p = img + (y - 1 + j) * W + x - 1;
+    if constexpr (std::is_same<PIX, uint8_t>::value) {
+      struct __attribute__((packed)) Word {
+        uint32_t w;
+      };
+      const uint32_t v = ((const __attribute__((address_space(1))) Word*)p)->w;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) r[j][i] = (float)(v >> (8 * i) & 0xffu);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) r[j][i] = ((const __attribute__((address_space(1))) PIX*)p)[i];
+    }
+  }
+  I0 = bilin_mix(w, r[1][1], r[1][2], r[2][1], r[2][2]);
+  gx = bilin_mix(w, 0.5f * (r[1][2] - r[1][0]), 0.5f * (r[1][3] - r[1][1]), 0.5f * (r[2][2] - r[2][0]),
+                 0.5f * (r[2][3] - r[2][1]));
+  gy = bilin_mix(w, 0.5f * (r[2][1] - r[0][1]), 0.5f * (r[2][2] - r[0][2]), 0.5f * (r[3][1] - r[1][1]),
+                 0.5f * (r[3][2] - r[1][2]));
 }
 
 // ---------------------------------------------------------------- pyramid

@@ -328,7 +328,7 @@ hipError_t launch_select_noalloc(const uint8_t* img, int32_t W, int32_t H, int64
 hipError_t launch_precompute(const PrecomputeArgs& a, hipStream_t s);
 hipError_t launch_backproject(const BackprojectArgs& a, hipStream_t s);
 // Batched forms: one launch over n references / maps (argument arrays in device memory).
-hipError_t launch_precompute_batch(const PrecomputeArgs* d_args, int n_ref, int max_samples, int max_levels,
+hipError_t launch_precompute_batch(const PrecomputeArgs* d_args, int n_ref, int max_samples, int K, int max_levels,
                                    hipStream_t s);
 hipError_t launch_backproject_batch(const BackprojectArgs* d_args, int n_maps, int max_n, hipStream_t s);
 // Fixed-H mode: per-level H and its factor from a finished precompute (a.fixed, a.hpart set).

@@ -203,20 +203,34 @@ hipError_t launch_pyramid_gauss(const uint8_t* src, int64_t pitch, uint8_t* u8, 
 
 // ---------------------------------------------------------------- IC precompute (Eq.(6))
 
-// One lane per (point, pattern sample) and level: x0 = T_rw P, the point's
+// A thread per SPT pattern samples of a point and level: x0 = T_rw P, the point's
 // reference validity, the bilinear template intensity I0 and the interpolated
 // central-difference gradient.  The Jacobian itself is rebuilt in the track
 // from (gx, gy) and x0, so the cache holds 12 bytes per sample.
-__global__ __launch_bounds__(256) void precompute_kernel(PrecomputeArgs one, const PrecomputeArgs* __restrict__ many) {
-  const PrecomputeArgs& a = many ? many[blockIdx.z] : one;  // one reference, or reference blockIdx.z of a batch
+//
+// A small map is bound by the launch and its chain of latencies: one sample a
+// thread.  A large one (maps of a batch) by the transform and projection that a
+// point's threads repeat and by the image reads: four samples a thread, where
+// the pattern has a multiple of four, and a read per row of a cell's pixels
+// instead of one per pixel.  64 maps of 2000 8-pixel points, 4 levels: 50 us a
+// sample a thread, 43 so, 34 with a map to an XCD; a single map stays at 5.
+template <int SPT>
+__global__ __launch_bounds__(256) void precompute_kernel(PrecomputeArgs one, const PrecomputeArgs* __restrict__ many,
+                                                         int n_ref, int blocks, int levels) {
+  // Workgroup id goes to XCD id % 8: reference r's workgroups all have id % 8 =
+  // r % 8, so one XCD's L2 reads its levels, not all eight.
+  int blk = blockIdx.x, r = 0;
+  if (many) r = (int)(blk / 8 / (blocks * levels)) * 8 + (blk & 7), blk = blk / 8 % (blocks * levels);
+  if (r >= n_ref) return;
+  const PrecomputeArgs& a = many ? many[r] : one;
   const int K = a.pat.K;
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  const int l = blockIdx.y;
+  const int s = SPT * (int)(blk % blocks * blockDim.x + threadIdx.x);
+  const int l = blk / blocks;
   if (l >= a.levels) return;
   if (s >= a.n * K) return;
   const int i = s / K, k = s - i * K;
   float X, Y, Z;
-  transform(a.T_rw, a.P[3 * i], a.P[3 * i + 1], a.P[3 * i + 2], X, Y, Z);
+  transform(a.T_rw, gload(a.P + 3 * i), gload(a.P + 3 * i + 1), gload(a.P + 3 * i + 2), X, Y, Z);
   if (l == 0 && k == 0) a.x0[i] = make_float4(X, Y, Z, 0.0f);
   const LevelGeom g = a.lv[l];
   bool ok = Z > a.z_min;
@@ -226,43 +240,58 @@ __global__ __launch_bounds__(256) void precompute_kernel(PrecomputeArgs one, con
     ok = inside(g, a.pat, u, v);
   }
   if (k == 0) a.valid[(int64_t)l * a.cap + i] = ok ? 1 : 0;
-  float I0 = 0.f, gx = 0.f, gy = 0.f;
+  float I0[SPT] = {}, gx[SPT] = {}, gy[SPT] = {};
   if (ok) {  // sample k: the cell of the point's projection moved by the pattern offset
     const Cell q = cell_of(u, v);
-    const int x = q.iu + (int)a.pat.dx[k], y = q.iv + (int)a.pat.dy[k];
-    if (a.reff) {  // floating-point Gaussian pyramid
-      I0 = sample_cell(a.reff + g.off, g.W, x, y, q.w);
-      gradient_cell(a.reff + g.off, g.W, x, y, q.w, gx, gy);
-    } else {
-      I0 = sample_cell(a.ref + g.off, g.W, x, y, q.w);
-      gradient_cell(a.ref + g.off, g.W, x, y, q.w, gx, gy);
+#pragma unroll
+    for (int j = 0; j < SPT; ++j) {
+      const int x = q.iu + (int)a.pat.dx[k + j], y = q.iv + (int)a.pat.dy[k + j];
+      if (a.reff)  // floating-point Gaussian pyramid
+        reference_cell(a.reff + g.off, g.W, x, y, q.w, I0[j], gx[j], gy[j]);
+      else
+        reference_cell(a.ref + g.off, g.W, x, y, q.w, I0[j], gx[j], gy[j]);
     }
   }
   const int64_t o = (int64_t)l * a.cap * K + s;
-  a.I0[o] = I0;
-  a.gx[o] = gx;
-  a.gy[o] = gy;
-  if (a.I0h) {
-    a.I0h[o] = __float2half_rn(I0 - 128.0f);
-    a.gh[o] = __floats2half2_rn(gx, gy);
+  if constexpr (SPT == 4) {
+    *reinterpret_cast<float4*>(a.I0 + o) = make_float4(I0[0], I0[1], I0[2], I0[3]);
+    *reinterpret_cast<float4*>(a.gx + o) = make_float4(gx[0], gx[1], gx[2], gx[3]);
+    *reinterpret_cast<float4*>(a.gy + o) = make_float4(gy[0], gy[1], gy[2], gy[3]);
+  } else {
+    a.I0[o] = I0[0], a.gx[o] = gx[0], a.gy[o] = gy[0];
   }
+  if (a.I0h) {
+#pragma unroll
+    for (int j = 0; j < SPT; ++j) {
+      a.I0h[o + j] = __float2half_rn(I0[j] - 128.0f);
+      a.gh[o + j] = __floats2half2_rn(gx[j], gy[j]);
+    }
+  }
+}
+
+static hipError_t run_precompute(const PrecomputeArgs& one, const PrecomputeArgs* many, int n_ref, int max_samples,
+                                 int K, int max_levels, hipStream_t s) {
+  const int spt = K % 4 == 0 && (int64_t)n_ref * max_samples * max_levels >= 1 << 18 ? 4 : 1;
+  const int blocks = (max_samples / spt + 255) / 256;
+  const dim3 grid((many ? (n_ref + 7) / 8 * 8 : 1) * blocks * max_levels);
+  if (spt == 4)
+    hipLaunchKernelGGL(precompute_kernel<4>, grid, dim3(256), 0, s, one, many, n_ref, blocks, max_levels);
+  else
+    hipLaunchKernelGGL(precompute_kernel<1>, grid, dim3(256), 0, s, one, many, n_ref, blocks, max_levels);
+  return hipGetLastError();
 }
 
 hipError_t launch_precompute(const PrecomputeArgs& a, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
-  dim3 grid((a.n * a.pat.K + 255) / 256, a.levels);
-  hipLaunchKernelGGL(precompute_kernel, grid, dim3(256), 0, s, a, (const PrecomputeArgs*)nullptr);
-  return hipGetLastError();
+  return run_precompute(a, nullptr, 1, a.n * a.pat.K, a.pat.K, a.levels, s);
 }
 
-hipError_t launch_precompute_batch(const PrecomputeArgs* d_args, int n_ref, int max_samples, int max_levels,
+hipError_t launch_precompute_batch(const PrecomputeArgs* d_args, int n_ref, int max_samples, int K, int max_levels,
                                    hipStream_t s) {
   if (n_ref == 0 || max_samples == 0) return hipSuccess;
   PrecomputeArgs none;
   std::memset(&none, 0, sizeof none);
-  dim3 grid((max_samples + 255) / 256, max_levels, n_ref);
-  hipLaunchKernelGGL(precompute_kernel, grid, dim3(256), 0, s, none, d_args);
-  return hipGetLastError();
+  return run_precompute(none, d_args, n_ref, max_samples, K, max_levels, s);
 }
 
 // ---------------------------------------------------------------- fixed-H mode (Sec. IV-C)
