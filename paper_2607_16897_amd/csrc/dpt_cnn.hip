@@ -42,10 +42,17 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
   u += 0x7fffu + ((u >> 16) & 1u);  // round to nearest even
   return (uint16_t)(u >> 16);
 }
+// The same of two floats (v_cvt_pk_bf16_f32).
+__device__ __forceinline__ uint32_t f2bf_pair(float lo, float hi) {
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{lo, hi}, b2));
+}
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 __device__ __forceinline__ short4_t bf16x4(uint2 v) {
-  return short4_t{(short)(v.x & 0xffff), (short)(v.x >> 16), (short)(v.y & 0xffff), (short)(v.y >> 16)};
+  typedef uint32_t words __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(short4_t, words{v.x, v.y});
 }
 
 // ---------------------------------------------------------------- layout
@@ -79,15 +86,26 @@ __host__ __device__ inline Offsets offsets() {
 // The BF16 convolution weights, in the layouts the kernels stage in LDS: layer l
 // forward as [co][tap][ci], rows of kWRow[l] elements, and (l >= 1) for the data
 // gradient as [tap][ci][co], rows of kTRow[l].  Sixteen lanes read 8 bytes each
-// from sixteen consecutive rows, four lane groups 8 bytes apart; a row of an odd
-// multiple of 32 bytes spreads them over all banks (rows of 576 or 1152 bytes
-// put eight or sixteen lanes on the same ones), so rows are padded to that.  The
-// same holds for the activations' pixels, two apart in the forward convolutions
-// (kXRow, layers' inputs) and adjacent in the data gradient (kDRow).
-constexpr int kWRow[4] = {18, 144, 304, 592};
-constexpr int kTRow[4] = {0, 48, 80, 80};
-constexpr int kXRow[4] = {2, 24, 40, 72};
-constexpr int kDRow[5] = {0, 0, 48, 80, 80};
+// from sixteen consecutive rows, four lane groups 8 bytes apart; rows an odd
+// multiple of 16 bytes apart spread a half wave over all banks (rows of 576 or
+// 1152 bytes put eight or sixteen lanes on the same ones), so rows are padded to
+// that.  The same holds for the activations' pixels, two apart in the forward
+// convolutions (kXRow, layers' inputs: an odd multiple of 8) and adjacent in the
+// data gradient (kDRow).
+constexpr int kWRow[4] = {18, 152, 296, 584};
+constexpr int kTRow[4] = {0, 40, 72, 72};
+constexpr int kXRow[4] = {2, 20, 36, 68};
+constexpr int kDRow[5] = {0, 0, 40, 72, 72};
+// Activations and gradients lie in LDS with the zero pixels the convolutions pad
+// with, so that every tap is at a fixed distance: inputs of layer l + 1 from row
+// and column -1 to 2 Ho - 1 and 2 Wo - 1, gradients with a row and column past the
+// last.
+constexpr int xrows(int l) { return 2 * kHs[l + 1] + 1; }
+constexpr int xcols(int l) { return 2 * kWs[l + 1] + 1; }
+constexpr int xbytes(int l) { return (2 * xrows(l) * xcols(l) * kXRow[l] + 15) / 16 * 16; }
+constexpr int drows(int l) { return kHs[l] + 1; }
+constexpr int dcols(int l) { return kWs[l] + 1; }
+constexpr int dbytes(int l) { return (2 * drows(l) * dcols(l) * kDRow[l] + 15) / 16 * 16; }
 __host__ __device__ constexpr int wrow_off(int l) { return l == 0 ? 0 : wrow_off(l - 1) + kC[l] * kWRow[l - 1]; }
 __host__ __device__ constexpr int trow_off(int l) { return l <= 1 ? 0 : trow_off(l - 1) + 9 * kC[l - 1] * kTRow[l - 1]; }
 constexpr int kPbTotal = wrow_off(4), kPbTTotal = trow_off(4);
@@ -122,60 +140,115 @@ __device__ __forceinline__ void propose_twist(const float* o6, double* rel) {
 
 // ---------------------------------------------------------------- forward convolutions (fused, MFMA)
 
-// Layer L + 1 of one sample inside a workgroup, as an implicit GEMM: rows m =
-// output pixels (i, j), columns n = output channels, k = (ky, kx, ci), stride
-// 2 and one pixel of zero padding; BF16 operands, FP32 accumulation, then bias
-// and ReLU, BF16 out (pixels YS elements apart).  The sample's activations and
-// the layer's weights are in LDS; the waves take the (16-row tile, 16-channel
-// tile) pairs in turn.  Lane l supplies A[m0 + l%16][k0 + 4(l/16) .. +3] and
-// B[k0 + 4(l/16) .. +3][n0 + l%16] and receives D[4(l/16) + j][l%16].
-template <int L, int YS>
+constexpr int kFuseThreads = 1024;
+
+// Zero the border pixels of a layer's input (rows and columns outside the image)
+// or of a gradient (past the last row and column).
+template <int ROWS, int COLS, int S, int R0, int R1, int C0, int C1>
+__device__ __forceinline__ void zero_border(uint16_t* __restrict__ x) {  // inside: rows R0 .. R1 - 1, columns C0 .. C1 - 1
+  constexpr int TOP = R0 * COLS, BOT = (ROWS - R1) * COLS, SIDE = C0 + COLS - C1, N = TOP + BOT + ROWS * SIDE;
+#pragma unroll
+  for (int k = (int)threadIdx.x; k < N; k += kFuseThreads) {
+    int p = k < TOP ? k : R1 * COLS + k - TOP;
+    if (k >= TOP + BOT) {
+      const int r = (k - TOP - BOT) / SIDE, c = (k - TOP - BOT) % SIDE;
+      p = r * COLS + (c < C0 ? c : C1 + c - C0);
+    }
+#pragma unroll
+    for (int c = 0; c < S; c += 2) *reinterpret_cast<uint32_t*>(x + p * S + c) = 0u;
+  }
+}
+template <int L>
+__device__ __forceinline__ void zero_input_border(uint16_t* x) {
+  zero_border<xrows(L), xcols(L), kXRow[L], 1, kHs[L] + 1, 1, kWs[L] + 1>(x);
+}
+template <int L>
+__device__ __forceinline__ void zero_grad_border(uint16_t* d) {
+  zero_border<drows(L), dcols(L), kDRow[L], 0, kHs[L], 0, kWs[L]>(d);
+}
+
+// Layer L + 1 of one sample inside a workgroup, as an implicit GEMM: rows n =
+// output channels, columns m = output pixels (i, j), k = (ky, kx, ci), stride 2
+// and one pixel of zero padding; BF16 operands, FP32 accumulation, then bias and
+// ReLU, BF16 out: into the padded input of the layer after (L < 3) or dense.  The
+// sample's activations and the layer's weights are in LDS; the waves take the
+// (16-channel tile, 16-pixel tile) pairs in turn, a wave always the same channels,
+// whose weights it keeps where they fit.  Lane l supplies A[n0 + l%16][k0 +
+// 4(l/16) .. +3] and B[k0 + 4(l/16) .. +3][m0 + l%16] and receives D[4(l/16) +
+// j][l%16]: four channels of one pixel, stored as one word pair; columns past the
+// last repeat pixel 0 and are not stored.
+//
+// Vector instructions take four cycles each and four waves share a SIMD, so what
+// surrounds a product is a layer's time: taps lie at fixed distances (no bounds
+// checks or selects, nineteen instructions a step before), and a lane's results
+// share one address (eleven instructions a value with pixels as rows).  The reads
+// of nine steps are in flight together.
+template <int L>
 __device__ __forceinline__ void conv_sample(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
                                             const float* __restrict__ bias, uint16_t* __restrict__ y) {
-  constexpr int CI = kC[L], CO = kC[L + 1], H = kHs[L], W = kWs[L], Ho = kHs[L + 1], Wo = kWs[L + 1];
+  constexpr int CI = kC[L], CO = kC[L + 1], Ho = kHs[L + 1], Wo = kWs[L + 1];
   constexpr int XS = kXRow[L], WS = kWRow[L], K = 9 * CI, NT = CO / 16, M = Ho * Wo, ITEMS = (M + 15) / 16 * NT;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6, kq = lane >> 4;
-  for (int it = wave; it < ITEMS; it += nw) {
-    const int m0 = it / NT * 16, n = it % NT * 16 + (lane & 15);
-    const int m = m0 + (lane & 15);
-    const bool mvalid = m < M;
-    const int i = mvalid ? m / Wo : 0, j = mvalid ? m % Wo : 0;
-    const float bn = bias[n];
+  constexpr int NW = kFuseThreads / 64;
+  static_assert(NW % NT == 0, "a wave keeps its channels");
+  const int lane = threadIdx.x & 63, kq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int n = wave % NT * 16 + (lane & 15), no = wave % NT * 16 + 4 * kq;  // of the operand, of the results
+  const float4 bn = *reinterpret_cast<const float4*>(bias + no);
+  constexpr int STEPS = (K + 15) / 16;
+  constexpr bool KEEP = STEPS <= 18;  // the wave's weights in registers
+  uint2 u[KEEP ? STEPS : 1];
+  int tap2[CI == 2 ? 2 * STEPS : 1];  // two channels: a lane's four k are two taps, a word of both channels each
+  if constexpr (CI == 2) {
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k) {
+      uint32_t h[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int tap = 8 * k + 2 * kq + e;
+        h[e] = *reinterpret_cast<const uint32_t*>(w + n * WS + (tap < 9 ? 2 * tap : 0));
+        h[e] = tap < 9 ? h[e] : 0u;
+        tap2[2 * k + e] = tap < 9 ? (tap / 3 * xcols(L) + tap % 3) * XS : 0;
+      }
+      u[k] = make_uint2(h[0], h[1]);
+    }
+  } else if constexpr (KEEP) {
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k) u[k] = *reinterpret_cast<const uint2*>(w + n * WS + 16 * k + 4 * kq);
+  }
+  for (int it = wave; it < ITEMS; it += NW) {
+    const int m = it / NT * 16 + (lane & 15), mi = m < M ? m : 0, i = mi / Wo, j = mi - i * Wo;
+    const uint16_t* xp = x + (2 * i * xcols(L) + 2 * j) * XS + (CI == 2 ? 0 : 4 * kq);
     float4_t acc = float4_t{0.f, 0.f, 0.f, 0.f};
-    if constexpr (CI % 16 == 0) {
+    constexpr int G = STEPS < 9 ? STEPS : 9;
+    static_assert(STEPS % G == 0, "whole batches");
 #pragma unroll
-      for (int ks = 0; ks < K / 16; ++ks) {
-        const int tap = ks * 16 / CI, c = ks * 16 % CI + 4 * kq;  // one tap per step
-        const int yy = 2 * i + tap / 3 - 1, xx = 2 * j + tap % 3 - 1;
-        const bool ok = mvalid & (yy >= 0) & (yy < H) & (xx >= 0) & (xx < W);
-        uint2 v = *reinterpret_cast<const uint2*>(x + (ok ? (yy * W + xx) * XS : 0) + c);
-        if (!ok) v = make_uint2(0u, 0u);
-        const uint2 u = *reinterpret_cast<const uint2*>(w + n * WS + ks * 16 + 4 * kq);
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(bf16x4(v), bf16x4(u), acc, 0, 0, 0);
-      }
-    } else {  // two channels: a lane's four k are two taps, a word of both channels each
-      static_assert(CI == 2 || CI % 16 == 0, "two channels or whole steps per tap");
+    for (int k0 = 0; k0 < STEPS; k0 += G) {
+      uint2 v[G], uk[G];
 #pragma unroll
-      for (int ks = 0; ks < (K + 15) / 16; ++ks) {
-        uint32_t v[2], u[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int tap = 8 * ks + 2 * kq + h, ky = tap / 3, kx = tap - 3 * ky;
-          const int yy = 2 * i + ky - 1, xx = 2 * j + kx - 1;
-          const bool in = tap < 9, ok = in & mvalid & (yy >= 0) & (yy < H) & (xx >= 0) & (xx < W);
-          v[h] = *reinterpret_cast<const uint32_t*>(x + (ok ? (yy * W + xx) * 2 : 0));
-          u[h] = *reinterpret_cast<const uint32_t*>(w + n * WS + (in ? 2 * tap : 0));
-          v[h] = ok ? v[h] : 0u, u[h] = in ? u[h] : 0u;
+      for (int g = 0; g < G; ++g) {
+        const int k = k0 + g;
+        if constexpr (CI == 2) {
+          v[g] = make_uint2(*reinterpret_cast<const uint32_t*>(xp + tap2[2 * k]),
+                            *reinterpret_cast<const uint32_t*>(xp + tap2[2 * k + 1]));
+        } else {
+          static_assert(CI == 2 || CI % 16 == 0, "one tap per step");
+          const int tap = 16 * k / CI;
+          v[g] = *reinterpret_cast<const uint2*>(xp + (tap / 3 * xcols(L) + tap % 3) * XS + 16 * k % CI);
         }
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(bf16x4(make_uint2(v[0], v[1])), bf16x4(make_uint2(u[0], u[1])),
-                                                         acc, 0, 0, 0);
+        if constexpr (!KEEP) uk[g] = *reinterpret_cast<const uint2*>(w + n * WS + 16 * k + 4 * kq);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        if constexpr (KEEP) uk[g] = u[k0 + g];
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(bf16x4(uk[g]), bf16x4(v[g]), acc, 0, 0, 0);
       }
     }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int mo = m0 + 4 * kq + q;
-      if (mo < M) y[mo * YS + n] = f2bf(fmaxf(acc[q] + bn, 0.0f));
-    }
+    int at = mi * CO;
+    if constexpr (L < 3) at = ((i + 1) * xcols(L < 3 ? L + 1 : 0) + j + 1) * kXRow[L < 3 ? L + 1 : 0];
+    if (m < M)
+      *reinterpret_cast<uint2*>(y + at + no) = make_uint2(f2bf_pair(fmaxf(acc[0] + bn.x, 0.0f), fmaxf(acc[1] + bn.y, 0.0f)),
+                                                          f2bf_pair(fmaxf(acc[2] + bn.z, 0.0f), fmaxf(acc[3] + bn.w, 0.0f)));
   }
 }
 
@@ -184,78 +257,74 @@ __device__ __forceinline__ void conv_sample(const uint16_t* __restrict__ x, cons
 // and channels o of W[o][ky][kx][c] dZ[i][j][o], where 2i + ky - 1 = y and 2j +
 // kx - 1 = x.  Stride 2 makes the reaching taps depend only on the parities of
 // (y, x): an even row is reached by ky = 1 alone, an odd one by ky = 0 and 2
-// (columns likewise), so the rows of the implicit GEMM are the input pixels of
-// one parity class and k = (reaching tap, o).  dZ and the weights ([tap][ci][co])
-// are in LDS; the waves take (class, 16 pixels, 16 channels) in turn, the classes
+// (columns likewise), so the pixels of the implicit GEMM are those of one
+// parity class and k = (reaching tap, o); columns are pixels as in conv_sample.
+// dZ and the weights ([tap][ci][co]) are in LDS; the waves take (class, 16 pixels, 16 channels) in turn, the classes
 // of most taps first.  out: dZprev in LDS for the next layer, or null; gout: dense.
 template <int L>
 __device__ __forceinline__ void conv_bwd_sample(const uint16_t* __restrict__ dz, const uint16_t* __restrict__ wT,
                                                 const uint16_t* __restrict__ aprev, uint16_t* __restrict__ out,
                                                 uint16_t* __restrict__ gout) {
-  constexpr int CI = kC[L], CO = kC[L + 1], H = kHs[L], W = kWs[L], Ho = kHs[L + 1], Wo = kWs[L + 1];
+  constexpr int CI = kC[L], CO = kC[L + 1], H = kHs[L], W = kWs[L];
   constexpr int NT = CI / 16, DS = kDRow[L + 1], WS = kTRow[L], OS = kDRow[L];
   static_assert(CI % 16 == 0 && CO % 16 == 0, "16-channel tiles");
-  const int lane = threadIdx.x & 63, q = lane >> 4, nw = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, q = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const auto tiles = [](int cls) {
     return (((H - (cls >> 1) + 1) / 2) * ((W - (cls & 1) + 1) / 2) + 15) / 16 * NT;
   };
   const int items = tiles(0) + tiles(1) + tiles(2) + tiles(3);
-  for (int it = wave; it < items; it += nw) {
+  for (int it = wave; it < items; it += kFuseThreads / 64) {
     int cls = 3, r0 = it;
     while (r0 >= tiles(cls)) r0 -= tiles(cls--);
     const int py = cls >> 1, px = cls & 1, Hc = (H - py + 1) / 2, Wc = (W - px + 1) / 2, M = Hc * Wc;
-    const int m0 = r0 / NT * 16, n = r0 % NT * 16 + (lane & 15);
-    const int m = m0 + (lane & 15);
-    const bool mvalid = m < M;
-    const int r = mvalid ? m : 0, y = 2 * (r / Wc) + py, x = 2 * (r % Wc) + px;
-    // the mask at the lane's four results D[4q + jq][lane % 16]
-    uint16_t mask[4];
-    int at[4];
-#pragma unroll
-    for (int jq = 0; jq < 4; ++jq) {
-      const int mo = min(m0 + 4 * q + jq, M - 1);
-      at[jq] = (2 * (mo / Wc) + py) * W + 2 * (mo % Wc) + px;
-      mask[jq] = aprev[at[jq] * CI + n];
-    }
+    const int m = r0 / NT * 16 + (lane & 15), n = r0 % NT * 16 + (lane & 15), no = r0 % NT * 16 + 4 * q;
+    const int r = m < M ? m : 0, i = r / Wc, j = r - i * Wc, y = 2 * i + py, x = 2 * j + px;
+    const uint2 mask = *reinterpret_cast<const uint2*>(aprev + (y * W + x) * CI + no);  // at the lane's four results
     float4_t acc = float4_t{0.f, 0.f, 0.f, 0.f};
+    // tap (ky, kx) is reached from pixel ((y + 1 - ky) / 2, (x + 1 - kx) / 2), at
+    // most a row or column past the last
+    constexpr int S = CO / 16;
+    const uint16_t* drow = dz + (i * dcols(L + 1) + j) * DS + 4 * q;
+    const uint16_t* wcol = wT + n * WS + 4 * q;
     for (int ta = 0; ta < (py ? 2 : 1); ++ta)
       for (int tb = 0; tb < (px ? 2 : 1); ++tb) {
-        const int ky = py ? 2 * ta : 1, kx = px ? 2 * tb : 1, tap = ky * 3 + kx;
-        const int i = (y + 1 - ky) >> 1, j = (x + 1 - kx) >> 1;  // y + 1 - ky >= 0 and even
-        const bool ok = mvalid & (i < Ho) & (j < Wo);
-        const uint16_t* drow = dz + (ok ? (i * Wo + j) * DS : 0) + 4 * q;
-        const uint16_t* wrow = wT + (tap * CI + n) * WS + 4 * q;
+        const int ky = py ? 2 * ta : 1, kx = px ? 2 * tb : 1;
+        const uint16_t* d = drow + ((py & (ta == 0)) * dcols(L + 1) + (px & (tb == 0))) * DS;
+        const uint16_t* w = wcol + (ky * 3 + kx) * CI * WS;
 #pragma unroll
-        for (int o0 = 0; o0 < CO; o0 += 16) {
-          uint2 dv = *reinterpret_cast<const uint2*>(drow + o0);
-          if (!ok) dv = make_uint2(0u, 0u);
-          acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(bf16x4(dv), bf16x4(*reinterpret_cast<const uint2*>(wrow + o0)),
-                                                           acc, 0, 0, 0);
-        }
+        for (int o = 0; o < S; ++o)
+          acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(bf16x4(*reinterpret_cast<const uint2*>(w + 16 * o)),
+                                                           bf16x4(*reinterpret_cast<const uint2*>(d + 16 * o)), acc, 0, 0, 0);
       }
-#pragma unroll
-    for (int jq = 0; jq < 4; ++jq) {
-      if (m0 + 4 * q + jq >= M) continue;
-      const uint16_t v = bf2f(mask[jq]) > 0.f ? f2bf(acc[jq]) : (uint16_t)0;
-      if (out) out[at[jq] * OS + n] = v;
-      gout[(size_t)at[jq] * CI + n] = v;
+    // ReLU outputs are >= 0: kept where any bit but the sign is set
+    const auto keep = [](uint32_t v, uint32_t a) {
+      return (a & 0x7fffu ? v & 0xffffu : 0u) | (a & 0x7fff0000u ? v & 0xffff0000u : 0u);
+    };
+    const uint2 v = make_uint2(keep(f2bf_pair(acc[0], acc[1]), mask.x), keep(f2bf_pair(acc[2], acc[3]), mask.y));
+    if (m < M) {
+      if (out) *reinterpret_cast<uint2*>(out + (y * dcols(L) + x) * OS + no) = v;
+      *reinterpret_cast<uint2*>(gout + (size_t)(y * W + x) * CI + no) = v;
     }
   }
 }
 
-// A layer's BF16 weights ([co][tap][ci], `bytes` a multiple of 16 from a
+// A layer's BF16 weights ([co][tap][ci], BYTES a multiple of 16 from a
 // 16-byte aligned source) copied into LDS by the workgroup, global memory
 // straight into LDS; the caller waits (s_waitcnt 0, then a barrier).
-__device__ __forceinline__ void stage_weights(const uint16_t* __restrict__ src, int bytes, uint16_t* lds) {
-  const int lane = threadIdx.x & 63, ng = bytes >> 4;
-  for (int q0 = (int)(threadIdx.x & ~63u); q0 < ng; q0 += blockDim.x)
-    if (q0 + lane < ng)
+template <int BYTES>
+__device__ __forceinline__ void stage_weights(const uint16_t* __restrict__ src, uint16_t* lds) {
+  constexpr int NG = BYTES / 16;
+  static_assert(BYTES % 16 == 0, "whole granules");
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+#pragma unroll
+  for (int q = 0; q < NG; q += kFuseThreads) {
+    const int q0 = q + 64 * wave;
+    if (q0 + lane < NG)
       __builtin_amdgcn_global_load_lds(reinterpret_cast<const uint32_t*>(src) + 4 * (q0 + lane),
                                        (__attribute__((address_space(3))) void*)(lds + 8 * q0), 16, 0, 0);
+  }
 }
-
-constexpr int kFuseThreads = 1024;
 
 // Where the fused pass reads and writes: the input pairs as per-sample level
 // pointers (refs, curs) or planar [B][2][60][94] bytes (pairs); act[l]
@@ -276,12 +345,30 @@ struct FusedIO {
   int B;
 };
 
-// n BF16 values (a multiple of 8) of C channels a pixel from LDS (pixels S
-// elements apart) to global memory, 16 bytes a thread.
-template <int C, int S>
-__device__ __forceinline__ void store_act(const uint16_t* __restrict__ src, uint16_t* __restrict__ dst, int n) {
-  for (int e = 8 * (int)threadIdx.x; e < n; e += 8 * (int)blockDim.x)
-    *reinterpret_cast<uint4*>(dst + e) = *reinterpret_cast<const uint4*>(src + (C == S ? e : e / C * S + e % C));
+// The N BF16 activations of layer L (a padded input) or 4 (dense) from LDS to
+// global memory, 16 bytes a thread.
+template <int L, int N>
+__device__ __forceinline__ void store_act(const uint16_t* __restrict__ src, uint16_t* __restrict__ dst) {
+  constexpr int C = kC[L];
+  static_assert(N % 8 == 0, "16-byte copies");
+#pragma unroll
+  for (int e = 8 * (int)threadIdx.x; e < N; e += 8 * kFuseThreads) {
+    uint2 v[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k = e + 4 * h, p = k / C, y = p / kWs[L], x = p % kWs[L];
+      if constexpr (C == 2) {  // two pixels
+        const int x2 = (p + 1) % kWs[L], y2 = (p + 1) / kWs[L];
+        v[h] = make_uint2(*reinterpret_cast<const uint32_t*>(src + ((y + 1) * xcols(0) + x + 1) * 2),
+                          *reinterpret_cast<const uint32_t*>(src + ((y2 + 1) * xcols(0) + x2 + 1) * 2));
+      } else if constexpr (L < 4) {
+        v[h] = *reinterpret_cast<const uint2*>(src + ((y + 1) * xcols(L < 4 ? L : 0) + x + 1) * kXRow[L < 4 ? L : 0] + k % C);
+      } else {
+        v[h] = *reinterpret_cast<const uint2*>(src + k);
+      }
+    }
+    *reinterpret_cast<uint4*>(dst + e) = make_uint4(v[0].x, v[0].y, v[1].x, v[1].y);
+  }
 }
 
 // LDS of the fused pass in bytes.  What a step reads and what is being staged for
@@ -293,23 +380,20 @@ __device__ __forceinline__ void store_act(const uint16_t* __restrict__ src, uint
 //   backward: D4, D3 (gradients) and T2 from the start, T3 over C3 and W4;
 //             D2 and T1 over T3
 struct FuseLds {
-  static constexpr int kA = 0, kW3 = kA + 2 * kHs[2] * kWs[2] * kXRow[2], kB = kW3 + 2 * kC[3] * kWRow[2],
-                       kW2 = kB + 2 * kHs[1] * kWs[1] * kXRow[1], kW1 = kW2 + 2 * kC[2] * kWRow[1],
-                       kFwdEnd = kW1 + 2 * kC[1] * kWRow[0];
-  static constexpr int kC3 = kB, kW4 = kC3 + 2 * kHs[3] * kWs[3] * kXRow[3], kEnd4 = kW4 + 2 * kC[4] * kWRow[3];
+  static constexpr int kA = 0, kW3 = xbytes(2) > xbytes(0) ? xbytes(2) : xbytes(0), kB = kW3 + 2 * kC[3] * kWRow[2],
+                       kW2 = kB + xbytes(1), kW1 = kW2 + 2 * kC[2] * kWRow[1], kFwdEnd = kW1 + 2 * kC[1] * kWRow[0];
+  static constexpr int kC3 = kB, kW4 = kC3 + xbytes(3), kEnd4 = kW4 + 2 * kC[4] * kWRow[3];
   static constexpr int kHead = kW3, kHeadEnd = kHead + 4 * (64 * 65 + kOut * kHidden);
-  static constexpr int kD4 = 2 * kHs[4] * kWs[4] * kC[4], kD3 = kD4 + 2 * kHs[4] * kWs[4] * kDRow[4],
-                       kT2 = kD3 + 2 * kHs[3] * kWs[3] * kDRow[3], kT3 = kT2 + 2 * 9 * kC[2] * kTRow[2],
-                       kEndT3 = kT3 + 2 * 9 * kC[3] * kTRow[3];
-  static constexpr int kD2 = kT3, kT1 = kD2 + 2 * kHs[2] * kWs[2] * kDRow[2], kEndT1 = kT1 + 2 * 9 * kC[1] * kTRow[1];
+  static constexpr int kD4 = 2 * kHs[4] * kWs[4] * kC[4], kD3 = kD4 + dbytes(4), kT2 = kD3 + dbytes(3),
+                       kT3 = kT2 + 2 * 9 * kC[2] * kTRow[2], kEndT3 = kT3 + 2 * 9 * kC[3] * kTRow[3];
+  static constexpr int kD2 = kT3, kT1 = kD2 + dbytes(2), kEndT1 = kT1 + 2 * 9 * kC[1] * kTRow[1];
   static constexpr int kFwd = kFwdEnd > kEnd4 ? kFwdEnd : kEnd4, kBwd = kEndT3 > kEndT1 ? kEndT3 : kEndT1;
   static constexpr int kBytes = kFwd > kBwd ? kFwd : kBwd;
 };
-static_assert(2 * kH0 * kW0 * 2 <= FuseLds::kW3 && FuseLds::kHeadEnd <= FuseLds::kB && FuseLds::kD3 <= FuseLds::kHead &&
-                  FuseLds::kT3 >= FuseLds::kHeadEnd && FuseLds::kT3 >= FuseLds::kC3 && FuseLds::kBytes <= 161 * 1024 &&
-                  FuseLds::kW3 % 16 == 0 && FuseLds::kB % 16 == 0 && FuseLds::kW2 % 16 == 0 && FuseLds::kW1 % 16 == 0 &&
-                  FuseLds::kW4 % 16 == 0 && FuseLds::kD4 % 16 == 0 && FuseLds::kD3 % 16 == 0 && FuseLds::kT2 % 16 == 0 &&
-                  FuseLds::kT3 % 16 == 0 && FuseLds::kT1 % 16 == 0,
+static_assert(FuseLds::kHeadEnd <= FuseLds::kB && FuseLds::kT2 <= FuseLds::kHead && FuseLds::kT3 >= FuseLds::kHeadEnd &&
+                  FuseLds::kBytes <= 160 * 1024 - 3072 && FuseLds::kW3 % 16 == 0 && FuseLds::kB % 16 == 0 &&
+                  FuseLds::kW2 % 16 == 0 && FuseLds::kW1 % 16 == 0 && FuseLds::kW4 % 16 == 0 && FuseLds::kD4 % 16 == 0 &&
+                  FuseLds::kD3 % 16 == 0 && FuseLds::kT2 % 16 == 0 && FuseLds::kT3 % 16 == 0 && FuseLds::kT1 % 16 == 0,
               "the regions follow the layer shapes");
 
 // Sample blockIdx.x in one workgroup: the input, the four convolutions and the
@@ -319,20 +403,20 @@ static_assert(2 * kH0 * kW0 * 2 <= FuseLds::kW3 && FuseLds::kHeadEnd <= FuseLds:
 // + fb1), out = fw2 h1 + fb2).  The steps are short and depend on each other, so
 // latency bounds them: each layer's weights are on their way while the layer
 // before is computed, and 1024 threads share a layer's tiles.  64 pairs with the
-// proposal: 27 us with unpadded rows and each layer's weights waited for, now
-// 18.4; the training pass of 256 pairs: 97 us as five launches, now 51.5.
+// proposal: 27 us with unpadded rows and each layer's weights waited for, now 16.2;
+// the training pass of 256 pairs: 97 us as five launches, 51.5 in one, now 39.
 template <bool TRAIN>
 __global__ __launch_bounds__(kFuseThreads) void conv_net_fused(FusedIO io, const uint16_t* __restrict__ Pb,
                                                                const uint16_t* __restrict__ PbT,
                                                                const float* __restrict__ P) {
   using R = FuseLds;
   __shared__ __align__(16) uint8_t lds[R::kBytes];
+  __shared__ __align__(16) float sh_bias[kC[1] + kC[2] + kC[3] + kC[4]];
   __shared__ float sh_g[64], sh_h1[64], sh_out[kOut], sh_dout[kOut], sh_dz1[64];
   __shared__ uint16_t sh_dg[64];
   const auto at = [&](int o) { return reinterpret_cast<uint16_t*>(lds + o); };
   constexpr int N0 = kH0 * kW0 * 2, N1 = kHs[1] * kWs[1] * kC[1], N2 = kHs[2] * kWs[2] * kC[2],
                 N3 = kHs[3] * kWs[3] * kC[3], N4 = kHs[4] * kWs[4] * kC[4], HW = kHs[4] * kWs[4];
-  static_assert(N0 % 8 == 0 && N1 % 8 == 0 && N2 % 8 == 0 && N3 % 8 == 0 && N4 % 8 == 0, "16-byte copies");
   const int b = blockIdx.x, t = threadIdx.x;
   const Offsets o = offsets();
   const uint8_t* ref = io.pairs ? io.pairs + (size_t)(2 * b) * kH0 * kW0 : io.refs[b];
@@ -344,26 +428,38 @@ __global__ __launch_bounds__(kFuseThreads) void conv_net_fused(FusedIO io, const
     const int r = min(t + k * kFuseThreads, kH0 * kW0 - 1);
     pr[k] = gload(ref + r), pc[k] = gload(cur + r);
   }
-  stage_weights(Pb + wrow_off(0), kC[1] * kWRow[0] * 2, at(R::kW1));
-  stage_weights(Pb + wrow_off(1), kC[2] * kWRow[1] * 2, at(R::kW2));
-  stage_weights(Pb + wrow_off(2), kC[3] * kWRow[2] * 2, at(R::kW3));
+  // the biases too: a read of global memory inside a layer would wait for the
+  // weights being staged
+  constexpr int B1 = kC[1], B2 = B1 + kC[2], B3 = B2 + kC[3], B4 = B3 + kC[4];
+  const float bias = t < B4 ? gload(P + (t < B1 ? o.b[0] + t : t < B2 ? o.b[1] + t - B1 : t < B3 ? o.b[2] + t - B2
+                                                                                              : o.b[3] + t - B3))
+                            : 0.f;
+  stage_weights<kC[1] * kWRow[0] * 2>(Pb + wrow_off(0), at(R::kW1));
+  stage_weights<kC[2] * kWRow[1] * 2>(Pb + wrow_off(1), at(R::kW2));
+  stage_weights<kC[3] * kWRow[2] * 2>(Pb + wrow_off(2), at(R::kW3));
 #pragma unroll
   for (int k = 0; k < PX; ++k) {  // (I - 128) / 64, exact in BF16
     const int r = t + k * kFuseThreads;
-    const uint32_t v = f2bf(((float)pr[k] - 128.0f) * (1.0f / 64.0f)), w = f2bf(((float)pc[k] - 128.0f) * (1.0f / 64.0f));
-    if (r < kH0 * kW0) *reinterpret_cast<uint32_t*>(at(R::kA) + 2 * r) = v | w << 16;
+    if (r < kH0 * kW0)
+      *reinterpret_cast<uint32_t*>(at(R::kA) + 2 * ((r / kW0 + 1) * xcols(0) + r % kW0 + 1)) =
+          f2bf_pair(((float)pr[k] - 128.0f) * (1.0f / 64.0f), ((float)pc[k] - 128.0f) * (1.0f / 64.0f));
   }
+  zero_input_border<0>(at(R::kA));
+  zero_input_border<1>(at(R::kB));
+  if (t < B4) sh_bias[t] = bias;
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  if (io.act[0]) store_act<2, 2>(at(R::kA), io.act[0] + (size_t)b * N0, N0);
-  conv_sample<0, kXRow[1]>(at(R::kA), at(R::kW1), P + o.b[0], at(R::kB));
+  if (io.act[0]) store_act<0, N0>(at(R::kA), io.act[0] + (size_t)b * N0);
+  conv_sample<0>(at(R::kA), at(R::kW1), sh_bias, at(R::kB));
   __syncthreads();
-  if (io.act[1]) store_act<kC[1], kXRow[1]>(at(R::kB), io.act[1] + (size_t)b * N1, N1);
-  conv_sample<1, kXRow[2]>(at(R::kB), at(R::kW2), P + o.b[1], at(R::kA));
+  if (io.act[1]) store_act<1, N1>(at(R::kB), io.act[1] + (size_t)b * N1);
+  zero_input_border<2>(at(R::kA));
+  conv_sample<1>(at(R::kB), at(R::kW2), sh_bias + B1, at(R::kA));
   __syncthreads();
-  stage_weights(Pb + wrow_off(3), kC[4] * kWRow[3] * 2, at(R::kW4));
-  if (io.act[2]) store_act<kC[2], kXRow[2]>(at(R::kA), io.act[2] + (size_t)b * N2, N2);
-  conv_sample<2, kXRow[3]>(at(R::kA), at(R::kW3), P + o.b[2], at(R::kC3));
+  stage_weights<kC[4] * kWRow[3] * 2>(Pb + wrow_off(3), at(R::kW4));
+  if (io.act[2]) store_act<2, N2>(at(R::kA), io.act[2] + (size_t)b * N2);
+  zero_input_border<3>(at(R::kC3));
+  conv_sample<2>(at(R::kA), at(R::kW3), sh_bias + B2, at(R::kC3));
   // the head's weights, to LDS once W3 is done with: fw1 transposed in rows of 65,
   // so that both fw1 g and fw1^T dz1 read it without conflicts
   static_assert(kFuseThreads * 4 == kHidden * 64, "four elements of fw1 per thread");
@@ -372,7 +468,7 @@ __global__ __launch_bounds__(kFuseThreads) void conv_net_fused(FusedIO io, const
               fb2 = t < kOut ? P[o.fb2 + t] : 0.f;
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  if (io.act[3]) store_act<kC[3], kXRow[3]>(at(R::kC3), io.act[3] + (size_t)b * N3, N3);
+  if (io.act[3]) store_act<3, N3>(at(R::kC3), io.act[3] + (size_t)b * N3);
   float* fw1 = reinterpret_cast<float*>(lds + R::kHead);  // [q][t]
   float* fw2 = fw1 + 64 * 65;
   {
@@ -381,10 +477,10 @@ __global__ __launch_bounds__(kFuseThreads) void conv_net_fused(FusedIO io, const
     if (t < kOut * kHidden) fw2[t] = f2;
   }
   uint16_t* a4 = at(R::kA);
-  conv_sample<3, kC[4]>(at(R::kC3), at(R::kW4), P + o.b[3], a4);
+  conv_sample<3>(at(R::kC3), at(R::kW4), sh_bias + B3, a4);
   __syncthreads();
-  if constexpr (TRAIN) stage_weights(PbT + trow_off(3), 9 * kC[3] * kTRow[3] * 2, at(R::kT3));
-  store_act<kC[4], kC[4]>(a4, io.act[4] + (size_t)b * N4, N4);
+  if constexpr (TRAIN) stage_weights<9 * kC[3] * kTRow[3] * 2>(PbT + trow_off(3), at(R::kT3));
+  store_act<4, N4>(a4, io.act[4] + (size_t)b * N4);
   if (!TRAIN && !io.out) return;
   if (t < 64) {
     float v = 0.f;
@@ -439,18 +535,21 @@ __global__ __launch_bounds__(kFuseThreads) void conv_net_fused(FusedIO io, const
   }
   __syncthreads();
   uint16_t* d4 = at(R::kD4);
+  zero_grad_border<4>(d4);
+  zero_grad_border<3>(at(R::kD3));
   for (int e = t; e < N4; e += kFuseThreads) {
     const uint16_t v = bf2f(a4[e]) > 0.f ? sh_dg[e & 63] : (uint16_t)0;
-    d4[(e >> 6) * kDRow[4] + (e & 63)] = v;
+    d4[((e >> 6) / kWs[4] * dcols(4) + (e >> 6) % kWs[4]) * kDRow[4] + (e & 63)] = v;
     io.dz[4][(size_t)b * N4 + e] = v;
   }
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  stage_weights(PbT + trow_off(2), 9 * kC[2] * kTRow[2] * 2, at(R::kT2));
+  stage_weights<9 * kC[2] * kTRow[2] * 2>(PbT + trow_off(2), at(R::kT2));
   conv_bwd_sample<3>(d4, at(R::kT3), io.act[3] + (size_t)b * N3, at(R::kD3), io.dz[3] + (size_t)b * N3);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  stage_weights(PbT + trow_off(1), 9 * kC[1] * kTRow[1] * 2, at(R::kT1));
+  stage_weights<9 * kC[1] * kTRow[1] * 2>(PbT + trow_off(1), at(R::kT1));
+  zero_grad_border<2>(at(R::kD2));
   conv_bwd_sample<2>(at(R::kD3), at(R::kT2), io.act[2] + (size_t)b * N2, at(R::kD2), io.dz[2] + (size_t)b * N2);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
