@@ -1285,7 +1285,7 @@ template <int TILE>
 __global__ __launch_bounds__(256) void pyramid_batch_kernel(const PyrJob* __restrict__ jobs) {
   const PyrJob& j = jobs[blockIdx.z];
   if ((int)blockIdx.x * TILE >= j.g.W[0] || (int)blockIdx.y * TILE >= j.g.H[0]) return;
-  if (TILE == 64 && j.vec16)
+  if constexpr (TILE == 64)
     pyramid_tile64v(j.src, j.pitch, j.dst, j.g);
   else
     pyramid_tile<TILE>(j.src, j.pitch, j.dst, j.g, j.vec4);
@@ -1300,13 +1300,13 @@ __global__ __launch_bounds__(256) void pyramid_batch_args_kernel(const PyrJob* _
   if ((int)blockIdx.x * TILE >= j.g.W[0] || (int)blockIdx.y * TILE >= j.g.H[0]) return;
   const uint8_t* src = srcs.src[z];
   const int64_t pitch = srcs.pitch[z];
-  const uintptr_t sa = reinterpret_cast<uintptr_t>(src), da = reinterpret_cast<uintptr_t>(j.dst);
-  const int W0 = j.g.W[0];
-  if (TILE == 64 && (pitch % 16) == 0 && (sa % 16) == 0 && (W0 % 16) == 0 && (da % 16) == 0)
+  if constexpr (TILE == 64) {
     pyramid_tile64v(src, pitch, j.dst, j.g);
-  else
+  } else {
+    const uintptr_t sa = reinterpret_cast<uintptr_t>(src), da = reinterpret_cast<uintptr_t>(j.dst);
     pyramid_tile<TILE>(src, pitch, j.dst, j.g,
-                       ((pitch % 4) == 0 && (sa % 4) == 0 && (W0 % 4) == 0 && (da % 4) == 0) ? 1 : 0);
+                       ((pitch % 4) == 0 && (sa % 4) == 0 && (j.g.W[0] % 4) == 0 && (da % 4) == 0) ? 1 : 0);
+  }
 }
 
 // pyramid_block over a batch: blockIdx.y = image, one thread per block.
@@ -1341,11 +1341,11 @@ hipError_t launch_pyramid_batch_args(const PyrJob* d_static, const PyrSrcArgs& s
 }
 
 // Window pyramids: blockIdx.z = stream * n_frames + frame; a workgroup builds
-// kWinTiles consecutive tiles of a tile row.
+// up to kWinTiles consecutive tiles of a tile row.
 constexpr int kWinTiles = 4;
 template <int TILE>
 __global__ __launch_bounds__(256) void pyramid_window_kernel(const WinJob* __restrict__ jobs, PyrWinSrc srcs,
-                                                             int n_frames) {
+                                                             int n_frames, int tiles) {
   const int z = blockIdx.z, js = z / n_frames, f = z - js * n_frames;
   const WinJob& j = jobs[js];
   const int oy = blockIdx.y * TILE;
@@ -1354,17 +1354,17 @@ __global__ __launch_bounds__(256) void pyramid_window_kernel(const WinJob* __res
   uint8_t* dst = j.dst + f * j.dst_stride;
   const int64_t pitch = srcs.pitch[js];
   const bool write_l0 = srcs.write_l0[js] != 0;
-  const uintptr_t sa = reinterpret_cast<uintptr_t>(src), da = reinterpret_cast<uintptr_t>(dst);
   const int W0 = j.g.W[0];
-  const bool v16 = TILE == 64 && (pitch % 16) == 0 && (sa % 16) == 0 && (W0 % 16) == 0 && (da % 16) == 0;
-  const int v4 = ((pitch % 4) == 0 && (sa % 4) == 0 && (W0 % 4) == 0 && (da % 4) == 0) ? 1 : 0;
-  for (int t = 0; t < kWinTiles; ++t) {  // the tile's LDS is free again when the previous call returns
-    const int ox = ((int)blockIdx.x * kWinTiles + t) * TILE;
+  for (int t = 0; t < tiles; ++t) {  // the tile's LDS is free again when the previous call returns
+    const int ox = ((int)blockIdx.x * tiles + t) * TILE;
     if (ox >= W0) break;
-    if (v16)
+    if constexpr (TILE == 64) {
       pyramid_tile64v_at(src, pitch, dst, j.g, ox, oy, write_l0);
-    else
+    } else {
+      const uintptr_t sa = reinterpret_cast<uintptr_t>(src), da = reinterpret_cast<uintptr_t>(dst);
+      const int v4 = ((pitch % 4) == 0 && (sa % 4) == 0 && (W0 % 4) == 0 && (da % 4) == 0) ? 1 : 0;
       pyramid_tile_at<TILE>(src, pitch, dst, j.g, v4, ox, oy, write_l0);
+    }
   }
 }
 
@@ -1395,14 +1395,14 @@ hipError_t launch_pyramid_window(const WinJob* d_jobs, const PyrWinSrc& srcs, in
                          d_jobs, srcs, n_frames);
     return hipGetLastError();
   }
-  constexpr int T64 = 64 * kWinTiles, T128 = 128 * kWinTiles;
+  // several tiles of a row per workgroup only where one each is many turns of the chip
+  const int T = levels <= 7 ? 64 : 128, nx = (max_w + T - 1) / T, ny = (max_h + T - 1) / T, nz = n_streams * n_frames;
+  const int tiles = (int64_t)nx * ny * nz > 8192 ? kWinTiles : 1;
+  const dim3 grid((nx + tiles - 1) / tiles, ny, nz);
   if (levels <= 7)
-    hipLaunchKernelGGL(pyramid_window_kernel<64>, dim3((max_w + T64 - 1) / T64, (max_h + 63) / 64, n_streams * n_frames),
-                       dim3(256), 0, s, d_jobs, srcs, n_frames);
+    hipLaunchKernelGGL(pyramid_window_kernel<64>, grid, dim3(256), 0, s, d_jobs, srcs, n_frames, tiles);
   else
-    hipLaunchKernelGGL(pyramid_window_kernel<128>,
-                       dim3((max_w + T128 - 1) / T128, (max_h + 127) / 128, n_streams * n_frames), dim3(256), 0, s,
-                       d_jobs, srcs, n_frames);
+    hipLaunchKernelGGL(pyramid_window_kernel<128>, grid, dim3(256), 0, s, d_jobs, srcs, n_frames, tiles);
   return hipGetLastError();
 }
 

@@ -219,7 +219,6 @@ struct PyrJob {
   uint8_t* dst;
   PyrGeom g;
   int32_t vec4;   // width, pitch and addresses multiples of 4
-  int32_t vec16;  // ... of 16 (pyramid_tile64v)
 };
 
 // Variants of the cooperative track kernel.

@@ -14,10 +14,9 @@ namespace dpt {
 
 // ---------------------------------------------------------------- pyramid
 
-template <int TILE>
-__global__ __launch_bounds__(256) void pyramid_kernel(const uint8_t* __restrict__ src, int64_t pitch,
-                                                      uint8_t* __restrict__ dst, PyrGeom g, int vec4) {
-  pyramid_tile<TILE>(src, pitch, dst, g, vec4);
+__global__ __launch_bounds__(256) void pyramid128_kernel(const uint8_t* __restrict__ src, int64_t pitch,
+                                                         uint8_t* __restrict__ dst, PyrGeom g, int vec4) {
+  pyramid_tile<128>(src, pitch, dst, g, vec4);
 }
 
 __global__ __launch_bounds__(256) void pyramid64v_kernel(const uint8_t* __restrict__ src, int64_t pitch,
@@ -35,12 +34,6 @@ __global__ __launch_bounds__(256) void pyramid_block_kernel(const uint8_t* __res
   pyramid_block<LV>(src, pitch, dst, g, t % nbx, t / nbx, true);
 }
 
-// Whether pyramid_tile64v applies: 16-byte aligned rows and destination, at most 7 levels.
-static bool pyramid_tile64v_ok(const PyrGeom& g, const void* src, int64_t pitch, const void* dst) {
-  return (pitch % 16) == 0 && (reinterpret_cast<uintptr_t>(src) % 16) == 0 && (g.W[0] % 16) == 0 &&
-         (reinterpret_cast<uintptr_t>(dst) % 16) == 0 && g.levels <= 7;
-}
-
 hipError_t launch_pyramid(const uint8_t* src, int64_t pitch, uint8_t* dst, const PyrGeom& g, hipStream_t s) {
   if (pyramid_block_ok(g, src, pitch, dst)) {
     const int B = 1 << (g.levels - 1), n = (g.W[0] / B) * (g.H[0] / B);
@@ -50,22 +43,14 @@ hipError_t launch_pyramid(const uint8_t* src, int64_t pitch, uint8_t* dst, const
       hipLaunchKernelGGL(pyramid_block_kernel<3>, dim3((n + 255) / 256), dim3(256), 0, s, src, pitch, dst, g);
     return hipGetLastError();
   }
-  int vec4 = ((pitch % 4) == 0 && (reinterpret_cast<uintptr_t>(src) % 4) == 0 && (g.W[0] % 4) == 0 &&
-              (reinterpret_cast<uintptr_t>(dst) % 4) == 0)
-                 ? 1
-                 : 0;
-  if (pyramid_tile64v_ok(g, src, pitch, dst)) {
+  if (g.levels <= 7) {
     dim3 grid((g.W[0] + 63) / 64, (g.H[0] + 63) / 64);
     hipLaunchKernelGGL(pyramid64v_kernel, grid, dim3(256), 0, s, src, pitch, dst, g);
-  } else if (g.levels <= 6) {
-    dim3 grid((g.W[0] + 31) / 32, (g.H[0] + 31) / 32);
-    hipLaunchKernelGGL(pyramid_kernel<32>, grid, dim3(256), 0, s, src, pitch, dst, g, vec4);
-  } else if (g.levels == 7) {
-    dim3 grid((g.W[0] + 63) / 64, (g.H[0] + 63) / 64);
-    hipLaunchKernelGGL(pyramid_kernel<64>, grid, dim3(256), 0, s, src, pitch, dst, g, vec4);
   } else {
+    const int vec4 = (pitch % 4) == 0 && (reinterpret_cast<uintptr_t>(src) % 4) == 0 && (g.W[0] % 4) == 0 &&
+                     (reinterpret_cast<uintptr_t>(dst) % 4) == 0;
     dim3 grid((g.W[0] + 127) / 128, (g.H[0] + 127) / 128);
-    hipLaunchKernelGGL(pyramid_kernel<128>, grid, dim3(256), 0, s, src, pitch, dst, g, vec4);
+    hipLaunchKernelGGL(pyramid128_kernel, grid, dim3(256), 0, s, src, pitch, dst, g, vec4);
   }
   return hipGetLastError();
 }
@@ -184,9 +169,8 @@ static void launch_gauss(int nd, const SRC* src, int64_t pitch, float* dst, uint
 
 hipError_t launch_pyramid_gauss(const uint8_t* src, int64_t pitch, uint8_t* u8, float* dst, const PyrGeom& g,
                                 hipStream_t s) {
-  // the uint8 levels go with the first launch where the 16-byte tiles apply (as
-  // in launch_pyramid)
-  if (u8 && !pyramid_tile64v_ok(g, src, pitch, u8)) {
+  // the uint8 levels go with the first launch where the 64x64 tiles hold them
+  if (u8 && g.levels > 7) {
     const hipError_t e = launch_pyramid(src, pitch, u8, g, s);
     if (e != hipSuccess) return e;
     u8 = nullptr;
