@@ -924,16 +924,22 @@ __device__ __forceinline__ void load_point(const TrackArgs& a, int l, int i, Poi
 }
 
 // The cooperative kernel's geometry of map point i, the same for every level
-// and frame of a launch: X0, Y0, Z0 of pr (a point past the map, behind the
-// camera or not finite, which no level holds as valid, becomes (0, 0, 1)).  Returns
-// whether the point can be valid; *j is its entry in a level's cache.
+// and frame of a launch: X0, Y0, Z0 of pr.  A point past the map, behind the
+// camera, not finite or with a Jacobian row that is not (|x / z| from 1.8e19 on,
+// or 1 / z past FP32) becomes (0, 0, 1): no level holds it as valid, but the matrix
+// products multiply every point's rows, by zero for an unusable one, and zero
+// times infinity would reach the whole stream.  Returns whether the point can be
+// valid; *j is its entry in a level's cache.
 template <class PR>
 __device__ __forceinline__ bool load_geometry_once(const TrackArgs& a, int i, PR& pr, int* j) {
   const bool in = i < a.ref.n;
   *j = in ? i : 0;
   const float4 p = gload(a.ref.x0 + *j);
+  const float iz = 1.0f / p.z, xp = p.x * iz, yp = p.y * iz;
+  // every entry of the rows (warp_rows) is at most one of these terms; NaN compares false
+  const float rows = fmaf(xp, xp, 1.0f) + fmaf(yp, yp, 1.0f) + fabsf(xp * iz) + fabsf(yp * iz) + iz;
   const bool can = in && p.z > a.z_min && p.z < __builtin_inff() && fabsf(p.x) < __builtin_inff() &&
-                   fabsf(p.y) < __builtin_inff();
+                   fabsf(p.y) < __builtin_inff() && rows < __builtin_inff();
   pr.X0 = can ? p.x : 0.0f;
   pr.Y0 = can ? p.y : 0.0f;
   pr.Z0 = can ? p.z : 1.0f;
