@@ -507,14 +507,14 @@ hipError_t read_cycle_profile(uint64_t* host, int n_slots, bool reset) {
 
 // Bytes of a level a workgroup stages in LDS (every kernel with its templates in
 // registers): levels of up to this size whole, larger ones as the band of rows
-// its points' taps span.
-// Launches of many workgroups (two per compute unit, 160 KB of LDS each) take
-// the small tile: with the kernel's own ~3 KB a workgroup stays within 64 KB.
-// A launch small enough to run one workgroup per compute unit (the plain-launch
-// path) takes the large one, which holds a 752x480 frame's second level whole
-// and ~190 rows of its first.
-constexpr int kTileBytesSmall = 60 * 1024;
-constexpr int kTileBytesLarge = 144 * 1024;
+// its points' taps span.  With the kernel's own 3 to 4 KB a workgroup stays within
+// 64 KB, so two share a compute unit's 160 KB: the co-residency that the launches
+// count on (coop_max_blocks) holds for every variant.  A map in index order gives
+// a workgroup a band of few rows, and a larger tile only copies more: 144 KB (one
+// workgroup per compute unit) took 396 us for a window of nine 752x480 frames of
+// 2000 points where 60 KB takes 383, 51.2 against 49.7 us for one 640x480 frame of
+// 500; a shuffled map, whose bands span the level, 68.2 against 69.5 us a frame.
+constexpr int kTileBytes = 60 * 1024;
 constexpr int kTilePad = 16;  // the last pair of words read past the last byte
 // Rows kept around the band at the level's start pose: the pose moves during the
 // level's iterations.  Points whose taps leave the band are read from global
@@ -532,9 +532,9 @@ constexpr int kBandMargin = 4;
 template <int NW, class PIX, class PR>
 __device__ __forceinline__ Tile8 stage_tile(const IterParams& a, const PatRegs& pat, const LevelGeom& g,
                                             const PIX* img, const float* T, const PR& pr, bool can,
-                                            uint8_t* tile_mem, int tile_bytes, int* sh_band) {
+                                            uint8_t* tile_mem, int* sh_band) {
   const int W = g.W, H = g.H, row = W * (int)sizeof(PIX);
-  const int rows_fit = (tile_bytes - 32) / row;
+  const int rows_fit = (kTileBytes - 32) / row;
   int lo = 0, hi = H - 1;
   if (rows_fit < H) {
     float X, Y, Z;
@@ -614,7 +614,7 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
                                                            const StartSlot* __restrict__ start,
                                                            TrackOut* __restrict__ out_ring, int slot, int n_out,
                                                            int n_frames, uint32_t seq0, uint32_t tag_base,
-                                                           int spin_limit, int tile_bytes) {
+                                                           int spin_limit) {
   static_assert(!(MIXED && FIXED), "the fixed-H mode computes in FP32");
   static_assert(!(MIXED && GENERIC) && (GENERIC || std::is_same<PIX, uint8_t>::value), "variant");
   static_assert(LPP == 1 || (LPP == 2 && !GENERIC), "two threads per point: the 8-pixel kernels");
@@ -636,7 +636,7 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
   __shared__ __align__(16) float sh_red[NW * kWaveWords];
   __shared__ float sh_grp[GENERIC ? CH : 1];  // the whole-workgroup exchange of many-chunk streams
   __shared__ int sh_band[2 * (CH / 64)];
-  extern __shared__ __align__(16) uint8_t sh_tile[];  // tile_bytes + kTilePad (TILED), else none
+  extern __shared__ __align__(16) uint8_t sh_tile[];  // kTileBytes + kTilePad (TILED), else none
   __shared__ __align__(16) StartSlot sh_start;
   const int2 w = work[blockIdx.x];
   if (w.x < 0) return;  // padding slot of the XCD-aware work list
@@ -761,7 +761,7 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
       } else {
         load_template(a, e, sub, pr);
         sample_offsets(g.W, offs);
-        tile = stage_tile<NW>(ip, pregs, g, img, T, pr, can, sh_tile, tile_bytes, sh_band);
+        tile = stage_tile<NW>(ip, pregs, g, img, T, pr, can, sh_tile, sh_band);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         if (l == 0) tile0 = tile, at0 = true;
@@ -994,6 +994,9 @@ static const void* coop_fn(int variant) {
 // Whether a variant stages its levels in LDS tiles.
 static bool tiled(int variant) { return !(variant & kCoopGeneric) || (variant & kCoopSlots); }
 
+// Dynamic LDS of a launch: what the co-residency is counted with.
+static size_t coop_tile_lds(int variant) { return tiled(variant) ? kTileBytes + kTilePad : 0; }
+
 // Co-resident workgroups per CU: the least over every variant at this chunk size.
 template <int CH>
 static int coop_blocks_per_cu() {
@@ -1018,8 +1021,7 @@ static int coop_blocks_per_cu() {
       for (const void* f : {coop_fn<CH, false>(v), coop_fn<CH, true>(v)}) {
         if (!f) continue;
         int k = 0;
-        const size_t dyn = tiled(v) ? kTileBytesSmall + kTilePad : 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&k, f, CH, dyn) != hipSuccess) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&k, f, CH, coop_tile_lds(v)) != hipSuccess) {
           (void)hipGetLastError();
           k = 0;
         }
@@ -1057,8 +1059,9 @@ int coop_max_blocks(int chunk) {
 // must be resident together.  A grid of at most a quarter of the device's
 // co-resident capacity is launched as an ordinary kernel: it is resident as
 // soon as the device has that much room, which leaves room for three more such
-// launches running concurrently on other streams, and it avoids the
-// cooperative launch's extra per-launch cost (about 15 us here).  Larger grids
+// launches running concurrently on other streams (on the XCD that a stream's
+// chunks are packed to as well: at most 16 of its 64 places each), and it avoids
+// the cooperative launch's extra per-launch cost (about 15 us here).  Larger grids
 // use the cooperative launch, which guarantees co-residency.  Either way every
 // wait is bounded by spin_limit, so a chunk that cannot be scheduled turns
 // into a reported timeout, not a hang.
@@ -1069,22 +1072,9 @@ static hipError_t coop_launch_k(const CoopStream* d_streams, const int2* d_work,
   const void* fn = n_frames > 0 ? coop_fn<CH, true>(variant) : coop_fn<CH, false>(variant);
   if (!fn) return hipErrorInvalidValue;
   const bool plain = 4 * n_work <= coop_max_blocks(CH);
-  // the level tile: large where the launch is small enough for one workgroup per
-  // compute unit, else small (two per compute unit)
-  int tile_bytes = !tiled(variant) ? 0 : plain ? kTileBytesLarge : kTileBytesSmall;
-  const size_t dyn = tile_bytes ? (size_t)tile_bytes + kTilePad : 0;
-  if (dyn > 64 * 1024) {
-    static bool raised[2][64] = {};  // per window form and variant: the attribute is set once
-    bool& r = raised[n_frames > 0][variant & 63];
-    if (!r) {
-      const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
-      if (e != hipSuccess) return e;
-      r = true;
-    }
-  }
+  const size_t dyn = coop_tile_lds(variant);
   void* args[] = {(void*)&d_streams, (void*)&d_work,   (void*)&start,    (void*)&out_ring,   (void*)&slot,
-                  (void*)&n_out,     (void*)&n_frames, (void*)&seq0,     (void*)&tag_base,   (void*)&spin_limit,
-                  (void*)&tile_bytes};
+                  (void*)&n_out,     (void*)&n_frames, (void*)&seq0,     (void*)&tag_base,   (void*)&spin_limit};
   if (plain) return hipLaunchKernel(fn, dim3(n_work), dim3(CH), args, dyn, s);
   return hipLaunchCooperativeKernel(fn, dim3(n_work), dim3(CH), args, dyn, s);
 }
