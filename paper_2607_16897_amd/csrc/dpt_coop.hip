@@ -521,6 +521,13 @@ constexpr int kTilePad = 16;  // the last pair of words read past the last byte
 // memory (their whole wave).
 constexpr int kBandMargin = 4;
 
+// Whether a pattern's taps (a row and a column past its last sample, read as pairs
+// of words) fit the tile's allocation from anywhere in its first granule, at a
+// level of W bytes a row.
+__device__ __forceinline__ bool tile_spans(const PatRegs& pat, int W) {
+  return ((int)pat.dy_max - (int)pat.dy_min + 1) * W + (int)pat.dx_max - (int)pat.dx_min + 16 + 8 <= kTileBytes + kTilePad;
+}
+
 // Stage level g of the current frame (img = its first byte) in the workgroup's
 // LDS tile: the whole level if it fits, else the rows the taps of the usable
 // points span at pose T, widened by kBandMargin and cut to the tile's size.
@@ -573,7 +580,7 @@ __device__ __forceinline__ Tile8 stage_tile(const IterParams& a, const PatRegs& 
   }
   Tile8 t;
   t.lds = (const __attribute__((address_space(3))) uint8_t*)(tile_mem);
-  t.lo = lo, t.hi = hi, t.delta = delta, t.bytes = ng * 16;
+  t.lo = lo, t.hi = hi, t.delta = delta, t.spans = tile_spans(pat, row);
   return t;
 }
 
@@ -587,11 +594,12 @@ __device__ __forceinline__ void lane_offsets(const PatRegs& pat, int W, int sub,
   for (int k = 0; k < NS; ++k) off[k] = NS == 8 ? all[k] : (sub ? all[NS + k] : all[k]);
 }
 
-// A tile that holds no row: every usable point reads global memory.
-__device__ __forceinline__ Tile8 no_tile(uint8_t* tile_mem) {
+// A tile that holds no row of a level of W bytes a row: every usable point reads
+// global memory.
+__device__ __forceinline__ Tile8 no_tile(uint8_t* tile_mem, const PatRegs& pat, int W) {
   Tile8 t;
   t.lds = (const __attribute__((address_space(3))) uint8_t*)(tile_mem);
-  t.lo = 1, t.hi = 0, t.delta = 0, t.bytes = 16;
+  t.lo = 1, t.hi = 0, t.delta = 0, t.spans = tile_spans(pat, W);
   return t;
 }
 
@@ -744,7 +752,7 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
     LaneTotals tot = {};
     // the level-0 tile and point registers, reused by the final pass when the
     // levels ran down to 0
-    Tile8 tile0 = no_tile(sh_tile);
+    Tile8 tile0 = no_tile(sh_tile, pregs, a.lv[0].W);
     bool at0 = false;
     if constexpr (kCycleProfile) cy_fr[0] += clock64() - cf0, ++cy_fr[3];
     for (int l = a.levels - 1; l >= 0 && !stop; --l) {

@@ -1071,10 +1071,12 @@ struct __attribute__((packed)) PixPair<float> {
 
 // The bytes of the current level a workgroup holds in LDS: rows lo..hi
 // (inclusive), each W bytes, byte (r, x) of the level at offset
-// delta + (r - lo) * W + x.  `bytes` is how many are valid from the start.
+// delta + (r - lo) * W + x.  spans: the tile's allocation is long enough for a
+// pattern of the level whose first row is the tile's.
 struct Tile8 {
   const __attribute__((address_space(3))) uint8_t* lds;
-  int lo, hi, delta, bytes;
+  int lo, hi, delta;
+  bool spans;
 };
 
 // Byte offset in the level of the pattern's sample k relative to its base
@@ -1140,10 +1142,11 @@ __device__ __forceinline__ PointSums sample_point(const IterParams& a, const Pat
   const int iu = q0.iu, iv = q0.iv, W = g.W;
   // Every usable point of the wave inside the tile?  An unusable one reads from
   // the tile position of a pattern whose top-left sample sits at the tile's first
-  // byte: a few rows, inside the allocation whatever the level, and masked below.
-  // Other patterns may span more rows than the tile holds: their unusable points
-  // read its first bytes.
+  // byte, masked below; a tile too short for that (8 samples 32 rows apart at a
+  // width of 2000, never the default pattern) holds no usable point either.  Other
+  // patterns' unusable points read the tile's first bytes.
   const bool in_tile = !ok | ((iv + (int)pat.dy_min >= tile.lo) & (iv + (int)pat.dy_max + 1 <= tile.hi));
+  const bool use_tile = (QUAD || tile.spans) && __all(in_tile);
   PointSums s = {};
   s.ok = ok;
   // Up to eight samples at a time: all their taps are requested before any is
@@ -1152,7 +1155,7 @@ __device__ __forceinline__ PointSums sample_point(const IterParams& a, const Pat
 #pragma unroll
   for (int k0 = 0; k0 < NS; k0 += B) {
     float t00[B], t10[B], t01[B], t11[B];
-    if (__all(in_tile)) {
+    if (use_tile) {
       const int lb = (int)(uint32_t)(uintptr_t)tile.lds;
       const int lbase = lb + tile.delta +
                         (int)sizeof(PIX) * (ok ? (iv - tile.lo) * W + iu : -((int)pat.dy_min * W + (int)pat.dx_min));
