@@ -379,11 +379,12 @@ __device__ __forceinline__ void wave_step() {
 // so the same result.  The second step runs only where the first began more than
 // 1e-7 off (it leaves 3/8 of the square): the products of tracked poses are
 // rotations to FP64 rounding, and two steps for each took a window of nine frames
-// from 396 to 401 us.  M: 12 doubles of scratch.
+// from 396 to 401 us.  A loop, not two copies: it is in the kernel three times, and
+// the code of both cost a launch of one frame 1.3 us more.  M: 12 doubles of scratch.
 __device__ __forceinline__ void orthonormalize_wave(double* T, double* M, int t) {
   const int r = (t >> 2) & 3, c = t & 3;
   const bool rot = t < 12 && c < 3;
-#pragma unroll
+#pragma unroll 1
   for (int it = 0; it < 2; ++it) {
     wave_step();
     // 3I - R^T R, element (r, c)
