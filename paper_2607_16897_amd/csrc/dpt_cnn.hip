@@ -691,7 +691,7 @@ __device__ __forceinline__ void wgrad_layer(const uint16_t* __restrict__ x, cons
       }
     }
   }
-  if constexpr (C::KG > 1) {  // the shares of the steps, summed in order
+  if constexpr (C::KG > 1) {  // the shares of the steps, summed in pairs
     float* sh = reinterpret_cast<float*>(lds);
     __syncthreads();
 #pragma unroll
@@ -699,11 +699,15 @@ __device__ __forceinline__ void wgrad_layer(const uint16_t* __restrict__ x, cons
       *reinterpret_cast<float4_t*>(sh + (((kg * C::MT + mt) * C::NT + nt0 + k) * 64 + lane) * 4) = acc[k];
     __syncthreads();
     for (int e = t; e < C::MT * C::NT * 256; e += kFuseThreads) {
-      float v = 0.f;
+      float v[C::KG];
 #pragma unroll
-      for (int g = 0; g < C::KG; ++g) v += sh[g * C::MT * C::NT * 256 + e];
+      for (int g = 0; g < C::KG; ++g) v[g] = sh[g * C::MT * C::NT * 256 + e];
+#pragma unroll
+      for (int w = C::KG / 2; w > 0; w >>= 1)
+#pragma unroll
+        for (int g = 0; g < w; ++g) v[g] += v[g + w];
       const int tile = e >> 8, l = e >> 2 & 63;
-      out[(tile / C::NT * 16 + 4 * (l >> 4) + (e & 3)) * C::NPAD + tile % C::NT * 16 + (l & 15)] = v;
+      out[(tile / C::NT * 16 + 4 * (l >> 4) + (e & 3)) * C::NPAD + tile % C::NT * 16 + (l & 15)] = v[0];
     }
   } else {
 #pragma unroll
@@ -716,9 +720,16 @@ __device__ __forceinline__ void wgrad_layer(const uint16_t* __restrict__ x, cons
 }
 
 // Samples per workgroup of layer l for B samples, in 1/256 of B: the workgroups of
-// all layers together are at most 246, one turn of the chip.
-constexpr int kWgradShare[4] = {4, 3, 4, 8};
-constexpr int wgrad_samples(int l, int B) { return (int)(((int64_t)B * kWgradShare[l] + 255) / 256); }
+// all layers together are at most 246, one turn of the chip.  Above 512 samples a
+// workgroup's stay at what they are there (6 to 16) and the workgroups take turns:
+// the products of a workgroup's samples meet in one accumulator, whose rounding
+// grows with their number.  One turn at any size lost 1.3e-6 of a gradient at 4096
+// equal samples, so 1.5e-7, for 4 % of the step's time (4096 samples 819 to 869 us,
+// and 919 with turns from 256 samples on).
+constexpr int kWgradShare[4] = {4, 3, 4, 8}, kWgradMost = 2;
+constexpr int wgrad_samples(int l, int B) {
+  return B <= 256 * kWgradMost ? (int)(((int64_t)B * kWgradShare[l] + 255) / 256) : kWgradMost * kWgradShare[l];
+}
 constexpr int wgrad_slots(int l, int B) { return (B + wgrad_samples(l, B) - 1) / wgrad_samples(l, B); }
 constexpr int npad(int l) { return (9 * kC[l] + 1 + 15) / 16 * 16; }
 
@@ -908,13 +919,16 @@ int cfail(int code, const char* msg) { return set_error(code, msg); }
     if (e_ != hipSuccess) return cfail(DPT_E_HIP, #expr);      \
   } while (0)
 
-// Room for them at any B: at most 256 / share slots a layer.
-constexpr size_t max_partial() {
+// Room for the weight gradients' slots at any B up to max_batch: at most 256 / share
+// a layer up to 512 samples, and above as many as at max_batch.
+size_t max_partial(int max_batch) {
   size_t n = 0;
-  for (int l = 0; l < 4; ++l) n += (size_t)((256 + kWgradShare[l] - 1) / kWgradShare[l]) * kC[l + 1] * npad(l);
+  for (int l = 0; l < 4; ++l) {
+    const size_t few = (256 + kWgradShare[l] - 1) / kWgradShare[l], all = wgrad_slots(l, max_batch);
+    n += std::max(few, all) * kC[l + 1] * npad(l);
+  }
   return n;
 }
-constexpr size_t kMaxPartial = max_partial();
 
 // The weight gradients' slots for B samples, one layer after the other in `partial`.
 size_t partial_floats(int B, size_t (&at)[4]) {
@@ -988,7 +1002,7 @@ int dpt_cnn_create(int32_t max_batch, void* hip_stream, dpt_cnn** out) {
     const size_t e = B * kHs[l] * kWs[l] * kC[l];
     ok = hipMalloc(&c->act[l], e * 2) == hipSuccess && hipMalloc(&c->dz[l], e * 4) == hipSuccess;
   }
-  c->partial_floats = kMaxPartial;
+  c->partial_floats = max_partial(max_batch);
   ok = ok && hipMalloc(&c->out, B * kOut * 4) == hipSuccess && hipMalloc(&c->tgt, B * kOut * 4) == hipSuccess &&
        hipMalloc(&c->sqerr, B * kOut * 4) == hipSuccess &&
        hipMalloc(&c->fcg, B * (size_t)(c->o.total - c->o.fw1) * 4) == hipSuccess &&

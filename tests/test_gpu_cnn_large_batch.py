@@ -6,6 +6,9 @@ size, round off at most 2^-25 of the sum each."""
 import numpy as np
 import pytest
 
+from oracle import cnn as ocnn
+from test_gpu_cnn import _bf16, _bf16_storage_grads, _cos, _data, _rel
+
 pytestmark = pytest.mark.gpu
 
 SHAPES = [("w1", 16 * 18), ("b1", 16), ("w2", 32 * 144), ("b2", 32), ("w3", 64 * 288), ("b3", 64), ("w4", 64 * 576),
@@ -45,3 +48,27 @@ def test_fc_gradients(gpu_lib, B):
     e = _errors(gpu_lib, B)
     bad = {k: e[k] for k in ("fw1", "fb1", "fw2", "fb2") if not e[k] <= _bound(B)}
     assert not bad, (bad, _bound(B))
+
+
+@pytest.mark.parametrize("B", [512, 1024, 4096, 16384])
+def test_conv_gradients(gpu_lib, B):
+    e = _errors(gpu_lib, B)
+    bad = {k: v for k, v in e.items() if k not in ("fw1", "fb1", "fw2", "fb2") and not v <= _bound(B)}
+    assert not bad, (bad, _bound(B))
+
+
+def test_ragged_last_workgroup(gpu_lib):
+    """513 pairs: one sample, or three, in the last workgroup of each layer; against
+    the BF16-storage reference of test_gpu_cnn at its bounds."""
+    p = ocnn.init_params(7)
+    pairs, tgt = _data(513, seed=513)
+    net = gpu_lib.Cnn(max_batch=513)
+    net.set_params(p)
+    loss = net.train_step(pairs, tgt, lr=0.0)
+    g = gpu_lib.cnn_unflatten(net.get_grads())
+    net.close()
+    le, eg = _bf16_storage_grads({k: (_bf16(v) if k.startswith("w") else v) for k, v in p.items()},
+                                 ocnn.normalise(pairs), tgt)
+    assert abs(loss - le) / le < 1e-4
+    for k in ocnn.PARAM_NAMES:
+        assert _cos(g[k], eg[k]) > 0.99999 and _rel(g[k], eg[k]) < 2e-3, k
