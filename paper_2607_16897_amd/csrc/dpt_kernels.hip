@@ -193,18 +193,20 @@ hipError_t launch_pyramid_gauss(const uint8_t* src, int64_t pitch, uint8_t* u8, 
 // from (gx, gy) and x0, so the cache holds 12 bytes per sample.
 //
 // A small map is bound by the launch and its chain of latencies: one sample a
-// thread.  A large one (maps of a batch) by the transform and projection that a
-// point's threads repeat and by the image reads: four samples a thread, where
-// the pattern has a multiple of four, and a read per row of a cell's pixels
-// instead of one per pixel.  64 maps of 2000 8-pixel points, 4 levels: 50 us a
-// sample a thread, 43 so, 34 with a map to an XCD; a single map stays at 5.
+// thread.  A large one by the transform and projection that a point's threads repeat
+// and by the image reads: four samples a thread, where the pattern has a multiple of
+// four, and a read per row of a cell's pixels instead of one per pixel.  The lines
+// between the forms are run_precompute's.
 template <int SPT>
 __global__ __launch_bounds__(256) void precompute_kernel(PrecomputeArgs one, const PrecomputeArgs* __restrict__ many,
-                                                         int n_ref, int blocks, int levels) {
-  // Workgroup id goes to XCD id % 8: reference r's workgroups all have id % 8 =
-  // r % 8, so one XCD's L2 reads its levels, not all eight.
+                                                         int n_ref, int blocks, int levels, int xcd) {
+  // Workgroup id goes to XCD id % 8.  xcd: reference r's workgroups all have id % 8
+  // = r % 8, so one XCD's L2 reads its levels, not all eight.
   int blk = blockIdx.x, r = 0;
-  if (many) r = (int)(blk / 8 / (blocks * levels)) * 8 + (blk & 7), blk = blk / 8 % (blocks * levels);
+  if (many) {
+    const int per = blocks * levels, id = xcd ? blk >> 3 : blk;
+    r = xcd ? id / per * 8 + (blk & 7) : id / per, blk = id % per;
+  }
   if (r >= n_ref) return;
   const PrecomputeArgs& a = many ? many[r] : one;
   const int K = a.pat.K;
@@ -253,15 +255,27 @@ __global__ __launch_bounds__(256) void precompute_kernel(PrecomputeArgs one, con
   }
 }
 
+// Which form: four samples a thread from 2^18 samples in all, if a map has 2^15 of
+// them or more; a map to an XCD if the maps fill the eight XCDs to an eighth, or if a
+// map's workgroups are few (two per compute unit of an XCD).  8-pixel points, 4 levels,
+// in us as: one sample a thread, four; the same with a map to an XCD:
+//    one map of 2000     5.0   7.3            16 x 500    6.0   7.4 |  6.2   6.5
+//    one of 8192         7.6   7.9            64 x 500   17.5  20.8 | 15.4  19.1
+//    one of 12000        8.7   8.2             2 x 2000   4.7   6.5 |  8.3   6.7
+//    one of 65536       28.5  18.4             8 x 2000   9.3   8.0 |  8.8   7.6
+//     2 x 500            4.2   6.2 |  3.9  5.6  9 x 5000  20.1  14.2 | 30.3  22.0
+//     6 x 1000           5.6   6.6 |  6.4  6.6 64 x 2000  53.2  41.1 | 48.8  33.8
 static hipError_t run_precompute(const PrecomputeArgs& one, const PrecomputeArgs* many, int n_ref, int max_samples,
                                  int K, int max_levels, hipStream_t s) {
-  const int spt = K % 4 == 0 && (int64_t)n_ref * max_samples * max_levels >= 1 << 18 ? 4 : 1;
-  const int blocks = (max_samples / spt + 255) / 256;
-  const dim3 grid((many ? (n_ref + 7) / 8 * 8 : 1) * blocks * max_levels);
+  const int64_t per_map = (int64_t)max_samples * max_levels;
+  const int spt = K % 4 == 0 && n_ref * per_map >= 1 << 18 && per_map >= 1 << 15 ? 4 : 1;
+  const int blocks = (max_samples / spt + 255) / 256, padded = (n_ref + 7) / 8 * 8;
+  const int xcd = many && (8 * (padded - n_ref) <= n_ref || (int64_t)blocks * max_levels <= 64);
+  const dim3 grid((xcd ? padded : n_ref) * blocks * max_levels);
   if (spt == 4)
-    hipLaunchKernelGGL(precompute_kernel<4>, grid, dim3(256), 0, s, one, many, n_ref, blocks, max_levels);
+    hipLaunchKernelGGL(precompute_kernel<4>, grid, dim3(256), 0, s, one, many, n_ref, blocks, max_levels, xcd);
   else
-    hipLaunchKernelGGL(precompute_kernel<1>, grid, dim3(256), 0, s, one, many, n_ref, blocks, max_levels);
+    hipLaunchKernelGGL(precompute_kernel<1>, grid, dim3(256), 0, s, one, many, n_ref, blocks, max_levels, xcd);
   return hipGetLastError();
 }
 
