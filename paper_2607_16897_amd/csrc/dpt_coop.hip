@@ -1345,8 +1345,7 @@ hipError_t launch_pyramid_batch_args(const PyrJob* d_static, const PyrSrcArgs& s
 }
 
 // Window pyramids: blockIdx.z = stream * n_frames + frame; a workgroup builds
-// up to kWinTiles consecutive tiles of a tile row.
-constexpr int kWinTiles = 4;
+// up to `tiles` consecutive tiles of a tile row.
 template <int TILE>
 __global__ __launch_bounds__(256) void pyramid_window_kernel(const WinJob* __restrict__ jobs, PyrWinSrc srcs,
                                                              int n_frames, int tiles) {
@@ -1399,9 +1398,14 @@ hipError_t launch_pyramid_window(const WinJob* d_jobs, const PyrWinSrc& srcs, in
                          d_jobs, srcs, n_frames);
     return hipGetLastError();
   }
-  // several tiles of a row per workgroup only where one each is many turns of the chip
+  // several tiles of a row per workgroup where one each is many turns of the chip:
+  // four, or two where four would leave places idle in a row.  5 levels, 9 frames a
+  // stream, in us with one, two and four tiles: 752x480, 2 streams (1728 tiles) 6.5,
+  // 7.0, 10.0; 5 (4320) 14.7, 13.2, 12.9; 8 19.8, 18.0, 17.4.  1001x700, one (1584)
+  // 9.0, 7.8, 10.5; 2 (3168) 17.6, 13.5, 12.8.  320x240 (rows of 5 tiles), 24 (4320)
+  // 13.0, 12.9, 13.9; 64 23.5, 22.2, 28.4.
   const int T = levels <= 7 ? 64 : 128, nx = (max_w + T - 1) / T, ny = (max_h + T - 1) / T, nz = n_streams * n_frames;
-  const int tiles = (int64_t)nx * ny * nz > 8192 ? kWinTiles : 1;
+  const int tiles = (int64_t)nx * ny * nz <= 3072 ? 1 : 8 * ((nx + 3) / 4 * 4 - nx) <= nx ? 4 : 2;
   const dim3 grid((nx + tiles - 1) / tiles, ny, nz);
   if (levels <= 7)
     hipLaunchKernelGGL(pyramid_window_kernel<64>, grid, dim3(256), 0, s, d_jobs, srcs, n_frames, tiles);
