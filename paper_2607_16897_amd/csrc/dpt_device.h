@@ -1341,11 +1341,15 @@ __device__ __forceinline__ PointSums sample_point_generic(const TrackArgs& a, co
   PointSums s = {};
   s.ok = ok;
   // Batches of four samples per lane: all their taps and cache entries are
-  // issued before any is used.  A slot past the pattern reads sample 0 (always
+  // issued before any is used (the barriers keep it so: left to itself the compiler
+  // waits for each sample's taps, 262 instead of 192 us for five iterations of 1500
+  // 11x11 patches over four levels).  A slot past the pattern reads sample 0 (always
   // in range) and is weighted by zero.
   constexpr int B = 4;
   for (int k0 = sub; k0 < K; k0 += B * kLanesPerPoint) {
     float t00[B], t10[B], t01[B], t11[B], i0[B], gxs[B], gys[B], msk[B];
+    uint32_t off[B];
+    PixPair<PIX> top[B], bot[B];
 #pragma unroll
     for (int j = 0; j < B; ++j) {
       const int k = k0 + j * kLanesPerPoint;
@@ -1353,11 +1357,17 @@ __device__ __forceinline__ PointSums sample_point_generic(const TrackArgs& a, co
       const int kk = has ? k : 0;
       msk[j] = has ? 1.0f : 0.0f;
       // an unusable point reads the level's first taps
-      const int off = ((q0.iv + (int)pat.dy[kk]) * W + q0.iu + (int)pat.dx[kk]) & -(int)ok;
-      t00[j] = gimg[off], t10[j] = gimg[off + 1], t01[j] = gimg[off + W], t11[j] = gimg[off + W + 1];
+      off[j] = (uint32_t)(((q0.iv + (int)pat.dy[kk]) * W + q0.iu + (int)pat.dx[kk]) & -(int)ok);
       i0[j] = gload(a.ref.I0 + pg.s0 + kk);
       if (!COST_ONLY) gxs[j] = gload(a.ref.gx + pg.s0 + kk), gys[j] = gload(a.ref.gy + pg.s0 + kk);
     }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < B; ++j) top[j].load(gimg + off[j]), bot[j].load(gimg + (off[j] + W));
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < B; ++j)
+      t00[j] = top[j].left(), t10[j] = top[j].right(), t01[j] = bot[j].left(), t11[j] = bot[j].right();
 #pragma unroll
     for (int j = 0; j < B; ++j) {
       const float Ic = bilin_mix(q0.w, t00[j], t10[j], t01[j], t11[j]);
