@@ -607,8 +607,8 @@ __device__ __forceinline__ Tile8 no_tile(uint8_t* tile_mem, const PatRegs& pat, 
 // MIXED: FP16 reference cache, Kahan-compensated FP32 sums across waves and
 // chunks, FP64 solve, exponential and pose state.
 // FIXED: fixed-H mode (FP32): unweighted residuals, only b, the cost and the
-// counts are reduced and exchanged (16 slots), and each level's constant H
-// comes factored from the precompute.
+// counts are reduced and exchanged (16 slots), and the inverse of each level's
+// constant H comes from the precompute.
 // GENERIC: any pattern K (four lanes per point, CH / 4 points per chunk) on
 // uint8 levels or (PIX = float) the floating-point Gaussian pyramid; 2: K up to
 // kMaxSlotPattern, the templates in registers and the levels in LDS tiles like
@@ -776,12 +776,13 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
         if (l == 0) tile0 = tile, at0 = true;
       }
       pr.ok = can & (vb != 0);
-      float hinv[6];  // fixed H: the lane's row of the level's H^-1
+      float hinv[6], hlo[6];  // fixed H: the lane's row of the level's H^-1, in two floats
       int hbad = 0;
       if constexpr (FIXED) {
         const FixedH* fh = a.ref.fixed + l;
 #pragma unroll
-        for (int j = 0; j < 6; ++j) hinv[j] = gload(fh->inv + 6 * min(li, 5) + j);
+        for (int j = 0; j < 6; ++j)
+          hinv[j] = gload(fh->inv + 6 * min(li, 5) + j), hlo[j] = gload(fh->inv_lo + 6 * min(li, 5) + j);
         hbad = gload(&fh->bad);
       }
       bool converged = false;
@@ -842,9 +843,15 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
         Pose delta, step = 0;
         if constexpr (FIXED) {
           bad = hbad != 0;
-          const float b = tot.row[6];
-          delta = fmaf(hinv[0], row_bcast<0>(b), fmaf(hinv[1], row_bcast<1>(b), hinv[2] * row_bcast<2>(b))) +
-                  fmaf(hinv[3], row_bcast<3>(b), fmaf(hinv[4], row_bcast<4>(b), hinv[5] * row_bcast<5>(b)));
+          const float b[6] = {row_bcast<0>(tot.row[6]), row_bcast<1>(tot.row[6]), row_bcast<2>(tot.row[6]),
+                              row_bcast<3>(tot.row[6]), row_bcast<4>(tot.row[6]), row_bcast<5>(tot.row[6])};
+          float s0 = hlo[0] * b[0], s1 = hlo[3] * b[3];  // two chains, the small terms first
+          s0 = fmaf(hlo[1], b[1], s0), s1 = fmaf(hlo[4], b[4], s1);
+          s0 = fmaf(hlo[2], b[2], s0), s1 = fmaf(hlo[5], b[5], s1);
+          s0 = fmaf(hinv[2], b[2], s0), s1 = fmaf(hinv[5], b[5], s1);
+          s0 = fmaf(hinv[1], b[1], s0), s1 = fmaf(hinv[4], b[4], s1);
+          s0 = fmaf(hinv[0], b[0], s0), s1 = fmaf(hinv[3], b[3], s1);
+          delta = s0 + s1;
         } else {
           Pose row[7];
 #pragma unroll

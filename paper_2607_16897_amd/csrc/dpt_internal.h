@@ -44,7 +44,9 @@ struct FixedH {
   double H[21];    // upper triangle, tri() order
   float L[21];     // factor L(i, j), i >= j, stored at tri(j, i)
   float invd[6];   // 1 / L(j, j)
-  float inv[36];   // H^-1, row-major (the cooperative track's solve: one dot product per row)
+  // H^-1, row-major, as the sum of two floats (the cooperative track's solve: one
+  // dot product per row)
+  float inv[36], inv_lo[36];
   int32_t bad;     // 1: a pivot <= 1e-6 of the largest diagonal entry (not positive definite)
   int32_t pad;
 };
@@ -330,7 +332,7 @@ hipError_t launch_backproject(const BackprojectArgs& a, hipStream_t s);
 hipError_t launch_precompute_batch(const PrecomputeArgs* d_args, int n_ref, int max_samples, int K, int max_levels,
                                    hipStream_t s);
 hipError_t launch_backproject_batch(const BackprojectArgs* d_args, int n_maps, int max_n, hipStream_t s);
-// Fixed-H mode: per-level H and its factor from a finished precompute (a.fixed, a.hpart set).
+// Fixed-H mode: per-level H, its factor and its inverse from a finished precompute (a.fixed, a.hpart set).
 hipError_t launch_fixed_h(const PrecomputeArgs& a, hipStream_t s);
 hipError_t launch_fixed_h_batch(const PrecomputeArgs* d_args, int n_ref, int max_n, int max_levels, hipStream_t s);
 hipError_t launch_track(const TrackArgs& a, hipStream_t s);
