@@ -481,7 +481,6 @@ __global__ __launch_bounds__(kFuseThreads) void conv_net_fused(FusedIO io, const
   __syncthreads();
   if constexpr (TRAIN) stage_weights<9 * kC[3] * kTRow[3] * 2>(PbT + trow_off(3), at(R::kT3));
   store_act<4, N4>(a4, io.act[4] + (size_t)b * N4);
-  if (!TRAIN && !io.out) return;
   if (t < 64) {
     float v = 0.f;
 #pragma unroll
@@ -896,7 +895,6 @@ struct dpt_cnn {
   int step = 0;
   float* h_buf = nullptr;  // pinned
   float* h_buf_dev = nullptr;  // its address on the device
-  size_t partial_floats = 0;
   ~dpt_cnn() {
     for (void* p : {(void*)P, (void*)G, (void*)M, (void*)V, (void*)Pb, (void*)PbT, (void*)out, (void*)tgt, (void*)sqerr,
                     (void*)fcg, (void*)partial, (void*)pairs, (void*)d_lv})
@@ -930,26 +928,16 @@ size_t max_partial(int max_batch) {
   return n;
 }
 
-// The weight gradients' slots for B samples, one layer after the other in `partial`.
-size_t partial_floats(int B, size_t (&at)[4]) {
-  size_t n = 0;
-  for (int l = 0; l < 4; ++l) {
-    at[l] = n;
-    n += (size_t)wgrad_slots(l, B) * kC[l + 1] * npad(l);
-  }
-  return n;
-}
-
 // Weight gradients, their sums with the FC gradients' and the loss's, and (lr > 0) Adam.
 hipError_t update(dpt_cnn* c, int B, float lr, float c1, float c2) {
-  size_t at[4];
-  partial_floats(B, at);
   WgradIO w{};
   UpdateIO u{};
   int blocks = 0;
+  float* partial = c->partial;  // one layer's slots after the other
   for (int l = 0; l < 4; ++l) {
-    w.act[l] = c->act[l], w.dz[l] = c->dz[l + 1], w.partial[l] = c->partial + at[l];
-    u.partial[l] = c->partial + at[l], u.slots[l] = wgrad_slots(l, B);
+    w.act[l] = c->act[l], w.dz[l] = c->dz[l + 1];
+    u.partial[l] = w.partial[l] = partial, u.slots[l] = wgrad_slots(l, B);
+    partial += (size_t)u.slots[l] * kC[l + 1] * npad(l);
     blocks += u.slots[l];
   }
   w.B = B;
@@ -1002,11 +990,10 @@ int dpt_cnn_create(int32_t max_batch, void* hip_stream, dpt_cnn** out) {
     const size_t e = B * kHs[l] * kWs[l] * kC[l];
     ok = hipMalloc(&c->act[l], e * 2) == hipSuccess && hipMalloc(&c->dz[l], e * 4) == hipSuccess;
   }
-  c->partial_floats = max_partial(max_batch);
   ok = ok && hipMalloc(&c->out, B * kOut * 4) == hipSuccess && hipMalloc(&c->tgt, B * kOut * 4) == hipSuccess &&
        hipMalloc(&c->sqerr, B * kOut * 4) == hipSuccess &&
        hipMalloc(&c->fcg, B * (size_t)(c->o.total - c->o.fw1) * 4) == hipSuccess &&
-       hipMalloc(&c->partial, c->partial_floats * 4) == hipSuccess &&
+       hipMalloc(&c->partial, max_partial(max_batch) * 4) == hipSuccess &&
        hipMalloc(&c->pairs, B * 2 * kH0 * kW0) == hipSuccess && hipMalloc(&c->d_lv, 2 * B * sizeof(void*)) == hipSuccess &&
        hipHostMalloc(&c->h_buf, std::max(n, B * kOut) * 4 + 64) == hipSuccess &&
        hipHostGetDevicePointer((void**)&c->h_buf_dev, c->h_buf, 0) == hipSuccess;

@@ -365,30 +365,7 @@ __device__ __forceinline__ void pyramid_tile64v(const uint8_t* __restrict__ src,
   pyramid_tile64v_at(src, pitch, dst, g, blockIdx.x * 64, blockIdx.y * 64, true);
 }
 
-// ---------------------------------------------------------------- block scans / reductions
-
-// Exclusive prefix sum of one int per thread over a 1024-thread workgroup.
-// `wsum` is 16 ints of LDS.  Returns the prefix; *total gets the block sum.
-__device__ __forceinline__ int block_exclusive_scan(int x, int* wsum, int* total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  int inc = x;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    int y = __shfl_up(inc, d, 64);
-    if (lane >= d) inc += y;
-  }
-  if (lane == 63) wsum[wave] = inc;
-  __syncthreads();
-  int base = 0, tot = 0;
-  for (int w = 0; w < nw; ++w) {
-    int v = wsum[w];
-    base += (w < wave) ? v : 0;
-    tot += v;
-  }
-  __syncthreads();
-  *total = tot;
-  return base + inc - x;
-}
+// ---------------------------------------------------------------- reductions
 
 // Row rotation within 16 lanes (DPP row_ror:K), a VALU operand modifier.
 template <int K>
@@ -462,28 +439,6 @@ __device__ __forceinline__ void block_reduce32(float (&a)[32], float* scratch, f
   if (threadIdx.x < 32) {
     float s = 0.0f;
     for (int w = 0; w < nw; ++w) s += scratch[w * 32 + threadIdx.x];
-    out[threadIdx.x] = s;
-  }
-  __syncthreads();
-}
-
-// As block_reduce32, with Kahan-compensated summation across the waves.
-__device__ __forceinline__ void block_reduce32_kahan(float (&a)[32], float* scratch, float* out) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  wave_reduce32(a);
-  if ((lane & 15) == 0) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) scratch[wave * 32 + 8 * (lane >> 4) + j] = a[j];
-  }
-  __syncthreads();
-  if (threadIdx.x < 32) {
-    float s = 0.0f, c = 0.0f;
-    for (int w = 0; w < nw; ++w) {
-      const float y = scratch[w * 32 + threadIdx.x] - c;
-      const float t = s + y;
-      c = (t - s) - y;
-      s = t;
-    }
     out[threadIdx.x] = s;
   }
   __syncthreads();
@@ -956,18 +911,11 @@ __device__ __forceinline__ bool load_geometry_once(const TrackArgs& a, int i, PR
 // camera or a pattern position outside the level) runs the same instructions
 // with its taps at the level's first pixels and its sums and counts masked to
 // zero, so no exit path has to materialise a zeroed accumulator.
-// GLOBAL_IMG: `img` is device global memory (loads compile to global_load);
-// otherwise it may be LDS.
-// NV = 32: robust mode, the kSlot* layout.  NV = kFixSlots: fixed-H mode, no
-// weights (w = 1, cost r^2 / 2) and only b, E and the counts (kFix* layout).
-template <bool COST_ONLY, bool GLOBAL_IMG, class PR, int NV = 32>
+// `img` is the level in global memory or its copy in LDS.
 __device__ __forceinline__ void accumulate_point(const TrackArgs& a, const PatRegs& pat, const LevelGeom& g,
                                                  const uint8_t* __restrict__ img, const float* T,
-                                                 const PR& pr, float (&acc)[NV]) {
-  constexpr bool FIXED = NV == kFixSlots;
-  static_assert(NV == 32 || FIXED, "slot layout");
-  constexpr int sE = FIXED ? kFixE : kSlotE, sN = FIXED ? kFixN : kSlotN, sP = FIXED ? kFixPts : kSlotPts;
-  const float kH = FIXED ? 0.0f : a.huber_k;
+                                                 const PointRegs& pr, float (&acc)[32]) {
+  const float kH = a.huber_k;
   float X, Y, Z;
   transform(T, pr.X0, pr.Y0, pr.Z0, X, Y, Z);
   float u, v;
@@ -985,14 +933,8 @@ __device__ __forceinline__ void accumulate_point(const TrackArgs& a, const PatRe
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     const int off = ((q0.iv + (int)pat.dy[k]) * W + q0.iu + (int)pat.dx[k]) & -(int)ok;  // masked, not branched
-    if constexpr (GLOBAL_IMG) {
-      const __attribute__((address_space(1))) uint8_t* p =
-          (const __attribute__((address_space(1))) uint8_t*)img + off;
-      t00[k] = p[0], t10[k] = p[1], t01[k] = p[W], t11[k] = p[W + 1];
-    } else {
-      const uint8_t* p = img + off;
-      t00[k] = p[0], t10[k] = p[1], t01[k] = p[W], t11[k] = p[W + 1];
-    }
+    const uint8_t* p = img + off;
+    t00[k] = p[0], t10[k] = p[1], t01[k] = p[W], t11[k] = p[W + 1];
   }
   // Phase 2: residuals, Huber weights and the point's sums.  The interpolation
   // repeats the precompute's arithmetic exactly.
@@ -1006,46 +948,33 @@ __device__ __forceinline__ void accumulate_point(const TrackArgs& a, const PatRe
     const float w = hub ? kH * __builtin_amdgcn_rcpf(ar) : 1.0f;  // v_rcp_f32, 1 ulp
     const float rho = hub ? kH * (ar - 0.5f * kH) : 0.5f * r * r;
     E += rho;
-    if (!COST_ONLY) {
-      const float gx = pr.gx(k), gy = pr.gy(k);
-      if (FIXED) {
-        v0 = fmaf(gx, r, v0);
-        v1 = fmaf(gy, r, v1);
-      } else {
-        const float wgx = w * gx, wgy = w * gy;
-        m00 = fmaf(wgx, gx, m00);
-        m01 = fmaf(wgx, gy, m01);
-        m11 = fmaf(wgy, gy, m11);
-        v0 = fmaf(wgx, r, v0);
-        v1 = fmaf(wgy, r, v1);
-      }
-    }
+    const float gx = pr.gx(k), gy = pr.gy(k);
+    const float wgx = w * gx, wgy = w * gy;
+    m00 = fmaf(wgx, gx, m00);
+    m01 = fmaf(wgx, gy, m01);
+    m11 = fmaf(wgy, gy, m11);
+    v0 = fmaf(wgx, r, v0);
+    v1 = fmaf(wgy, r, v1);
   }
-  acc[sE] += ok ? E : 0.0f;
-  acc[sN] += ok ? 8.0f : 0.0f;
-  acc[sP] += ok ? 1.0f : 0.0f;
-  if (COST_ONLY) return;
+  acc[kSlotE] += ok ? E : 0.0f;
+  acc[kSlotN] += ok ? 8.0f : 0.0f;
+  acc[kSlotPts] += ok ? 1.0f : 0.0f;
   v0 = ok ? v0 : 0.0f, v1 = ok ? v1 : 0.0f;
   const float iz = pr.iz, xp = pr.xp, yp = pr.yp;
   const float au[6] = {-g.fx * xp * yp, g.fx * fmaf(xp, xp, 1.0f), -g.fx * yp, g.fx * iz, 0.0f, -g.fx * xp * iz};
   const float av[6] = {-g.fy * fmaf(yp, yp, 1.0f), g.fy * xp * yp, g.fy * xp, 0.0f, g.fy * iz, -g.fy * yp * iz};
-  if constexpr (FIXED) {
+  m00 = ok ? m00 : 0.0f, m01 = ok ? m01 : 0.0f, m11 = ok ? m11 : 0.0f;
+  int q = 0;
 #pragma unroll
-    for (int r = 0; r < 6; ++r) acc[kFixB + r] -= fmaf(au[r], v0, av[r] * v1);
-  } else {
-    m00 = ok ? m00 : 0.0f, m01 = ok ? m01 : 0.0f, m11 = ok ? m11 : 0.0f;
-    int q = 0;
+  for (int r = 0; r < 6; ++r) {
+    const float ma = fmaf(m00, au[r], m01 * av[r]);
+    const float mc = fmaf(m01, au[r], m11 * av[r]);
 #pragma unroll
-    for (int r = 0; r < 6; ++r) {
-      const float ma = fmaf(m00, au[r], m01 * av[r]);
-      const float mc = fmaf(m01, au[r], m11 * av[r]);
-#pragma unroll
-      for (int c = r; c < 6; ++c) {
-        acc[q] = fmaf(ma, au[c], fmaf(mc, av[c], acc[q]));
-        ++q;
-      }
-      acc[kSlotB + r] -= fmaf(au[r], v0, av[r] * v1);
+    for (int c = r; c < 6; ++c) {
+      acc[q] = fmaf(ma, au[c], fmaf(mc, av[c], acc[q]));
+      ++q;
     }
+    acc[kSlotB + r] -= fmaf(au[r], v0, av[r] * v1);
   }
 }
 
