@@ -828,8 +828,8 @@ __global__ __launch_bounds__(256) void update_kernel(UpdateIO io) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int k = k0 + j * PARTS;
-        const float y = gload(v + (size_t)min(k, K - 1) * stride);
-        x[j] = k < K ? y : 0.f;
+        x[j] = 0.f;
+        if (k < K) x[j] = gload(v + (size_t)k * stride);
       }
       chain += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
     }
