@@ -20,6 +20,7 @@
 // suffices and the result is reproducible.  Waits are bounded: a chunk that
 // polls longer than `spin_limit` times gives up and reports a timeout instead
 // of hanging.
+#include <atomic>
 #include <climits>
 #include <cstring>
 #include <type_traits>
@@ -507,15 +508,15 @@ hipError_t read_cycle_profile(uint64_t* host, int n_slots, bool reset) {
 // ---------------------------------------------------------------- LDS tiles of the current level
 
 // Bytes of a level a workgroup stages in LDS (every kernel with its templates in
-// registers): levels of up to this size whole, larger ones as the band of rows
-// its points' taps span.  With the kernel's own 3 to 4 KB a workgroup stays within
-// 64 KB, so two share a compute unit's 160 KB: the co-residency that the launches
-// count on (coop_max_blocks) holds for every variant.  A map in index order gives
-// a workgroup a band of few rows, and a larger tile only copies more: 144 KB (one
-// workgroup per compute unit) took 396 us for a window of nine 752x480 frames of
-// 2000 points where 60 KB takes 383, 51.2 against 49.7 us for one 640x480 frame of
-// 500; a shuffled map, whose bands span the level, 68.2 against 69.5 us a frame.
-constexpr int kTileBytes = 60 * 1024;
+// registers): levels of up to the small tile's size whole, larger ones as the band of
+// rows its points' taps span, cut to the tile.  With the small tile and the kernel's
+// own 3 to 4 KB a workgroup stays within 64 KB, so two share a compute unit's 160 KB;
+// with the large one a workgroup has a compute unit to itself (coop_large_tile).
+// Maps in index order have bands of few rows: a level is not copied whole because the
+// large tile would hold it (a window of nine 752x480 frames of 2000 points 393 us so,
+// 381 by bands).  A shuffled map's bands span the level: 71 us a frame with the large
+// tile, 74 with the small one (2000 points, one thread each).
+constexpr int kTileSmall = 60 * 1024, kTileLarge = 144 * 1024;
 constexpr int kTilePad = 16;  // the last pair of words read past the last byte
 // Rows kept around the band at the level's start pose: the pose moves during the
 // level's iterations.  Points whose taps leave the band are read from global
@@ -523,10 +524,10 @@ constexpr int kTilePad = 16;  // the last pair of words read past the last byte
 constexpr int kBandMargin = 4;
 
 // Whether a pattern's taps (a row and a column past its last sample, read as pairs
-// of words) fit the tile's allocation from anywhere in its first granule, at a
+// of words) fit either tile's allocation from anywhere in its first granule, at a
 // level of W bytes a row.
 __device__ __forceinline__ bool tile_spans(const PatRegs& pat, int W) {
-  return ((int)pat.dy_max - (int)pat.dy_min + 1) * W + (int)pat.dx_max - (int)pat.dx_min + 16 + 8 <= kTileBytes + kTilePad;
+  return ((int)pat.dy_max - (int)pat.dy_min + 1) * W + (int)pat.dx_max - (int)pat.dx_min + 16 + 8 <= kTileSmall + kTilePad;
 }
 
 // Stage level g of the current frame (img = its first byte) in the workgroup's
@@ -540,11 +541,11 @@ __device__ __forceinline__ bool tile_spans(const PatRegs& pat, int W) {
 template <int NW, class PIX, class PR>
 __device__ __forceinline__ Tile8 stage_tile(const IterParams& a, const PatRegs& pat, const LevelGeom& g,
                                             const PIX* img, const float* T, const PR& pr, bool can,
-                                            uint8_t* tile_mem, int* sh_band) {
+                                            uint8_t* tile_mem, bool large, int* sh_band) {
   const int W = g.W, H = g.H, row = W * (int)sizeof(PIX);
-  const int rows_fit = (kTileBytes - 32) / row;
+  const int rows_fit = ((large ? kTileLarge : kTileSmall) - 32) / row;
   int lo = 0, hi = H - 1;
-  if (rows_fit < H) {
+  if (row * H > kTileSmall - 32) {
     float X, Y, Z;
     transform(T, pr.X0, pr.Y0, pr.Z0, X, Y, Z);
     const float iz = __builtin_amdgcn_rcpf(Z);
@@ -623,7 +624,7 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
                                                            const StartSlot* __restrict__ start,
                                                            TrackOut* __restrict__ out_ring, int slot, int n_out,
                                                            int n_frames, uint32_t seq0, uint32_t tag_base,
-                                                           int spin_limit) {
+                                                           int spin_limit, int large_tile) {
   static_assert(!(MIXED && FIXED), "the fixed-H mode computes in FP32");
   static_assert(!(MIXED && GENERIC) && (GENERIC || std::is_same<PIX, uint8_t>::value), "variant");
   static_assert(LPP == 1 || (LPP == 2 && !GENERIC), "two threads per point: the 8-pixel kernels");
@@ -645,7 +646,7 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
   __shared__ __align__(16) float sh_red[NW * kWaveWords];
   __shared__ float sh_grp[GENERIC ? CH : 1];  // the whole-workgroup exchange of many-chunk streams
   __shared__ int sh_band[2 * (CH / 64)];
-  extern __shared__ __align__(16) uint8_t sh_tile[];  // kTileBytes + kTilePad (TILED), else none
+  extern __shared__ __align__(16) uint8_t sh_tile[];  // the tile and kTilePad (TILED), else none
   __shared__ __align__(16) StartSlot sh_start;
   const int2 w = work[blockIdx.x];
   if (w.x < 0) return;  // padding slot of the XCD-aware work list
@@ -770,7 +771,7 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
       } else {
         load_template(a, e, sub, pr);
         sample_offsets(g.W, offs);
-        tile = stage_tile<NW>(ip, pregs, g, img, T, pr, can, sh_tile, sh_band);
+        tile = stage_tile<NW>(ip, pregs, g, img, T, pr, can, sh_tile, large_tile != 0, sh_band);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         if (l == 0) tile0 = tile, at0 = true;
@@ -1010,8 +1011,15 @@ static const void* coop_fn(int variant) {
 // Whether a variant stages its levels in LDS tiles.
 static bool tiled(int variant) { return !(variant & kCoopGeneric) || (variant & kCoopSlots); }
 
-// Dynamic LDS of a launch: what the co-residency is counted with.
-static size_t coop_tile_lds(int variant) { return tiled(variant) ? kTileBytes + kTilePad : 0; }
+// Dynamic LDS that the co-residency is counted with.
+static size_t coop_tile_lds(int variant) { return tiled(variant) ? kTileSmall + kTilePad : 0; }
+
+// Whether a launch takes the large tile: at most eight chunks on an XCD (work items
+// are dealt to the eight XCDs in turn).  Four launches at once, as many as the hardware
+// queues of a process run, then still fit an XCD's 32 compute units with any mix of
+// tiles: k of them with the large one hold 8 k units, and the others' 16 chunks each
+// share the rest in twos.
+static bool coop_large_tile(int variant, int n_work) { return tiled(variant) && n_work <= 64; }
 
 // Co-resident workgroups per CU: the least over every variant at this chunk size.
 template <int CH>
@@ -1088,9 +1096,23 @@ static hipError_t coop_launch_k(const CoopStream* d_streams, const int2* d_work,
   const void* fn = n_frames > 0 ? coop_fn<CH, true>(variant) : coop_fn<CH, false>(variant);
   if (!fn) return hipErrorInvalidValue;
   const bool plain = 4 * n_work <= coop_max_blocks(CH);
-  const size_t dyn = coop_tile_lds(variant);
+  int large = coop_large_tile(variant, n_work);
+  const size_t dyn = large ? kTileLarge + kTilePad : coop_tile_lds(variant);
+  if (large) {  // past the default limit: raised once per kernel and device
+    static std::atomic<bool> raised[64][2][64];  // zeroed; one array per chunk size
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+    std::atomic<bool>& r = raised[dev][n_frames > 0][variant & 63];
+    if (!r.load(std::memory_order_acquire)) {
+      if ((e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn)) != hipSuccess) return e;
+      r.store(true, std::memory_order_release);
+    }
+  }
   void* args[] = {(void*)&d_streams, (void*)&d_work,   (void*)&start,    (void*)&out_ring,   (void*)&slot,
-                  (void*)&n_out,     (void*)&n_frames, (void*)&seq0,     (void*)&tag_base,   (void*)&spin_limit};
+                  (void*)&n_out,     (void*)&n_frames, (void*)&seq0,     (void*)&tag_base,   (void*)&spin_limit,
+                  (void*)&large};
   if (plain) return hipLaunchKernel(fn, dim3(n_work), dim3(CH), args, dyn, s);
   return hipLaunchCooperativeKernel(fn, dim3(n_work), dim3(CH), args, dyn, s);
 }
