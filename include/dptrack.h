@@ -146,9 +146,9 @@ int dpt_select_points(dpt_ctx* ctx, int32_t n, int32_t margin, int32_t* host_idx
 /* For callers that cannot allocate memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid allocation): the selection of
  * dpt_select_points on a device image the caller passes, needing no context
- * and allocating nothing.  Its histograms, completion counter and per-chunk
- * counts live in a static device array of the library (about 36 KB per GPU,
- * held until the process ends) instead of context memory; the call only
+ * and allocating nothing.  Its histograms and the chunks' counts live in a
+ * static device array of the library (about 11 KB per GPU, held until the
+ * process ends) instead of context memory; the call only
  * enqueues kernels on hip_stream (a kernel clears the array first) and never
  * waits.  img: device uint8 image width x height, rows `pitch` bytes apart
  * (width <= pitch < 2^31); idx: device int32[n], receives min(n, candidates)

@@ -7,12 +7,12 @@
 // convolution weights are BF16 in NHWC / [co][ky][kx][ci] layouts; the
 // forward convolutions are implicit GEMMs on the matrix cores
 // (v_mfma_f32_16x16x16bf16_1k, FP32 accumulation) with bias and ReLU fused in
-// the epilogue.  The backward convolutions are implicit GEMMs on the same
-// instruction: the data gradient per stride-parity class of the input pixels
-// (only the taps that reach a class), the weight gradient as dZ^T Xcol split
-// over samples, with the bias gradient as a column of ones; gradients
-// flowing between layers are stored in BF16, split reductions are summed in a
-// fixed order.  Pooling, the FC layers, the loss and Adam run on the vector
+// the epilogue.  The backward convolutions are implicit GEMMs too: the data
+// gradient per stride-parity class of the input pixels (only the taps that reach a
+// class) on the same instruction, the weight gradient as dZ^T Xcol
+// (v_mfma_f32_16x16x32_bf16) split over samples, with the bias gradient as a column
+// of ones; gradients flowing between layers are stored in BF16, split reductions are
+// summed in a fixed order.  Pooling, the FC layers, the loss and Adam run on the vector
 // units; master weights and Adam moments are FP32.
 #include <cmath>
 #include <cstring>
@@ -404,7 +404,7 @@ static_assert(FuseLds::kHeadEnd <= FuseLds::kB && FuseLds::kT2 <= FuseLds::kHead
 // latency bounds them: each layer's weights are on their way while the layer
 // before is computed, and 1024 threads share a layer's tiles.  64 pairs with the
 // proposal: 27 us with unpadded rows and each layer's weights waited for, now 16.2;
-// the training pass of 256 pairs: 97 us as five launches, 51.5 in one, now 39.
+// the training pass of 256 pairs: 97 us as five launches, 51.5 in one, now 35.
 template <bool TRAIN>
 __global__ __launch_bounds__(kFuseThreads) void conv_net_fused(FusedIO io, const uint16_t* __restrict__ Pb,
                                                                const uint16_t* __restrict__ PbT,

@@ -1,7 +1,7 @@
 // Cooperative multi-workgroup track: every camera stream's map is split into
-// chunks of CH points, one workgroup per chunk, one thread per point, and all
-// chunks of all streams run in one cooperative (co-resident) launch that
-// covers every level and iteration of the frame.
+// chunks, one workgroup each, with one or two threads per point (four for patterns
+// other than the 8-pixel one), and all chunks of all streams run in one co-resident
+// launch that covers every level and iteration of the frame.
 //
 // Per Gauss-Newton iteration the chunks of a stream exchange their 32 partial
 // sums through a double-buffered global array.  Each partial is one 64-bit
@@ -15,8 +15,8 @@
 // about half the round trip of the second; every eighth poll reads the second
 // copies instead, so a chunk that the dispatcher placed on another XCD is still
 // seen.  Every chunk then sums the partials in one fixed order
-// and every thread solves the 6x6 system itself: all threads of all chunks of
-// a stream compute bitwise-identical poses, so one exchange per iteration
+// and solves the 6x6 system across the lanes of every 16-lane row: all rows of all
+// chunks of a stream compute bitwise-identical poses, so one exchange per iteration
 // suffices and the result is reproducible.  Waits are bounded: a chunk that
 // polls longer than `spin_limit` times gives up and reports a timeout instead
 // of hanging.

@@ -1000,8 +1000,8 @@ struct __attribute__((packed)) PixPair<float> {
 
 // The bytes of the current level a workgroup holds in LDS: rows lo..hi
 // (inclusive), each W bytes, byte (r, x) of the level at offset
-// delta + (r - lo) * W + x.  spans: the tile's allocation is long enough for a
-// pattern of the level whose first row is the tile's.
+// delta + (r - lo) * W + x.  spans: the allocation is long enough for a pattern of
+// the level whose first row is the tile's.
 struct Tile8 {
   const __attribute__((address_space(3))) uint8_t* lds;
   int lo, hi, delta;
@@ -1071,9 +1071,10 @@ __device__ __forceinline__ PointSums sample_point(const IterParams& a, const Pat
   const int iu = q0.iu, iv = q0.iv, W = g.W;
   // Every usable point of the wave inside the tile?  An unusable one reads from
   // the tile position of a pattern whose top-left sample sits at the tile's first
-  // byte, masked below; a tile too short for that (8 samples 32 rows apart at a
-  // width of 2000, never the default pattern) holds no usable point either.  Other
-  // patterns' unusable points read the tile's first bytes.
+  // byte, masked below; where the small tile is too short for that (8 samples 32
+  // rows apart at a width of 2000, never the default pattern), and so holds no usable
+  // point either, every point reads global memory.  Other patterns' unusable points
+  // read the tile's first bytes.
   const bool in_tile = !ok | ((iv + (int)pat.dy_min >= tile.lo) & (iv + (int)pat.dy_max + 1 <= tile.hi));
   const bool use_tile = (QUAD || tile.spans) && __all(in_tile);
   PointSums s = {};

@@ -416,7 +416,8 @@ SelJob make_sel_job(const uint8_t* img, int32_t W, int32_t H, int32_t margin, in
 // The pipeline for one image (many == nullptr) or for n_img images whose
 // chunk counts are at most G_max.  The write pass leaves the histograms
 // cleared, so sel_clear runs only where an image has no candidates (its count
-// must still be written); the scratch starts zeroed (select_scratch_init).
+// must still be written); the coarse histogram starts zeroed (a fresh scratch by
+// its owner).
 static hipError_t run_select(const SelJob& one, const SelJob* many, int n_img, int G_max, int chunk, bool any_empty,
                              hipStream_t s) {
   // Histogram workgroups: as many as have a group of four per thread, but at most
@@ -455,7 +456,7 @@ hipError_t launch_select_batch(const SelJob* d_jobs, int n_img, int G_max, int c
 
 // ---------------------------------------------------------------- selection without allocation
 
-// Histograms, completion counter and per-chunk counts of one selection of an
+// Histograms, coarse bucket and the chunks' words of one selection of an
 // image of up to kNoAllocSelectPixels pixels, for callers that cannot allocate.
 // Every device holds its own copy for the life of the process; all calls on a
 // device share it (calls that overlap on one device race).
@@ -496,8 +497,8 @@ hipError_t launch_select_noalloc(const uint8_t* img, int32_t W, int32_t H, int64
   const int chunk = select_chunk((int64_t)W * H);
   SelJob j = make_sel_job(img, W, H, margin, n, idx, count, sc, chunk);
   j.g.pitch = (int32_t)pitch;
-  // the histograms and the completion counter start at zero: cleared by a
-  // kernel (no memset node, so the call can also be captured into a graph);
+  // the histograms start at zero: cleared by a kernel (no memset node, so the
+  // call can also be captured into a graph);
   // sel_clear also writes the count of an image without candidates
   hipLaunchKernelGGL(sel_clear, dim3(1, 1), dim3(kSelThreads), 0, s, j, nullptr);
   if ((e = hipGetLastError()) != hipSuccess) return e;
