@@ -353,6 +353,7 @@ struct dpt_ctx {
   RefBank phys[2];             // the banks' buffers by identity (bank 0: allocated at creation)
   int32_t bank = 0;            // which of phys[] the fields hold
   int32_t bank_n[2] = {0, 0};  // points committed to each bank
+  bool in_order = false;       // the committed map lists its points by pixel index (selected, not given)
   hipEvent_t ev_read[2] = {nullptr, nullptr};  // context stream: past the last track that read bank b
   hipEvent_t ev_ready = nullptr;               // reference stream: the last committed update done
   bool update_open = false;    // a reference update has started writing the fields' bank
@@ -746,11 +747,12 @@ PrecomputeArgs precompute_args(const dpt_ctx* c, const float* P, int32_t n, cons
   return a;
 }
 
-int commit_reference(dpt_ctx* c, int32_t n, const double T_rw[16], bool record = true) {
+int commit_reference(dpt_ctx* c, int32_t n, const double T_rw[16], bool in_order, bool record = true) {
   std::memcpy(c->T_rw, T_rw, sizeof c->T_rw);
   c->n_points = n;
   c->have_ref = true;
   c->bank_n[c->bank] = n;
+  c->in_order = in_order;
   if (c->rstream && !c->batch_owned) {
     if (record) HIP_TRY(hipEventRecord(c->ev_ready, c->rstream));
     c->commit_pending = true;
@@ -768,11 +770,11 @@ int check_update_open(const dpt_ctx* c) {
 }
 
 // IC precompute of the reference cache from n device points P at T_rw.
-int precompute_reference(dpt_ctx* c, const float* P, int32_t n, const double T_rw[16]) {
+int precompute_reference(dpt_ctx* c, const float* P, int32_t n, const double T_rw[16], bool in_order) {
   const PrecomputeArgs a = precompute_args(c, P, n, T_rw);
   HIP_TRY(launch_precompute(a, ref_stream(c)));
   if (c->prm.flags & DPT_FLAG_FIXED_H) HIP_TRY(launch_fixed_h(a, ref_stream(c)));
-  return commit_reference(c, n, T_rw);
+  return commit_reference(c, n, T_rw, in_order);
 }
 
 }  // namespace
@@ -799,7 +801,7 @@ int dpt_set_reference_points(dpt_ctx* c, const float* xyz, int32_t n, const doub
     HIP_TRY(hipEventRecord(c->ev_pts, ref_stream(c)));
     P = c->pts;
   }
-  return precompute_reference(c, P, n, T_rw);
+  return precompute_reference(c, P, n, T_rw, false);
 }
 
 int dpt_set_reference_from_depth(dpt_ctx* c, int32_t n, int32_t margin, const float* depth, int64_t depth_pitch,
@@ -842,7 +844,7 @@ int dpt_set_reference_from_depth(dpt_ctx* c, int32_t n, int32_t margin, const fl
   for (int j = 0; j < 12; ++j) b.T_rw[j] = T_rw[j];
   b.P = c->pts;
   HIP_TRY(launch_backproject(b, rs));
-  return precompute_reference(c, c->pts, n, T_rw);
+  return precompute_reference(c, c->pts, n, T_rw, true);
 }
 
 }  // extern "C"
@@ -1122,7 +1124,7 @@ int enqueue_coop(dpt_ctx* c, int mode, const double* T_cw_init, dpt_result* out)
   fill_start(c, mode, T_cw_init, c->eng.start(slot), c->d_prop);
   int ps = -1;
   if (c->prof) HIP_TRY(c->prof_trk.begin(c->stream, &ps));
-  HIP_TRY(c->eng.launch(c->spin_limit, slot));
+  HIP_TRY(c->eng.launch(c->spin_limit, slot, c->in_order));
   if (c->prof) HIP_TRY(c->prof_trk.end(c->stream, ps));
   c->pending.emplace_back(slot, out);
   return DPT_OK;
@@ -1454,7 +1456,7 @@ int dpt_track_window_enqueue(dpt_ctx* c, const uint8_t* frames, int64_t pitch, i
     st->l0_stride = sst;
   }
   if (c->prof) HIP_TRY(c->prof_trk.begin(c->stream, &ps));
-  HIP_TRY(c->eng.launch(c->spin_limit, slot, n_frames));
+  HIP_TRY(c->eng.launch(c->spin_limit, slot, c->in_order, n_frames));
   if (c->prof) HIP_TRY(c->prof_trk.end(c->stream, ps));
   for (int f = 0; f < n_frames; ++f) c->pending.emplace_back((slot + f) % kRing, out + f);
   c->slot_next = (slot + n_frames) % kRing;
@@ -1762,6 +1764,11 @@ int batch_winjobs(dpt_batch* b, int bank, WinJob** out) {
   return DPT_OK;
 }
 
+// Whether every stream's map lists its points by pixel index.
+bool maps_in_order(const dpt_batch* b) {
+  return std::all_of(b->ctx.begin(), b->ctx.end(), [](const dpt_ctx* c) { return c->in_order; });
+}
+
 int batch_chunks(const dpt_batch* b, int s) {
   const dpt_ctx* c = b->ctx[s];
   const int n = std::max(c->n_points, std::max(c->bank_n[0], c->bank_n[1]));  // the chunks cover both banks
@@ -1954,7 +1961,7 @@ int batch_enqueue_coop(dpt_batch* b, const int* modes, const double* T_cw_init, 
   }
   int ps = -1;
   if (b->prof) HIP_TRY(b->prof_trk.begin(b->stream, &ps));
-  for (CoopEngine* g : b->groups) HIP_TRY(g->launch(b->spin_limit, slot));
+  for (CoopEngine* g : b->groups) HIP_TRY(g->launch(b->spin_limit, slot, maps_in_order(b)));
   if (b->prof) HIP_TRY(b->prof_trk.end(b->stream, ps));
   b->pending.emplace_back(slot, out);
   return DPT_OK;
@@ -2321,7 +2328,7 @@ int dpt_batch_set_reference_from_depth_all(dpt_batch* b, const int32_t* n_points
   if (b->ctx[0]->prm.flags & DPT_FLAG_FIXED_H) HIP_TRY(launch_fixed_h_batch(dp, b->n, max_n, max_levels, rs));
   for (int s = 0; s < b->n; ++s) {
     if (b->ctx[s]->n_points != n_points[s]) b->groups_dirty = true;
-    const int e = commit_reference(b->ctx[s], n_points[s], T_rw + 16 * s);
+    const int e = commit_reference(b->ctx[s], n_points[s], T_rw + 16 * s, true);
     if (e != DPT_OK) return e;
   }
   return batch_close_update(b);
@@ -2508,7 +2515,7 @@ int dpt_batch_track_window_enqueue(dpt_batch* b, const uint8_t* const* frames, c
     }
   }
   if (b->prof) HIP_TRY(b->prof_trk.begin(b->stream, &ps));
-  for (CoopEngine* g : b->groups) HIP_TRY(g->launch(b->spin_limit, slot, n_frames));
+  for (CoopEngine* g : b->groups) HIP_TRY(g->launch(b->spin_limit, slot, maps_in_order(b), n_frames));
   if (b->prof) HIP_TRY(b->prof_trk.end(b->stream, ps));
   for (int f = 0; f < n_frames; ++f) b->pending.emplace_back((slot + f) % kRing, out + (size_t)f * b->n);
   b->slot_next = (slot + n_frames) % kRing;

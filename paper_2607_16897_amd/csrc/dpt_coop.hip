@@ -512,10 +512,8 @@ hipError_t read_cycle_profile(uint64_t* host, int n_slots, bool reset) {
 // rows its points' taps span, cut to the tile.  With the small tile and the kernel's
 // own 3 to 4 KB a workgroup stays within 64 KB, so two share a compute unit's 160 KB;
 // with the large one a workgroup has a compute unit to itself (coop_large_tile).
-// Maps in index order have bands of few rows: a level is not copied whole because the
-// large tile would hold it (a window of nine 752x480 frames of 2000 points 393 us so,
-// 381 by bands).  A shuffled map's bands span the level: 71 us a frame with the large
-// tile, 74 with the small one (2000 points, one thread each).
+// A level is not copied whole because the large tile would hold it: bands took a window
+// of nine 752x480 frames of 2000 points from 393 to 381 us.
 constexpr int kTileSmall = 60 * 1024, kTileLarge = 144 * 1024;
 constexpr int kTilePad = 16;  // the last pair of words read past the last byte
 // Rows kept around the band at the level's start pose: the pose moves during the
@@ -846,13 +844,8 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
           bad = hbad != 0;
           const float b[6] = {row_bcast<0>(tot.row[6]), row_bcast<1>(tot.row[6]), row_bcast<2>(tot.row[6]),
                               row_bcast<3>(tot.row[6]), row_bcast<4>(tot.row[6]), row_bcast<5>(tot.row[6])};
-          float s0 = hlo[0] * b[0], s1 = hlo[3] * b[3];  // two chains, the small terms first
-          s0 = fmaf(hlo[1], b[1], s0), s1 = fmaf(hlo[4], b[4], s1);
-          s0 = fmaf(hlo[2], b[2], s0), s1 = fmaf(hlo[5], b[5], s1);
-          s0 = fmaf(hinv[2], b[2], s0), s1 = fmaf(hinv[5], b[5], s1);
-          s0 = fmaf(hinv[1], b[1], s0), s1 = fmaf(hinv[4], b[4], s1);
-          s0 = fmaf(hinv[0], b[0], s0), s1 = fmaf(hinv[3], b[3], s1);
-          delta = s0 + s1;
+          const auto half = [&](const float (&m)[6], int j) { return fmaf(m[j], b[j], fmaf(m[j + 1], b[j + 1], m[j + 2] * b[j + 2])); };
+          delta = (half(hinv, 0) + half(hinv, 3)) + (half(hlo, 0) + half(hlo, 3));
         } else {
           Pose row[7];
 #pragma unroll
@@ -1014,12 +1007,21 @@ static bool tiled(int variant) { return !(variant & kCoopGeneric) || (variant & 
 // Dynamic LDS that the co-residency is counted with.
 static size_t coop_tile_lds(int variant) { return tiled(variant) ? kTileSmall + kTilePad : 0; }
 
-// Whether a launch takes the large tile: at most eight chunks on an XCD (work items
-// are dealt to the eight XCDs in turn).  Four launches at once, as many as the hardware
+// Whether a launch takes the large tile.  At most eight chunks on an XCD (work items
+// are dealt to the eight XCDs in turn): four launches at once, as many as the hardware
 // queues of a process run, then still fit an XCD's 32 compute units with any mix of
 // tiles: k of them with the large one hold 8 k units, and the others' 16 chunks each
-// share the rest in twos.
-static bool coop_large_tile(int variant, int n_work) { return tiled(variant) && n_work <= 64; }
+// share the rest in twos.  Of those launches, the ones whose chunks' points span more
+// of the levels than the small tile holds: maps in no order (2000 points at 752x480
+// 73.8 us a frame, 75.8 with the small tile; 320x240 65.9, 70.6) and maps in index order
+// of so few points that a chunk's band of level 1 is past the large tile too (200 points
+// at 1280x720 53.1, 55.1).  Others wait longer for the larger copy (1111 points at
+// 641x479, fixed H, a window of nine 390 us, 382 with the small tile; 1111 at 1280x720
+// 66.1, 63.4 a frame).  band: of level 1 in bytes, the widest stream's; INT64_MAX for
+// maps in no order.
+static bool coop_large_tile(int variant, int n_work, int64_t band) {
+  return tiled(variant) && n_work <= 64 && band > kTileLarge;
+}
 
 // Co-resident workgroups per CU: the least over every variant at this chunk size.
 template <int CH>
@@ -1092,11 +1094,11 @@ int coop_max_blocks(int chunk) {
 template <int CH>
 static hipError_t coop_launch_k(const CoopStream* d_streams, const int2* d_work, int n_work, const StartSlot* start,
                                 TrackOut* out_ring, int slot, int n_out, int n_frames, uint32_t seq0, uint32_t tag_base,
-                                int variant, int spin_limit, hipStream_t s) {
+                                int variant, int64_t band, int spin_limit, hipStream_t s) {
   const void* fn = n_frames > 0 ? coop_fn<CH, true>(variant) : coop_fn<CH, false>(variant);
   if (!fn) return hipErrorInvalidValue;
   const bool plain = 4 * n_work <= coop_max_blocks(CH);
-  int large = coop_large_tile(variant, n_work);
+  int large = coop_large_tile(variant, n_work, band);
   const size_t dyn = large ? kTileLarge + kTilePad : coop_tile_lds(variant);
   if (large) {  // past the default limit: raised once per kernel and device
     static std::atomic<bool> raised[64][2][64];  // zeroed; one array per chunk size
@@ -1119,18 +1121,18 @@ static hipError_t coop_launch_k(const CoopStream* d_streams, const int2* d_work,
 
 hipError_t launch_coop_track(const CoopStream* d_streams, const int2* d_work, int n_work, const StartSlot* start,
                              TrackOut* out_ring, int slot, int n_out, int n_frames, uint32_t seq0, uint32_t tag_base,
-                             int chunk, int variant, int spin_limit, hipStream_t s) {
+                             int chunk, int variant, int64_t band, int spin_limit, hipStream_t s) {
   if (slot < 0 || slot >= kRing || n_frames < 0 || n_frames > kRing) return hipErrorInvalidValue;
   switch (chunk) {
     case 64:
       return coop_launch_k<64>(d_streams, d_work, n_work, start, out_ring, slot, n_out, n_frames, seq0, tag_base,
-                               variant, spin_limit, s);
+                               variant, band, spin_limit, s);
     case 128:
       return coop_launch_k<128>(d_streams, d_work, n_work, start, out_ring, slot, n_out, n_frames, seq0, tag_base,
-                                variant, spin_limit, s);
+                                variant, band, spin_limit, s);
     case 256:
       return coop_launch_k<256>(d_streams, d_work, n_work, start, out_ring, slot, n_out, n_frames, seq0, tag_base,
-                                variant, spin_limit, s);
+                                variant, band, spin_limit, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1248,7 +1250,7 @@ hipError_t CoopEngine::upload() {
 
 int CoopEngine::grid() const { return (int)h_work.size(); }
 
-hipError_t CoopEngine::launch(int spin_limit, int slot, int n_frames) {
+hipError_t CoopEngine::launch(int spin_limit, int slot, bool in_order, int n_frames) {
   hipError_t e;
   if (slot < 0 || slot >= kRing || n_frames < 0 || n_frames > kRing) return hipErrorInvalidValue;
   if (dirty && (e = upload()) != hipSuccess) return e;
@@ -1264,8 +1266,15 @@ hipError_t CoopEngine::launch(int spin_limit, int slot, int n_frames) {
   const uint32_t seq0 = seq_next;
   seq_next += (uint32_t)nf;
   for (int f = 0; f < nf; ++f) slot_seq[(slot + f) % kRing] = seq0 + (uint32_t)f;
+  int64_t band = in_order ? 0 : INT64_MAX;
+  for (const CoopStream& c : h_streams) {  // rows of level 1 under a chunk's points, with the tile's margins
+    const LevelGeom& g = c.a.lv[std::min(1, c.a.levels - 1)];
+    const int64_t pts = std::max(std::max(c.a.ref.n, c.ref_alt.n), 1);
+    const int64_t rows = std::min<int64_t>(g.H, g.H * std::min<int64_t>(ppc, pts) / pts + 16);
+    band = std::max(band, rows * g.W * ((variant & kCoopFloatPyr) ? 4 : 1));
+  }
   e = launch_coop_track(d_streams, d_work, grid(), dv_start + (size_t)slot * n, dv_out, slot, n, n_frames, seq0,
-                        tag_base, chunk, variant, spin_limit, stream);
+                        tag_base, chunk, variant, band, spin_limit, stream);
   tag_base += span;
   return e;
 }

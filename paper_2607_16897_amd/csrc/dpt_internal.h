@@ -269,8 +269,9 @@ struct CoopEngine {
   // Enqueue the track of every stream from start slot `slot`; its results land
   // in out(slot) once the stream reaches this point.  n_frames > 0: track that
   // many consecutive frames of each stream's window pyramids in one launch,
-  // frame f's results in out((slot + f) % kRing).
-  hipError_t launch(int spin_limit, int slot, int n_frames = 0);
+  // frame f's results in out((slot + f) % kRing).  in_order: every map lists its
+  // points by pixel index, so a chunk's lie in a band of rows.
+  hipError_t launch(int spin_limit, int slot, bool in_order, int n_frames = 0);
   // Whether every stream's results in ring slot `slot` have arrived (non-blocking).
   bool done(int slot) const;
   hipError_t clear_partials();
@@ -347,7 +348,7 @@ hipError_t launch_normal_equations(const TrackArgs& a, hipStream_t s);
 // n_frames > 0: that many frames from the streams' window pyramids.
 hipError_t launch_coop_track(const CoopStream* d_streams, const int2* d_work, int n_work, const StartSlot* start,
                              TrackOut* out_ring, int slot, int n_out, int n_frames, uint32_t seq0, uint32_t tag_base,
-                             int chunk, int variant, int spin_limit, hipStream_t s);
+                             int chunk, int variant, int64_t band, int spin_limit, hipStream_t s);
 // Set a pose history (two row-major 4x4 T_cw) on the stream.
 hipError_t launch_set_history(double* hist, const double* T0, const double* T1, hipStream_t s);
 // Pose histories of n streams: d_vals[24 s ..] = (older, newer) 3x4 into d_hists[s] (device arrays).
