@@ -376,39 +376,35 @@ __device__ __forceinline__ void wave_step() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// orthonormalize34 on T across the lanes: the same products and sums per element,
-// so the same result.  The second step runs only where the first began more than
-// 1e-7 off (it leaves 3/8 of the square): the products of tracked poses are
-// rotations to FP64 rounding, and two steps for each took a window of nine frames
-// from 396 to 401 us.  A loop, not two copies: it is in the kernel three times, and
-// the code of both cost a launch of one frame 1.3 us more.  M: 12 doubles of scratch.
-__device__ __forceinline__ void orthonormalize_wave(double* T, double* M, int t) {
+// One step of orthonormalize34 on T across the lanes: the same products and sums per
+// element, so the same result.  M: 12 doubles of scratch.  Whether an entry of R^T R
+// was more than 1e-7 off the identity's (the step leaves 3/8 of the square).
+__device__ __forceinline__ bool orthonormalize_step(double* T, double* M, int t) {
   const int r = (t >> 2) & 3, c = t & 3;
   const bool rot = t < 12 && c < 3;
-#pragma unroll 1
-  for (int it = 0; it < 2; ++it) {
-    wave_step();
-    // 3I - R^T R, element (r, c)
-    const double rtr = T[r] * T[c] + T[4 + r] * T[4 + c] + T[8 + r] * T[8 + c];
-    const double m = (r == c ? 3.0 : 0.0) - rtr;
-    const bool rough = __any(rot & (fabs(rtr - (r == c ? 1.0 : 0.0)) > 1e-7));
-    if (rot) M[t] = m;
-    wave_step();
-    const int q = min(r, 2);
-    const double v = 0.5 * (T[4 * q] * M[c] + T[4 * q + 1] * M[4 + c] + T[4 * q + 2] * M[8 + c]);
-    wave_step();
-    if (rot) T[t] = v;
-    if (!rough) break;
-  }
   wave_step();
+  // 3I - R^T R, element (r, c)
+  const double rtr = T[r] * T[c] + T[4 + r] * T[4 + c] + T[8 + r] * T[8 + c];
+  const double m = (r == c ? 3.0 : 0.0) - rtr;
+  if (rot) M[t] = m;
+  wave_step();
+  const int q = min(r, 2);
+  const double v = 0.5 * (T[4 * q] * M[c] + T[4 * q + 1] * M[4 + c] + T[4 * q + 2] * M[8 + c]);
+  wave_step();
+  if (rot) T[t] = v;
+  wave_step();
+  return __any(rot & (fabs(rtr - (r == c ? 1.0 : 0.0)) > 1e-7));
 }
 
 // Constant-velocity start P1 P0^-1 P1 from the pose history (h1 = P1, h0i =
 // P0^-1, in LDS), taken relative to the reference (P T_rw^-1, rwi = T_rw^-1), into
 // T0: the two products (P1 P0^-1) and (P1 T_rw^-1) side by side, then theirs, and
-// the rotation back on SO(3).  Two steps, as the host takes for a given pose: a
-// caller's history may hold poses rounded to a few decimals (off by 1e-2, one step
-// leaves 1e-4, two 1e-8).  One wave, t its lane.  m1, m2: 12 doubles of scratch each.
+// the rotation back on SO(3): two steps, as the host takes for a given pose, where the
+// first began more than 1e-7 off.  A caller's history may hold poses rounded to a few
+// decimals (off by 1e-2, one step leaves 1e-4, two 1e-8); the products of tracked poses
+// are rotations to FP64 rounding, and two steps for each took a window of nine frames
+// from 396 to 401 us.  The second is a turn of a loop, not a second copy of cold code.
+// One wave, t its lane.  m1, m2: 12 doubles of scratch each.
 __device__ __forceinline__ void predict_wave(double* T0, const double* rwi, const double* h0i, const double* h1,
                                              double* m1, double* m2, int t) {
   wave_step();
@@ -421,7 +417,9 @@ __device__ __forceinline__ void predict_wave(double* T0, const double* rwi, cons
   double v = 0.0;
   if (t < 12) v = compose34_elem(m1, m2, t);
   if (t < 12) T0[t] = v;
-  orthonormalize_wave(T0, m2, t);
+#pragma unroll 1
+  for (int it = 0; it < 2 && orthonormalize_step(T0, m2, t); ++it) {
+  }
 }
 
 // Start pose relative to the reference for this launch: the given one, one
@@ -884,7 +882,7 @@ __global__ __launch_bounds__(CH, 2) void coop_track_kernel(const CoopStream* __r
     // frame's estimate T_cw = T_rel T_rw, and the next frame's start.
     const auto finish_pose = [&] {
       if (lane < 12) sh_Tf[lane] = (double)Tl, sh_h0i[lane] = invert34_elem(sh_h1, lane), sh_h0[lane] = sh_h1[lane];
-      orthonormalize_wave(sh_Tf, sh_m2, lane);
+      orthonormalize_step(sh_Tf, sh_m2, lane), orthonormalize_step(sh_Tf, sh_m2, lane);
       if (lane < 12) sh_h1[lane] = compose34_elem(sh_Tf, sh_rw, lane);
       if (WIN && f + 1 < nf) predict_wave(sh_T0, sh_rwi, sh_h0i, sh_h1, sh_m1, sh_m2, lane);
       wave_step();
